@@ -115,8 +115,9 @@ int make_layout(const blstm_dims* d, Layout* lo) {
   L.dat_bytes = align256(L.write_dat ? (size_t)M * 8 * H * es : 0);
   L.DAT = a; a += (size_t)std::max(2, d->L) * L.dat_bytes;
   // per-step 16-row partials (per-step BPTT) or per-workgroup partials over
-  // all steps (persistent BPTT, 8-row workgroups)
-  L.dbp_bytes = align256((size_t)std::max<int64_t>((int64_t)d->T * cdiv(d->B, 16), cdiv(d->B, 8)) * 8 * H * 4);
+  // all steps (persistent BPTT)
+  // (8-row workgroups in bf16, 4-row ones in float32)
+  L.dbp_bytes = align256((size_t)std::max<int64_t>((int64_t)d->T * cdiv(d->B, 16), cdiv(d->B, es == 2 ? 8 : 4)) * 8 * H * 4);
   L.DBP = a; a += (size_t)std::max(2, d->L) * L.dbp_bytes;   // per layer when the bias sums wait for the last BPTT
   L.CSP = a; a = align256(a + (size_t)COLSUM_MAX_CHUNKS * 8 * H * 4);
   // split-K plans and partial buffers of the backward GEMMs
@@ -147,7 +148,7 @@ int make_layout(const blstm_dims* d, Layout* lo) {
   }
   L.SKP = a; a = align256(a + skp);
   L.SKP2 = a; a = align256(a + skp);   // split-K partials of the side-stream products
-  L.XCH = a; a = align256(a + persist_xch_bytes(d->B, d->H));   // recurrent step exchange
+  L.XCH = a; a = align256(a + (es == 2 ? persist_xch_bytes(d->B, d->H) : persist32_xch_bytes(d->B, d->H)));   // recurrent step exchange
   // recurrence status block, the last PERSIST_STATUS_BYTES of act_ws
   L.SYNC = a; a += PERSIST_STATUS_BYTES;
   L.act_bytes = a;

@@ -405,11 +405,10 @@ static bool step_rows_32(int H, int B) { return (int64_t)(H / 16) * cdiv(B, 32) 
 // Which recurrent kernels run.  Default (measured fastest on MI355X at the
 // paper's shapes): the persistent kernels for both passes;
 // ADPSGD_BLSTM_RECURRENCE=per-step (or ADPSGD_BLSTM_NO_PERSIST=1) the
-// per-step kernels.  The persistent kernels need bf16 and a W_hh slice that fits in LDS;
-// inside stream capture they are recorded as cooperative kernel nodes.
+// per-step kernels.  The persistent kernels need a W_hh slice that fits a
+// workgroup's registers (H up to 512).
 template <typename T>
 static bool use_persistent(int H, int steps, bool backward, hipStream_t s) {
-  if (!std::is_same<T, bf16>::value) return false;
   const char* off = getenv("ADPSGD_BLSTM_NO_PERSIST");
   if (off && atoi(off)) return false;
   const char* pol = getenv("ADPSGD_BLSTM_RECURRENCE");
@@ -422,7 +421,7 @@ static bool use_persistent(int H, int steps, bool backward, hipStream_t s) {
     const char* g = getenv("ADPSGD_BLSTM_GRAPH_PERSIST");
     if (g && !atoi(g)) return false;
   }
-  return persist_supported(H, steps);
+  return std::is_same<T, bf16>::value ? persist_supported(H, steps) : persist32_supported(H);
 }
 
 static PersistArgs persist_args(const Layout& lo, const bf16* W, char* ws, int l) {
@@ -437,6 +436,22 @@ static PersistArgs persist_args(const Layout& lo, const bf16* W, char* ws, int l
   pa.B = lo.B;
   pa.H = lo.H;
   pa.tag = (uint32_t)l;
+  return pa;
+}
+
+static Persist32Args persist32_args(const Layout& lo, const float* W, char* ws, int l) {
+  Persist32Args pa;
+  memset(&pa, 0, sizeof(pa));
+  pa.W = W;
+  pa.whh0 = lo.Whh[l][0];
+  pa.whh1 = lo.Whh[l][1];
+  pa.C = (float*)(ws + lo.C[l]);
+  pa.G = (float*)(ws + lo.G[l]);
+  pa.X = (uint64_t*)(ws + lo.XCH);
+  pa.status = (int*)(ws + lo.SYNC);
+  pa.Tn = lo.T;
+  pa.B = lo.B;
+  pa.H = lo.H;
   return pa;
 }
 
@@ -509,7 +524,23 @@ static int fwd_impl(const Layout& lo, const float* theta, const T* W, const floa
         gemm_launch<T, true, true, V, 4>("gemm_gx", s, A, Bw, M, 4 * H, Dl, 2, 1, epi);
     };
     if (!fuse) launch_gx();
-    if (persist) {
+    if constexpr (std::is_same<T, float>::value) {
+      if (persist) {
+        Persist32Args pa = persist32_args(lo, W, ws, l);
+        pa.Y = Yl; pa.Gx = GX; pa.tag0 = (uint32_t)l;
+        if (!xch_cleared) {
+          xch_cleared = persist32_clear(false, pa, s) == hipSuccess;
+          status_cleared = status_cleared || xch_cleared;
+        }
+        if (!status_cleared) {
+          (void)hipGetLastError();
+          if (persist_status_init((int*)(ws + lo.SYNC), s) != hipSuccess) return blstm_check_launch("blstm_fwd");
+          status_cleared = true;
+        }
+        if (xch_cleared && persist32_layer(false, pa, s) == hipSuccess) continue;
+        (void)hipGetLastError();
+      }
+    } else if (persist) {
       PersistArgs pa = persist_args(lo, (const bf16*)W, ws, l);
       pa.Y = (bf16*)Yl; pa.Gx = (bf16*)GX; pa.C = Cl; pa.G = (bf16*)Gl;
       if (fuse) {
@@ -643,6 +674,8 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
   // launch after the last BPTT (on per-layer bias partials)
   const bool dy_parts = defer && fuse_dy() && use_persistent<T>(H, lo.T, true, s) &&
                         persist_bwd_dy_partials_ok(H, B, lo.T);
+  // the row block of the persistent BPTT's bias partials
+  const int rows_wg = lp ? persist_rows_per_workgroup(H, B) : persist32_rows_per_workgroup(H, B);
   ReduceGroup pending_dy;   // the held dX reduction the next BPTT takes over
   pending_dy.n = 0;
   ColSumJob bias_jobs[MAX_LAYERS];
@@ -660,7 +693,17 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
     const float* Cl = (const float*)(ws + lo.C[l]);
     // BPTT over the chunk, both directions at once
     bool done = false, step_fused = false;
-    if (use_persistent<T>(H, lo.T, true, s)) {
+    if constexpr (!lp) {
+      if (use_persistent<T>(H, lo.T, true, s)) {
+        Persist32Args pa = persist32_args(lo, W, ws, l);
+        pa.tag0 = (uint32_t)(lo.L - 1 - l);   // the backward runs the layers top-down
+        pa.DA = DA; pa.DY = dY; pa.DBP = DBPl;
+        if (!xch_cleared) xch_cleared = persist32_clear(true, pa, s) == hipSuccess;
+        done = xch_cleared && persist32_layer(true, pa, s) == hipSuccess;
+        if (!done) (void)hipGetLastError();
+        step_fused = done;
+      }
+    } else if (use_persistent<T>(H, lo.T, true, s)) {
       PersistArgs pa = persist_args(lo, (const bf16*)W, ws, l);
       pa.tag = (uint32_t)(lo.L - 1 - l);   // the backward runs the layers top-down
       pa.DA = (bf16*)DA; pa.DY = dY; pa.C = (float*)Cl; pa.G = (bf16*)Gl;
@@ -741,7 +784,7 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
           g[ng++] = F32Job{opnd(DA, 8 * H, 8 * H, M), Bw, M, Dl, 8 * H, 1, lo.sp_dX[l], dst_dx, Dl, 0, part_dx};
         // db_ih = db_hh = sum over frames of da, from the BPTT kernel's
         // per-row-block partials, in the same reduction launch
-        const int dbp_rows = done ? (int)cdiv(B, persist_rows_per_workgroup(H, B)) : Tn * (int)cdiv(B, 16);
+        const int dbp_rows = done ? (int)cdiv(B, rows_wg) : Tn * (int)cdiv(B, 16);
         const ColSumJob cs{DBPl, dbp_rows, 2, 4 * H, 8 * H, 4 * H,
                            grad + lo.bih[l][0], grad + lo.bhh[l][0], lo.bih[l][1] - lo.bih[l][0]};
         const bool with_db = step_fused && colsum_job_ok(cs);
@@ -793,7 +836,7 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
     if (!db_done) {
       if (step_fused)
         colsum_parts("colsum_db", ss, DBPl,
-                     done ? (int)cdiv(B, persist_rows_per_workgroup(H, B)) : Tn * (int)cdiv(B, 16), 8 * H, 4 * H,
+                     done ? (int)cdiv(B, rows_wg) : Tn * (int)cdiv(B, 16), 8 * H, 4 * H,
                      lo.bih[l][1] - lo.bih[l][0], grad + lo.bih[l][0], grad + lo.bhh[l][0]);
       else
         colsum<T>("colsum_db", s, DA, M, 8 * H, 8 * H, csp, 4 * H, lo.bih[l][1] - lo.bih[l][0],

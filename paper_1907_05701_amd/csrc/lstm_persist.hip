@@ -938,7 +938,7 @@ size_t persist_lds_bytes(int H, bool backward, int RV) {
 // Compute units: one persistent workgroup fits per CU (its 8 waves hold
 // the W_hh slice in half of the register file and the rest in working
 // registers).
-static int persist_max_wg() {
+int persist_max_wg() {
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
@@ -965,27 +965,22 @@ static bool force_cooperative() {
   return e && e[0] == '1';
 }
 
-template <int RV, bool BWD>
-static hipError_t launch_one(PersistArgs a, hipStream_t s) {
-  const void* fn;
-  if constexpr (BWD) fn = (const void*)lstm_bwd_persist<RV>;
-  else fn = (const void*)lstm_fwd_persist<RV>;
-  const size_t lds = persist_lds_bytes(a.H, BWD, RV);
+hipError_t persist_launch(const char* name, const void* fn, dim3 grid, int threads, size_t lds, void* arg,
+                          hipStream_t s) {
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  const dim3 grid(2 * a.NS * (a.H / PU)), block(NTH);
-  void* args[] = {&a};
+  const dim3 block(threads);
+  void* args[] = {arg};
   // the whole grid resident at once? (per device; the answer depends only
   // on the kernel and its resources)
   bool fits = false;
   if (!force_cooperative()) {
     int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, NTH, lds) == hipSuccess)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, lds) == hipSuccess)
       fits = (int64_t)per_cu * persist_max_wg() >= (int64_t)grid.x;
     else
       (void)hipGetLastError();
   }
-  const char* name = BWD ? "lstm_rec_bwd_persist" : "lstm_rec_fwd_persist";
   const int slot = g_timing_on ? timing_pre(name, s) : -1;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   e = hipStreamIsCapturing(s, &cap);
@@ -1012,6 +1007,15 @@ static hipError_t launch_one(PersistArgs a, hipStream_t s) {
   }
   if (slot >= 0) timing_post(slot, s);
   return e;
+}
+
+template <int RV, bool BWD>
+static hipError_t launch_one(PersistArgs a, hipStream_t s) {
+  const void* fn;
+  if constexpr (BWD) fn = (const void*)lstm_bwd_persist<RV>;
+  else fn = (const void*)lstm_fwd_persist<RV>;
+  return persist_launch(BWD ? "lstm_rec_bwd_persist" : "lstm_rec_fwd_persist", fn, dim3(2 * a.NS * (a.H / PU)), NTH,
+                        persist_lds_bytes(a.H, BWD, RV), &a, s);
 }
 
 // Rows per workgroup and rows per launch: 8 rows (half of each MFMA tile
@@ -1052,16 +1056,16 @@ hipError_t persist_clear(bool backward, const PersistArgs& a, hipStream_t s) {
   // also initialises the status block of a fresh workspace
   const int64_t words = backward ? (int64_t)2 * 2 * ((chunk + 3) / 4) * (a.H / PU) * a.H
                                  : (int64_t)2 * 2 * chunk * (a.H / 4);
-  const int64_t n16 = words / 2;
-  hipLaunchKernelGGL(clear_exchange_kernel, dim3((unsigned)std::min<int64_t>(cdiv(n16, 256), 2048)), dim3(256), 0,
-                     s, (uint4*)a.X, n16, backward ? nullptr : a.status);
+  return persist_clear_words(a.X, words / 2, backward ? nullptr : a.status, s);
+}
+
+hipError_t persist_clear_words(void* p, int64_t n16, int* status, hipStream_t s) {
+  const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(cdiv(n16, 256), 2048));
+  hipLaunchKernelGGL(clear_exchange_kernel, dim3(grid), dim3(256), 0, s, (uint4*)p, n16, status);
   return hipGetLastError();
 }
 
-hipError_t persist_status_init(int* status, hipStream_t s) {
-  hipLaunchKernelGGL(clear_exchange_kernel, dim3(1), dim3(64), 0, s, (uint4*)nullptr, (int64_t)0, status);
-  return hipGetLastError();
-}
+hipError_t persist_status_init(int* status, hipStream_t s) { return persist_clear_words(nullptr, 0, status, s); }
 
 hipError_t persist_status_reset(int* status, hipStream_t s) {
   hipLaunchKernelGGL(status_reset_kernel, dim3(1), dim3(1), 0, s, status);

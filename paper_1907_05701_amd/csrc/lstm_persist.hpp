@@ -89,3 +89,44 @@ hipError_t persist_status_reset(int* status, hipStream_t s);
 // in the order they run (an exchange word tells its launch from the two
 // before it by the launch's position modulo 4).
 hipError_t persist_layer(bool backward, PersistArgs a, hipStream_t s);
+
+// ---------------------------------------------------------------------------
+// float32 persistent kernels (lstm_persist32.hip): the same split, exchange
+// protocol, status block and launch rules with float32 operands.
+// ---------------------------------------------------------------------------
+struct Persist32Args {
+  float* Y;             // forward: layer output [M][2H]
+  const float* W;       // parameters (flat layout)
+  int64_t whh0, whh1;   // element offsets of W_hh for the two directions
+  const float* Gx;      // forward: input projection incl. both biases [M][8H]
+  float* C;             // cell states [M][2H] (forward writes, backward reads)
+  float* G;             // gate pre-activations [M][2][H][4] (forward writes, backward reads)
+  float* DA;            // backward: gate pre-activation gradients [M][8H]
+  const float* DY;      // backward: gradient reaching the layer output [M][2H]
+  float* DBP;           // backward: sums of da over each workgroup's rows and all steps
+                        // [cdiv(B, persist32_rows_per_workgroup)][8H]
+  uint64_t* X;          // step-exchange words, persist32_xch_bytes
+  int* status;          // recurrence status block
+  uint32_t tag0;        // caller: the layer's position in the call; per launch: the tag before its first step's
+  int Tn, B, H;
+  int b0, rows, NS;     // filled in by persist32_layer
+};
+
+// True if these kernels handle this H (a multiple of 16 up to 512).
+bool persist32_supported(int H);
+int persist32_rows_per_workgroup(int H, int B);
+size_t persist32_xch_bytes(int B, int H);
+hipError_t persist32_clear(bool backward, const Persist32Args& a, hipStream_t s);
+hipError_t persist32_layer(bool backward, Persist32Args a, hipStream_t s);
+
+// Compute units of the current device (0: unknown); one persistent workgroup
+// runs on each.
+int persist_max_wg();
+// Launches a kernel whose workgroups wait for each other: plain when the
+// occupancy query shows the whole grid resident at once, else cooperative.
+// args: the kernel's only argument.
+hipError_t persist_launch(const char* name, const void* fn, dim3 grid, int threads, size_t lds, void* args,
+                          hipStream_t s);
+// Zeroes n16 16-byte pieces at p (may be none) and, if status is given,
+// initialises the status block of a fresh workspace.
+hipError_t persist_clear_words(void* p, int64_t n16, int* status, hipStream_t s);

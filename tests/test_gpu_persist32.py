@@ -1,0 +1,25 @@
+"""The float32 persistent recurrences against the float64 oracle, at the edges
+of their plan: members of 128, 64 and 32 units (H up to 128, 256, 512) with a
+partial last member, slices of 4, 8 and 16 rows with a partial last slice, more
+than one launch per layer, one and two steps (both exchange slots).  The
+tolerance is the float32 path's (tests/test_gpu_parity.py)."""
+
+import pytest
+
+from test_gpu_parity import FP32_TOL, run_step_and_compare
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("H,T,B", [
+    (16, 3, 1), (48, 2, 5), (128, 4, 9),               # one member, no exchange
+    (128, 2, 1030),                                    # one member, 8-row slices, two launches
+    (144, 3, 6), (240, 5, 130), (256, 3, 270),         # 64-unit members: partial last member, 4 and 8 rows, two launches
+    (272, 1, 3), (272, 4, 33), (512, 3, 62), (512, 2, 130),   # 32-unit members: 4, 8 and 16 rows, two launches
+], ids=lambda v: str(v))
+def test_float32_recurrence_plan_edges(gpu_lib, H, T, B):
+    run_step_and_compare(dict(L=2, D=24, H=H, P=16, K=30, T=T, B=B), "fp32", FP32_TOL, seed=17, check_update=False)
+
+
+def test_float32_recurrence_many_steps(gpu_lib):
+    run_step_and_compare(dict(L=1, D=8, H=288, P=8, K=10, T=70, B=7), "fp32", FP32_TOL, seed=18, check_update=False)
