@@ -98,6 +98,13 @@ __device__ __forceinline__ void p32_poll(uint64_t (&wv)[N], const uint64_t* base
   }
 }
 
+// Barrier of the steps: every thread's LDS accesses are done, while its global
+// stores and prefetches stay in flight (the fence of __syncthreads would wait
+// for them at each step).
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
 // LDS row pitch (floats) of a row operand of n k values: the 4 rows x 16 k
 // of one operand read fall in 64 distinct banks.
 __host__ __device__ static inline int p32_pitch(int n) { return (n + 63) / 64 * 64 + 16; }
@@ -105,7 +112,8 @@ __host__ __device__ static inline int p32_pitch(int n) { return (n + 63) / 64 * 
 // ---------------------------------------------------------------------------
 // Forward.
 // ---------------------------------------------------------------------------
-template <int NCB, int RT>
+// SOLO: one member (no exchange; h stays in LDS).
+template <int NCB, int RT, bool SOLO>
 __global__ __launch_bounds__(P32_THREADS) void lstm_fwd_persist32(const Persist32Args a) {
   extern __shared__ __attribute__((aligned(16))) char lds_raw[];
   constexpr int PU = 16 * NCB, KS = 8 / NCB, RV = 4 * RT, NCOL = 64 * NCB;
@@ -113,7 +121,7 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_fwd_persist32(const Persist3
   constexpr int RPI = P32_THREADS / NCOL;       // rows between a thread's items
   const int H = a.H, B = a.B, Tn = a.Tn;
   const int NG = 2 * a.NS;
-  const int g = blockIdx.x % NG, mem = blockIdx.x / NG, nmem = gridDim.x / NG;
+  const int g = blockIdx.x % NG, mem = blockIdx.x / NG;
   const int d = g & 1, s = g >> 1;
   const int u0 = mem * PU;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -121,25 +129,43 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_fwd_persist32(const Persist3
   const int KQ = (H + 16 * KS - 1) / (16 * KS) * 16;   // k values per part (whole groups of 16)
   const int k0 = ks * KQ;
 
-  // W_hh rows of this lane's gate column, k0 .. k0 + KQ (zeros past H)
+  // W_hh rows of this lane's gate column, k0 .. k0 + KQ (zeros past H), through
+  // a wave's own piece of LDS so that the global loads take whole lines (8
+  // rows of 32 k values per instruction; a lane loading its own row by itself
+  // touches 64 lines per instruction: 17.0 -> 10.6 us for a one-step launch
+  // at H = 512)
   float bw[P32_KW];
   {
-    const int unit = u0 + cb * 16 + (lane >> 2);
-    const float* row = a.W + (d ? a.whh1 : a.whh0) + ((int64_t)(lane & 3) * H + min(unit, H - 1)) * H;
+    constexpr int SP = 36;   // staging pitch (floats): 16-byte aligned rows
+    float* stg = (float*)lds_raw + w * 64 * SP;
+    const float* wd = a.W + (d ? a.whh1 : a.whh0);
 #pragma unroll
-    for (int i = 0; i < P32_KW / 4; ++i) {
-      const bool ok = unit < H && i * 4 < KQ && k0 + i * 4 < H;   // H is a multiple of 16
-      const f32x4u v = ok ? *(const f32x4u*)(row + k0 + i * 4) : f32x4u{0.f, 0.f, 0.f, 0.f};
+    for (int c = 0; c < P32_KW / 32; ++c) {
+      f32x4u v[8];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) bw[i * 4 + e] = v[e];
+      for (int i = 0; i < 8; ++i) {
+        const int cl = i * 8 + (lane >> 3), kk = c * 32 + (lane & 7) * 4;
+        const int un = u0 + cb * 16 + (cl >> 2);
+        const bool ok = un < H && kk < KQ && k0 + kk < H;   // H and KQ are multiples of 16
+        v[i] = ok ? *(const f32x4u*)(wd + ((int64_t)(cl & 3) * H + un) * H + k0 + kk) : f32x4u{0.f, 0.f, 0.f, 0.f};
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) *(f32x4*)&stg[(i * 8 + (lane >> 3)) * SP + (lane & 7) * 4] = v[i];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const f32x4 r = *(const f32x4*)&stg[lane * SP + j * 4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bw[c * 32 + j * 4 + e] = r[e];
+      }
     }
+    __syncthreads();   // the step buffers reuse this LDS
   }
 
   const int HS = p32_pitch(H);
   float* hl = (float*)lds_raw;        // h of the previous step [RV][HS]
   float* red = hl + RV * HS;          // products by k part [KS][RV][NCOL]
   for (int i = tid; i < RV * HS; i += P32_THREADS) hl[i] = 0.f;
-  __syncthreads();
+  lds_barrier();
 
   const int rowbase = a.b0 + s * RV, rend = a.b0 + a.rows;
   const int64_t slot_stride = (int64_t)2 * a.rows * H;
@@ -165,7 +191,7 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_fwd_persist32(const Persist3
 #pragma unroll
     for (int i = 0; i < IT; ++i) pre[i] = gxn[i];
     if (tau > 0) {
-      if (nmem > 1) {
+      if constexpr (!SOLO) {
         // h of the previous step: the slice's RV rows x H words are
         // contiguous; up to GB words per thread at a time
         constexpr int GB = RV < 8 ? RV : 8;
@@ -189,7 +215,7 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_fwd_persist32(const Persist3
           }
         }
       }
-      __syncthreads();
+      lds_barrier();
       f32x4 acc[RT];
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) acc[rt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -204,7 +230,7 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_fwd_persist32(const Persist3
       for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
         for (int r = 0; r < 4; ++r) red[(ks * RV + rt * 4 + r) * NCOL + cb * 64 + lane] = acc[rt][r];
-      __syncthreads();
+      lds_barrier();
 #pragma unroll
       for (int i = 0; i < IT; ++i) {
         float sum = red[(r0 + RPI * i) * NCOL + col];
@@ -223,37 +249,47 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_fwd_persist32(const Persist3
       const float ig = quad<QUAD_0>(act), fg = quad<QUAD_1>(act), gg = quad<QUAD_2>(act), og = quad<QUAD_3>(act);
       creg[i] = fg * creg[i] + ig * gg;
       hv[i] = og * tanhf_(creg[i]);
-      const int rl = r0 + RPI * i, row = rowbase + rl;
-      if (q == 0 && uok && row < rend) {
-        if (nmem > 1)
+    }
+    if (q == 0) {
+#pragma unroll
+      for (int i = 0; i < IT; ++i) {
+        const int rl = r0 + RPI * i, row = rowbase + rl;
+        if constexpr (SOLO) {
+          // (rows past the batch feed only themselves; a unit past H, a copy
+          // of the last one here, meets zero weights)
+          if (tau + 1 < Tn) hl[rl * HS + unit] = hv[i];
+        } else if (uok && row < rend) {
           p32_publish(xo + ((int64_t)d * a.rows + (row - a.b0)) * H + unit, hv[i], a.tag0 + tau + 1);
-        else
-          hl[rl * HS + unit] = hv[i];
+        }
       }
     }
+    // the prefetch before the stores: its wait then leaves them in flight
+    if (tau + 1 < Tn) load_gx(d ? Tn - 2 - tau : tau + 1);
 #pragma unroll
     for (int i = 0; i < IT; ++i) {
       const int row = rowbase + r0 + RPI * i;
       if (!uok || row >= rend) continue;
       const int64_t f = (int64_t)t * B + row;
       a.G[f * 8 * H + (int64_t)d * 4 * H + (int64_t)unit * 4 + q] = pre[i];
-      if (q == 1) a.C[f * 2 * H + (int64_t)d * H + unit] = creg[i];
-      if (q == 2) a.Y[f * 2 * H + (int64_t)d * H + unit] = hv[i];
+      if (q == 1 || q == 2) (q == 1 ? a.C : a.Y)[f * 2 * H + (int64_t)d * H + unit] = q == 1 ? creg[i] : hv[i];
     }
-    if (tau + 1 < Tn) load_gx(d ? Tn - 2 - tau : tau + 1);
   }
 }
 
 // ---------------------------------------------------------------------------
 // Backward (BPTT).
 // ---------------------------------------------------------------------------
-template <int NCB, int RT>
+// KS: k parts of the own gate rows; SOLO: one member (the partial sums stay
+// in LDS).
+template <int NCB, int RT, int KS, bool SOLO>
 __global__ __launch_bounds__(P32_THREADS) void lstm_bwd_persist32(const Persist32Args a) {
   extern __shared__ __attribute__((aligned(16))) char lds_raw[];
   constexpr int PU = 16 * NCB, RV = 4 * RT, NCOL = 64 * NCB;   // NCOL own gate rows
-  constexpr int KS = NCB / 2, CBS = 8 / KS;                    // k parts of 128 own rows, unit blocks of 64
+  constexpr int CBS = 8 / KS, KW = NCOL / KS;                  // unit blocks of 64; own rows per k part
+  static_assert(KW <= P32_KW && KW % 16 == 0, "W_hh slice in registers");
   constexpr int IT = RV * NCOL / P32_THREADS, RPI = P32_THREADS / NCOL;
-  constexpr int MPP = NCB == 2 ? 4 : NCB == 4 ? 2 : 1;         // partial sums per thread of a quad (at most)
+  constexpr int MEMS = SOLO ? 1 : NCB == 2 ? 16 : 4;           // members at most
+  constexpr int MPP = (MEMS * KS + 3) / 4;                     // partial sums per thread of a quad
   constexpr int AS = (NCOL + 63) / 64 * 64 + 16;
   const int H = a.H, B = a.B, Tn = a.Tn;
   const int NG = 2 * a.NS;
@@ -265,13 +301,13 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_bwd_persist32(const Persist3
   const int hu = cb * 64 + lane;   // hidden unit of this lane's product column
   const int parts = nmem * KS;
 
-  // W_hh[own gate row][hu], own row 4 (unit - u0) + gate, 128 rows of part ks
-  float bw[P32_KW];
+  // W_hh[own gate row][hu], own row 4 (unit - u0) + gate, the KW rows of part ks
+  float bw[KW];
   {
     const float* wd = a.W + (d ? a.whh1 : a.whh0) + min(hu, H - 1);
 #pragma unroll
-    for (int k = 0; k < P32_KW; ++k) {
-      const int unit = u0 + ks * (P32_KW / 4) + (k >> 2);
+    for (int k = 0; k < KW; ++k) {
+      const int unit = u0 + ks * (KW / 4) + (k >> 2);
       const bool ok = unit < H && hu < H;
       const float v = wd[((int64_t)(k & 3) * H + min(unit, H - 1)) * H];
       bw[k] = ok ? v : 0.f;
@@ -316,7 +352,7 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_bwd_persist32(const Persist3
 #pragma unroll
     for (int i = 0; i < IT; ++i) dhr[i] = 0.f;
     if (tau > 0) {
-      if (nmem > 1) {
+      if constexpr (!SOLO) {
         const uint64_t* src = a.X + ((tau - 1) & 1) * slot_stride;
         const uint32_t want = a.tag0 + tau;
         constexpr int IB = IT * MPP <= 8 ? IT : 8 / MPP;   // items gathered at a time
@@ -369,17 +405,17 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_bwd_persist32(const Persist3
       dbacc[i] += da[i];
       cc[i] = cpn[i];
     }
-    __syncthreads();   // own da complete (and, one member, the sums of dhl read)
+    lds_barrier();   // own da complete (and, one member, the sums of dhl read)
     if (tau + 1 < Tn) {
       f32x4 acc[RT];
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) acc[rt] = f32x4{0.f, 0.f, 0.f, 0.f};
-      const float* ab = alp + (lane & 3) * AS + ks * P32_KW + (lane >> 2);
+      const float* ab = alp + (lane & 3) * AS + ks * KW + (lane >> 2);
 #pragma unroll
-      for (int kg = 0; kg < P32_KW / 16; ++kg)
+      for (int kg = 0; kg < KW / 16; ++kg)
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) acc[rt] = mfma_rows4<16>(ab[rt * 4 * AS + kg * 16], &bw[kg * 16], acc[rt]);
-      if (nmem > 1) {
+      if constexpr (!SOLO) {
         uint64_t* xo = a.X + (tau & 1) * slot_stride + ((int64_t)d * parts + mem * KS + ks) * a.rows * H + hu;
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)
@@ -392,7 +428,8 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_bwd_persist32(const Persist3
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) dhl[(ks * RV + rt * 4 + r) * PU + hu] = acc[rt][r];
+          for (int r = 0; r < 4; ++r)
+            if (CBS * 64 <= PU || hu < PU) dhl[(ks * RV + rt * 4 + r) * PU + hu] = acc[rt][r];
       }
       fetch(tau + 1);
     }
@@ -402,7 +439,7 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_bwd_persist32(const Persist3
       if (uok && row < rend)
         a.DA[((int64_t)t * B + row) * 8 * H + (int64_t)d * 4 * H + (int64_t)q * H + unit] = da[i];
     }
-    if (nmem == 1) __syncthreads();   // the partial sums in LDS
+    if constexpr (SOLO) lds_barrier();   // the partial sums in LDS
   }
   // bias partials: the slice's rows in order
   __syncthreads();
@@ -423,17 +460,22 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_bwd_persist32(const Persist3
 namespace {
 struct Plan32 {
   int ncb, rt, members, chunk;   // column blocks per member, row tiles, members per group, rows per launch
+  int bks;                       // k parts of the backward
 };
 }  // namespace
 
-// Members as large as the registers allow (fewest words to exchange); slices
-// of 4 rows while they all fit the chip at one workgroup per CU, then of 8,
-// then of 16, in as many launches as it takes (members of 64 and
-// 128 units: at most 8 rows, whose cell registers fit beside the W_hh slice).
+// One member while its 4H gate rows fit (H up to 128: no exchange), of the
+// least width that holds them (a 64-cell layer on 64-unit members halves each
+// thread's cells and splits the products' k over all waves); else members as
+// large as the registers allow, 64 units up to 256 cells, 32 above.  Slices of
+// 4 rows while they all fit the chip at one workgroup per CU, then of 8, then
+// of 16 (32-unit members only: the cell registers of wider ones spill), in as
+// many launches as it takes.
 static bool plan32(int H, int B, Plan32* p) {
   const int cus = std::min(persist_max_wg(), 256);   // the exchange buffer is sized for 256
-  p->ncb = H <= 128 ? 8 : H <= 256 ? 4 : 2;
+  p->ncb = H <= 32 ? 2 : H <= 64 ? 4 : H <= 128 ? 8 : H <= 256 ? 4 : 2;
   p->members = (int)cdiv(H, 16 * p->ncb);
+  p->bks = p->members == 1 ? (p->ncb == 8 ? 4 : 8) : p->ncb / 2;
   const int slices = cus / (2 * p->members);
   if (slices < 1) return false;
   const int top = p->ncb == 2 ? 4 : 2;
@@ -463,33 +505,40 @@ hipError_t persist32_clear(bool backward, const Persist32Args& a, hipStream_t s)
   Plan32 p;
   if (!plan32(a.H, a.B, &p)) return hipErrorInvalidValue;
   int64_t words = 0;   // one member exchanges nothing
-  if (p.members > 1) words = (int64_t)2 * 2 * (backward ? p.members * (p.ncb / 2) : 1) * p.chunk * a.H;
+  if (p.members > 1) words = (int64_t)2 * 2 * (backward ? p.members * p.bks : 1) * p.chunk * a.H;
   if (backward && words == 0) return hipSuccess;
   return persist_clear_words(a.X, words / 2, backward ? nullptr : a.status, s);
 }
 
-template <int NCB, int RT>
+template <int NCB, int RT, int BKS, bool SOLO>
 static const void* fn32(bool backward) {
-  return backward ? (const void*)lstm_bwd_persist32<NCB, RT> : (const void*)lstm_fwd_persist32<NCB, RT>;
+  return backward ? (const void*)lstm_bwd_persist32<NCB, RT, BKS, SOLO> : (const void*)lstm_fwd_persist32<NCB, RT, SOLO>;
 }
 
 hipError_t persist32_layer(bool backward, Persist32Args a, hipStream_t s) {
   Plan32 p;
   if (!plan32(a.H, a.B, &p)) return hipErrorInvalidValue;
+  const bool solo = p.members == 1;
   const void* fn = nullptr;
-  switch (p.ncb * 8 + p.rt) {
-    case 2 * 8 + 1: fn = fn32<2, 1>(backward); break;
-    case 2 * 8 + 2: fn = fn32<2, 2>(backward); break;
-    case 2 * 8 + 4: fn = fn32<2, 4>(backward); break;
-    case 4 * 8 + 1: fn = fn32<4, 1>(backward); break;
-    case 4 * 8 + 2: fn = fn32<4, 2>(backward); break;
-    case 8 * 8 + 1: fn = fn32<8, 1>(backward); break;
-    case 8 * 8 + 2: fn = fn32<8, 2>(backward); break;
+  switch (p.ncb * 100 + p.rt * 10 + (solo ? 1 : 0)) {
+    case 210: fn = fn32<2, 1, 1, false>(backward); break;
+    case 220: fn = fn32<2, 2, 1, false>(backward); break;
+    case 240: fn = fn32<2, 4, 1, false>(backward); break;
+    case 410: fn = fn32<4, 1, 2, false>(backward); break;
+    case 420: fn = fn32<4, 2, 2, false>(backward); break;
+    case 211: fn = fn32<2, 1, 8, true>(backward); break;
+    case 221: fn = fn32<2, 2, 8, true>(backward); break;
+    case 241: fn = fn32<2, 4, 8, true>(backward); break;
+    case 411: fn = fn32<4, 1, 8, true>(backward); break;
+    case 421: fn = fn32<4, 2, 8, true>(backward); break;
+    case 811: fn = fn32<8, 1, 4, true>(backward); break;
+    case 821: fn = fn32<8, 2, 4, true>(backward); break;
     default: return hipErrorInvalidValue;
   }
   const int RV = 4 * p.rt, ncol = 64 * p.ncb;
-  const size_t lds = backward ? ((size_t)2 * RV * (ncol + 16) + (size_t)(p.ncb / 2) * RV * 16 * p.ncb) * 4
-                              : ((size_t)RV * p32_pitch(a.H) + (size_t)8 / p.ncb * RV * ncol) * 4;
+  size_t lds = backward ? ((size_t)2 * RV * (ncol + 16) + (size_t)p.bks * RV * 16 * p.ncb) * 4
+                        : ((size_t)RV * p32_pitch(a.H) + (size_t)8 / p.ncb * RV * ncol) * 4;
+  if (!backward) lds = std::max(lds, (size_t)8 * 64 * 36 * 4);   // W_hh staging
   for (int b0 = 0; b0 < a.B; b0 += p.chunk) {
     Persist32Args c = a;
     c.b0 = b0;

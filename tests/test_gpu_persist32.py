@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("H,T,B", [
-    (16, 3, 1), (48, 2, 5), (128, 4, 9),               # one member, no exchange
+    (16, 3, 1), (32, 4, 300), (48, 2, 5), (64, 5, 700), (80, 3, 6), (128, 4, 9),   # one member, no exchange
     (128, 2, 1030),                                    # one member, 8-row slices, two launches
     (144, 3, 6), (240, 5, 130), (256, 3, 270),         # 64-unit members: partial last member, 4 and 8 rows, two launches
     (272, 1, 3), (272, 4, 33), (512, 3, 62), (512, 2, 130),   # 32-unit members: 4, 8 and 16 rows, two launches
