@@ -1024,6 +1024,7 @@ static hipError_t launch_one(PersistArgs a, hipStream_t s) {
 // False if no launch fits.
 static bool persist_plan(int H, int B, int* RVo, int* chunko) {
   const int NM = H / PU;
+  if (NM < 1) return false;
   const int max_ns = std::min(persist_max_wg() / (2 * NM), PERSIST_MAX_SLICES);
   if (max_ns < 1) return false;
   int RV = (B + 7) / 8 <= max_ns ? 8 : 16;
