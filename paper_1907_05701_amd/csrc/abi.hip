@@ -107,13 +107,10 @@ int make_layout(const blstm_dims* d, Layout* lo) {
   L.WT = a; a = align256(a + (size_t)2 * d->L * 4 * H * H * es);
   L.WP0_bytes = es == 2 && d->D % 8 != 0 ? (size_t)2 * 4 * H * L.Dp0 * es : 0;
   L.WP0 = a; a = align256(a + L.WP0_bytes);
-  // bf16 with B % 8 == 0: the BPTT kernels also write da frame-contiguous
-  // (da^T), the A operand of the weight gradients
-  L.write_dat = es == 2 && d->B % 8 == 0;
-  // da^T [8H][M], one per layer (the weight gradients of every layer run
-  // after the last BPTT; the side-stream path alternates two of them)
-  L.dat_bytes = align256(L.write_dat ? (size_t)M * 8 * H * es : 0);
-  L.DAT = a; a += (size_t)std::max(2, d->L) * L.dat_bytes;
+  // bf16: da [M][8H], one per layer (the weight gradients of every layer run
+  // after the last BPTT); float32 uses the G_x scratch
+  L.da_bytes = es == 2 ? align256((size_t)M * 8 * H * es) : 0;
+  L.DA = a; a += (size_t)d->L * L.da_bytes;
   // per-step 16-row partials (per-step BPTT) or per-workgroup partials over
   // all steps (persistent BPTT)
   // (8-row workgroups in bf16, 4-row ones in float32)

@@ -14,15 +14,14 @@
 // offset, which the hardware returns as zeros.
 //
 // An MN-contiguous operand (element (mn, k) at k*ld + mn) is staged as it
-// lies: LDS rows of one k, 256 bytes (128 mn) each, one load instruction
-// filling 4 rows, chunk c of row k in slot c ^ mn_swz(k).  Its MFMA fragments
+// lies, in panels of 64 mn: LDS rows of one k, 128 bytes each, one load
+// instruction filling 8 rows, chunk c of row k in slot mn_slot(c, k).  Its MFMA fragments
 // come from gfx950's transposing LDS read (ds_read_b64_tr_b16): within each
 // 16-lane group, lane r points at 4 consecutive mn of k row r/4 and the
 // instruction hands lane i the 4 values of mn column i over those 4 k rows
 // (lane i, element j = lane 4j + i/4's element i%4).  Two such reads give a
-// lane its 8 consecutive k.  Such an operand may also come in k segments (a
-// power of two of rows, whole k-tiles, at a fixed stride): the two direction
-// blocks of W_ih.
+// lane its 8 consecutive k.  Such an operand may also come in two k segments
+// (whole k-tiles): the two direction blocks of W_ih.
 //
 // Per k-tile each workgroup waits for its own oldest tile (vmcnt), meets at
 // one barrier (which also retires the previous tile's LDS reads), refills the
@@ -38,11 +37,11 @@
 struct KcArgs {
   const bf16* A;
   int64_t lda, azs, arows;   // A rows m (< arows valid), batch stride azs
-  int asegsh;                // MN-contiguous A: k rows in segments of 2^asegsh (0: one segment) ...
-  int64_t asegs;             // ... whose starts are asegs elements apart
+  int64_t aseg;              // MN-contiguous A: k rows in two segments, the second from row aseg ...
+  int64_t asegs;             // ... asegs elements after the first (aseg 0: one segment)
   const bf16* B;
   int64_t ldb, bzs, brows;
-  int bsegsh;
+  int64_t bseg;
   int64_t bsegs;
   int64_t M, N, K, ksplit;   // k range of split s: [s*ksplit, min(K, (s+1)*ksplit))
   int splits, ntm, ntn;      // tiles along m and n
@@ -84,10 +83,10 @@ __device__ __forceinline__ int kc_slot(int c, int r) {
   else return c ^ ((((r >> 1) ^ (r >> 3)) & 1) | (((r >> 2) & 1) << 1));
 }
 
-// Slot of 16-byte chunk c (8 mn) in k row r of an MN-contiguous tile (16
-// chunks per 256-byte row): the 16 k rows one transposing read touches
-// (r & 3 and bit 3 of r vary) take distinct chunk pairs.
-__device__ __forceinline__ int mn_slot(int c, int r) { return c ^ (2 * ((r & 3) | (((r >> 3) & 1) << 2))); }
+// Slot of 16-byte chunk c (8 mn) in k row r of an MN-contiguous panel (8
+// chunks per 128-byte row): the k rows one transposing read touches (r & 3 and
+// bit 3 of r vary) take distinct 32-byte pieces of the 256-byte bank window.
+__device__ __forceinline__ int mn_slot(int c, int r) { return c ^ (2 * (((r >> 1) & 1) | (((r >> 3) & 1) << 1))); }
 
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
@@ -126,18 +125,19 @@ __device__ __forceinline__ void kc_lds_wait(bf16x8 (&f)[N]) {
 // side, BK deep), K-contiguous (KC) or MN-contiguous.
 template <bool KC, int BMN, int BK, int NW>
 struct KcOperand {
-  static constexpr int ROWB = KC ? BK * 2 : BMN * 2;        // LDS row bytes
+  static constexpr int ROWB = KC ? BK * 2 : 128;            // LDS row bytes
   static constexpr int CPR = ROWB / 16;                     // 16-byte chunks per row
   static constexpr int RPI = 64 / CPR;                      // rows per load instruction
-  static constexpr int LOADS = (KC ? BMN : BK) / RPI / NW;  // load instructions per wave per k-tile
-  static_assert(LOADS >= 1 && (KC ? BMN : BK) % (RPI * NW) == 0, "tile rows must split over the waves");
-  static_assert(KC || BMN == 128, "MN-contiguous tiles are 128 wide");
+  static constexpr int PANEL = BK * 128;                    // bytes of an MN-contiguous panel (64 mn)
+  static constexpr int LOADS = BMN * BK * 2 / 1024 / NW;    // load instructions per wave per k-tile
+  static_assert(LOADS >= 1 && BMN * BK * 2 % (1024 * NW) == 0, "tile rows must split over the waves");
+  static_assert(KC || (BMN % 64 == 0 && BK % 8 == 0), "MN-contiguous panels of 64");
 
   // base: the operand's batch base; mn0: tile's first MN row; ld: row pitch;
-  // mnrows: valid MN rows of this tile (KC) / MN extent left (MNC); segsh,
-  // segs: k rows of an MNC operand in segments of 2^segsh rows (at least BK,
-  // so no k-tile straddles two) whose starts are segs apart, or segsh = 0
-  __device__ __forceinline__ static void issue(const bf16* base, int64_t ld, int segsh, int64_t segs, int64_t mn0,
+  // mnrows: valid MN rows of this tile (KC) / MN extent left (MNC); seg, segs:
+  // k rows of an MNC operand from seg on (a multiple of BK, so no k-tile
+  // straddles it) start segs elements after the first, or seg = 0
+  __device__ __forceinline__ static void issue(const bf16* base, int64_t ld, int64_t seg, int64_t segs, int64_t mn0,
                                                int64_t mnrows, int64_t k0, int64_t kend, char* tile, int wid,
                                                int lane) {
     if constexpr (KC) {
@@ -153,15 +153,16 @@ struct KcOperand {
       }
     } else {
       // per-k-tile base keeps the offsets small for long operands
-      const int64_t kb = segsh ? (k0 >> segsh) * segs + (k0 & ((1LL << segsh) - 1)) * ld : k0 * ld;
+      const int64_t kb = seg && k0 >= seg ? segs + (k0 - seg) * ld : k0 * ld;
       const __amdgpu_buffer_rsrc_t r = dma_rsrc(base + kb + mn0);
       const int lr = lane / CPR, ls = lane % CPR;
 #pragma unroll
       for (int q = 0; q < LOADS; ++q) {
-        const int row = (q * NW + wid) * RPI + lr;   // k row within the tile
-        const int c = mn_slot(ls, row);
-        const bool ok = k0 + row < kend && c * 8 + 8 <= mnrows;
-        dma16(r, ok ? (uint32_t)((row * ld + c * 8) * 2) : DMA_OFF_NONE, tile + (q * NW + wid) * 1024);
+        const int ins = q * NW + wid, panel = ins / (BK / RPI);
+        const int row = ins % (BK / RPI) * RPI + lr;   // k row within the tile
+        const int mn = panel * 64 + mn_slot(ls, row) * 8;
+        const bool ok = k0 + row < kend && mn + 8 <= mnrows;
+        dma16(r, ok ? (uint32_t)((row * ld + mn) * 2) : DMA_OFF_NONE, tile + ins * 1024);
       }
     }
   }
@@ -178,7 +179,7 @@ struct KcOperand {
 #pragma unroll
       for (int hh = 0; hh < 2; ++hh) {
         const int k = ks * 32 + 8 * g + 4 * hh + (r >> 2);
-        const char* pa = tile + k * ROWB + mn_slot(mn >> 3, k) * 16 + (mn & 7) * 2;
+        const char* pa = tile + (mn >> 6) * PANEL + k * ROWB + mn_slot((mn >> 3) & 7, k) * 16 + (mn & 7) * 2;
         h[hh] = kc_read_tr(pa);
       }
       return bf16x8{h[0][0], h[0][1], h[0][2], h[0][3], h[1][0], h[1][1], h[1][2], h[1][3]};
@@ -215,8 +216,8 @@ __device__ __forceinline__ void kc_gemm_tile(const KcArgs& p, const Epi& epi, in
   auto issue = [&](int j) {
     const int64_t k0 = kbeg + (int64_t)j * BK;
     char* st = kc_lds + (j % STAGES) * STAGE;
-    OA::issue(abase, p.lda, p.asegsh, p.asegs, m0, arows, k0, kend, st, wid, lane);
-    OB::issue(bbase, p.ldb, p.bsegsh, p.bsegs, n0, brows, k0, kend, st + TA, wid, lane);
+    OA::issue(abase, p.lda, p.aseg, p.asegs, m0, arows, k0, kend, st, wid, lane);
+    OB::issue(bbase, p.ldb, p.bseg, p.bsegs, n0, brows, k0, kend, st + TA, wid, lane);
   };
 
   f32x4 acc[FM][FN];
@@ -261,8 +262,14 @@ __device__ __forceinline__ void kc_gemm_tile(const KcArgs& p, const Epi& epi, in
     epi.template apply<FM, FN>(z, sp, m0 + wm * (BM / WM), n0 + wn * (BN / WN), acc, lane);
 }
 
+// Waves per SIMD of a tile shape: the workgroups whose stages fit 160 KB of LDS.
+template <int BM, int BN, int WM, int WN, int STAGES, int BK>
+struct KcOcc {
+  static constexpr int v = 160 * 1024 / ((BM + BN) * BK * 2 * STAGES) * WM * WN / 4;
+};
+
 template <int BM, int BN, int WM, int WN, int STAGES, int BK, bool AKC, bool BKC, class Epi>
-__global__ __launch_bounds__(WM * WN * 64, WM * WN / 2) void gemm_kc_kernel(const KcArgs p, const Epi epi) {
+__global__ __launch_bounds__(WM * WN * 64, (KcOcc<BM, BN, WM, WN, STAGES, BK>::v)) void gemm_kc_kernel(const KcArgs p, const Epi epi) {
   kc_gemm_tile<BM, BN, WM, WN, STAGES, BK, AKC, BKC, Epi>(p, epi, blockIdx.x);
 }
 
@@ -279,7 +286,7 @@ struct KcGroup {
 };
 
 template <int BM, int BN, int WM, int WN, int STAGES, int BK, bool AKC, bool BKC, class Epi>
-__global__ __launch_bounds__(WM * WN * 64, WM * WN / 2) void gemm_kc_group_kernel(const KcGroup<Epi> g) {
+__global__ __launch_bounds__(WM * WN * 64, (KcOcc<BM, BN, WM, WN, STAGES, BK>::v)) void gemm_kc_group_kernel(const KcGroup<Epi> g) {
   // the product index: every start compared at once (the loads are
   // independent, so they issue together)
   int i = 0;
@@ -292,7 +299,7 @@ __global__ __launch_bounds__(WM * WN * 64, WM * WN / 2) void gemm_kc_group_kerne
 // (each alone would leave part of its last round of the chip idle): the
 // first owns workgroups [0, n1) (n1 a multiple of 8), the second the rest.
 template <int BM, int BN, int WM, int WN, int STAGES, int BK, bool AKC1, bool BKC1, bool AKC2, bool BKC2, class Epi>
-__global__ __launch_bounds__(WM * WN * 64, WM * WN / 2) void gemm_kc_pair_kernel(const KcArgs p1, const Epi e1,
+__global__ __launch_bounds__(WM * WN * 64, (KcOcc<BM, BN, WM, WN, STAGES, BK>::v)) void gemm_kc_pair_kernel(const KcArgs p1, const Epi e1,
                                                                              const KcArgs p2, const Epi e2, int n1) {
   if ((int)blockIdx.x < n1)
     kc_gemm_tile<BM, BN, WM, WN, STAGES, BK, AKC1, BKC1, Epi>(p1, e1, (int)blockIdx.x);
@@ -303,17 +310,15 @@ __global__ __launch_bounds__(WM * WN * 64, WM * WN / 2) void gemm_kc_pair_kernel
 // Whether an operand can go through the direct-to-LDS path: no gate
 // interleave, 16-byte aligned rows and batch strides, the whole k range inside
 // the operand; MN-contiguous operands also need an MN extent that is a
-// multiple of 8 (whole 16-byte chunks), and may come in k segments of a power
-// of two of at least 64 rows (whole k-tiles); K-contiguous ones may not be
-// segmented.
+// multiple of 8 (whole 16-byte chunks), and may come in two k segments, the
+// first of a multiple of 64 rows (whole k-tiles); K-contiguous ones need a k
+// range of whole chunks and may not be segmented.
 static inline bool kc_operand_ok(const Opnd& o, int64_t K, bool kc) {
   const bool plain = o.ilH == 0 && o.ld % 8 == 0 && o.zstride % 8 == 0 && ((uintptr_t)o.base & 15) == 0;
-  if (kc) return plain && o.seg == 0 && o.ext >= K;
-  const bool segok = o.seg == 0 || (o.seg >= 64 && (o.seg & (o.seg - 1)) == 0 && o.segstride % 8 == 0);
+  if (kc) return plain && K % 8 == 0 && o.seg == 0 && o.ext >= K;
+  const bool segok = o.seg == 0 || (o.seg % 64 == 0 && K <= 2 * o.seg && o.segstride % 8 == 0);
   return plain && o.rows >= K && o.ext % 8 == 0 && segok;
 }
-
-static inline int kc_seg_shift(const Opnd& o) { return o.seg > 0 ? __builtin_ctzll((unsigned long long)o.seg) : 0; }
 
 static constexpr int kc_group_rows = 4;   // measured best at the learner-step shapes
 
@@ -326,8 +331,8 @@ static inline KcArgs kc_args(const Opnd& A, const Opnd& B, int64_t M, int64_t N,
   // epilogue drops)
   p.A = (const bf16*)A.base; p.lda = A.ld; p.azs = A.zstride; p.arows = AKC ? std::min<int64_t>(A.rows, M) : A.ext;
   p.B = (const bf16*)B.base; p.ldb = B.ld; p.bzs = B.zstride; p.brows = BKC ? std::min<int64_t>(B.rows, N) : B.ext;
-  p.asegsh = AKC ? 0 : kc_seg_shift(A); p.asegs = A.segstride;
-  p.bsegsh = BKC ? 0 : kc_seg_shift(B); p.bsegs = B.segstride;
+  p.aseg = AKC ? 0 : A.seg; p.asegs = A.segstride;
+  p.bseg = BKC ? 0 : B.seg; p.bsegs = B.segstride;
   p.M = M; p.N = N; p.K = K;
   p.ksplit = splits > 1 ? rup(cdiv(K, splits), C::BK) : (K > 0 ? K : 1);
   p.splits = splits;
@@ -376,7 +381,7 @@ static inline bool kc_tall(int64_t M, int64_t N, int batches, int splits) {
 }
 // Whether a product can take the direct-to-LDS kernel.
 static inline bool kc_eligible(const Opnd& A, const Opnd& B, int64_t K, bool akc, bool bkc) {
-  return K % 8 == 0 && kc_operand_ok(A, K, akc) && kc_operand_ok(B, K, bkc);
+  return kc_operand_ok(A, K, akc) && kc_operand_ok(B, K, bkc);
 }
 
 // GEMM dispatch: bf16 operands with 16-byte aligned rows go to the
@@ -442,8 +447,7 @@ static inline bool gemm_kc_group_launch_cfg(const char* name, hipStream_t s, int
   g.n = n;
   int start = 0;
   for (int i = 0; i < n; ++i) {
-    if (it[i].K % 8 != 0 || !kc_operand_ok(it[i].A, it[i].K, AKC) || !kc_operand_ok(it[i].B, it[i].K, BKC))
-      return false;
+    if (!kc_eligible(it[i].A, it[i].B, it[i].K, AKC, BKC)) return false;
     g.p[i] = kc_args<C, AKC, BKC>(it[i].A, it[i].B, it[i].M, it[i].N, it[i].K, it[i].batches, it[i].splits);
     g.e[i] = epi[i];
     g.start[i] = start;

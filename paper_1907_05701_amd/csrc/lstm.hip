@@ -172,7 +172,6 @@ struct RecBwdArgs {
   const T* G;        // saved gate pre-activations [M][2][H][4]
   const float* C;    // saved cell states [M][2H]
   float* DC;         // carried cell gradient [2][B][H]
-  T* DAT;            // optional: da also written frame-contiguous, [8H][M]
   float* DBP;        // optional: per-(step, 16-row block) sums of da, [Tn][B/16][8H]
   int64_t M;
   int Tn, B, H, tau;
@@ -278,21 +277,6 @@ __global__ __launch_bounds__(256) void lstm_rec_bwd_step(const RecBwdArgs<T> a) 
     T* da = a.DA + row * 8 * H + (int64_t)d * 4 * H + u;
 #pragma unroll
     for (int g = 0; g < 4; ++g) da[g * H] = from_f32<T>(dav[r][g]);
-  }
-  const int b0 = rb * 16 * MBK + mb * 16 + (lane >> 4) * 4;
-  if (a.DAT && b0 < B) {
-    // 4 consecutive frames of one gate row: one 8-byte store (B % 4 == 0)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      T* p = a.DAT + ((int64_t)d * 4 * H + g * H + u) * a.M + (int64_t)t * B + b0;
-      if constexpr (sizeof(T) == 2) {
-        const bf16 v[4] = {(bf16)dav[0][g], (bf16)dav[1][g], (bf16)dav[2][g], (bf16)dav[3][g]};
-        *(uint2*)p = *(const uint2*)v;
-      } else {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) p[r] = from_f32<T>(dav[r][g]);
-      }
-    }
   }
   if (a.DBP) {
     // bias gradient partial: the 16 rows of this block, in a fixed order
@@ -430,7 +414,8 @@ static PersistArgs persist_args(const Layout& lo, const bf16* W, char* ws, int l
   pa.W = W;
   pa.whh0 = lo.Whh[l][0];
   pa.whh1 = lo.Whh[l][1];
-  pa.X = (uint64_t*)(ws + lo.XCH);
+  pa.place = (uint64_t*)(ws + lo.XCH);
+  pa.X = pa.place + PERSIST_PLACE_WORDS;
   pa.status = (int*)(ws + lo.SYNC);
   pa.Tn = lo.T;
   pa.B = lo.B;
@@ -447,7 +432,8 @@ static Persist32Args persist32_args(const Layout& lo, const float* W, char* ws, 
   pa.whh1 = lo.Whh[l][1];
   pa.C = (float*)(ws + lo.C[l]);
   pa.G = (float*)(ws + lo.G[l]);
-  pa.X = (uint64_t*)(ws + lo.XCH);
+  pa.place = (uint64_t*)(ws + lo.XCH);
+  pa.X = pa.place + PERSIST_PLACE_WORDS;
   pa.status = (int*)(ws + lo.SYNC);
   pa.Tn = lo.T;
   pa.B = lo.B;
@@ -618,7 +604,6 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
   const int64_t M = lo.M;
   const int H = lo.H, B = lo.B, Tn = lo.T;
   T* WT = (T*)(ws + lo.WT);
-  T* DA = (T*)(ws + lo.GX);
   float* DC = (float*)(ws + lo.DC);
   float* part = (float*)(ws + lo.SKP);
   float* csp = (float*)(ws + lo.CSP);
@@ -648,24 +633,23 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
     have_wt = true;
   };
   if (!use_persistent<T>(H, lo.T, true, s) || persist_bwd_needs_wt(H, B)) make_copies();
-  // weight gradients on the side stream (bf16 per-step BPTT writing da^T):
-  // layer l's buffers (da^T, bias partials, split-K partials) alternate by
-  // layer parity, so BPTT of layer l waits only for the side work of l+2
+  // weight gradients on the side stream (bf16 per-step BPTT): layer l's bias
+  // partials alternate by layer parity, so BPTT of layer l waits only for the
+  // side work of l+2
   SideStream* side = nullptr;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(s, &cap) != hipSuccess) { (void)hipGetLastError(); cap = hipStreamCaptureStatusActive; }
   // not under stream capture: replaying graphs with these parallel branches
   // measured far slower on MI355X than the serial graph
-  if (lp && lo.write_dat && cap == hipStreamCaptureStatusNone && !use_persistent<T>(H, lo.T, true, s))
+  if (lp && cap == hipStreamCaptureStatusNone && !use_persistent<T>(H, lo.T, true, s))
     side = side_stream();
   hipStream_t ss = side ? side->st : s;
   float* part_side = side ? (float*)(ws + lo.SKP2) : part;
-  // bf16 with da^T and no side stream: each layer's weight-gradient products
-  // wait for one grouped launch after the last BPTT (their da^T kept per
-  // layer), so a layer's own launch after its BPTT holds only dX, the
+  // bf16 without the side stream: each layer's weight-gradient products wait
+  // for one grouped launch after the last BPTT (da is kept per layer), so a layer's own launch after its BPTT holds only dX, the
   // product the next BPTT needs; the deferred products all have about the
   // same k length and fill whole rounds of the chip together
-  const bool defer = lp && lo.write_dat && !side;
+  const bool defer = lp && !side;
   F32Job deferred[2 * MAX_LAYERS];
   int nd = 0;
   // with the persistent BPTT, a layer's dX stays as its split-K partial
@@ -683,7 +667,7 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
   const float* dY = dytop;
   for (int l = lo.L - 1; l >= 0; --l) {
     const int par = side ? (l & 1) : 0;
-    T* DATl = (T*)(ws + lo.DAT + (defer ? l : par) * lo.dat_bytes);
+    T* DA = lp ? (T*)(ws + lo.DA + l * lo.da_bytes) : (T*)(ws + lo.GX);
     float* DBPl = (float*)(ws + lo.DBP + (dy_parts ? l : par) * lo.dbp_bytes);
     if (side && l + 2 < lo.L) (void)hipStreamWaitEvent(s, side->dw_done[l + 2], 0);
     const T* Xl = l == 0 ? (const T*)(ws + lo.X0) : (const T*)(ws + lo.Y[l - 1]);
@@ -708,9 +692,7 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
       pa.tag = (uint32_t)(lo.L - 1 - l);   // the backward runs the layers top-down
       pa.DA = (bf16*)DA; pa.DY = dY; pa.C = (float*)Cl; pa.G = (bf16*)Gl;
       pa.WT = have_wt ? (const bf16*)(WT + (int64_t)(2 * l) * 4 * H * H) : nullptr;
-      pa.DAT = lo.write_dat ? (bf16*)DATl : nullptr;
       pa.DBP = DBPl;
-      pa.M = M;
       if (pending_dy.n == 1) {
         pa.DYP = pending_dy.j[0].part;
         pa.ndy = pending_dy.j[0].splits;
@@ -730,9 +712,7 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
       RecBwdArgs<T> rb;
       rb.DA = DA; rb.WT0 = WT + (int64_t)(2 * l) * 4 * H * H; rb.WT1 = WT + (int64_t)(2 * l + 1) * 4 * H * H;
       rb.DY = dY; rb.G = Gl; rb.C = Cl; rb.DC = DC; rb.Tn = Tn; rb.B = B; rb.H = H;
-      rb.DAT = lo.write_dat ? DATl : nullptr;
       rb.DBP = DBPl;
-      rb.M = M;
       const dim3 grid(H / 16, (unsigned)cdiv(B, 16), 2);
       TimedRun timed("lstm_rec_bwd", s, Tn);
       for (int tau = 0; tau < Tn; ++tau) {
@@ -750,86 +730,78 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
     float* part_hh = (float*)((char*)part_side + lo.skp_hh[l]);
     float* part_dx = (float*)((char*)part + lo.skp_dx[l]);
     float* dst_dx = (dY == (const float*)(ws + lo.DYa)) ? (float*)(ws + lo.DYb) : (float*)(ws + lo.DYa);
-    bool dw_done = false, dx_done = l == 0, db_done = false;
+    bool dx_done = l == 0, db_done = false;
     // W_ih of both directions as the dX product's B operand, read as it lies
     // (k = gate row of direction d in segment d, n = input unit)
     Opnd Bw = opnd(W + lo.Wih[l][0], Dl, Dl, 8 * H);
     Bw.seg = 4 * H;
     Bw.segstride = lo.Wih[l][1] - lo.Wih[l][0];
+    // dW_ih[d] = da_d^T X_l  (4H x D_l, reduction over all frames), and
+    // dW_hh[d] = sum_t da_d[t]^T h_d[t_prev] (frames shifted by one step, the
+    // forward direction pairing t with t-1, the reverse one t with t+1); every
+    // operand as it lies (frame rows)
+    const Opnd Aw = opnd(DA, 8 * H, 4 * H, M, 4 * H);
+    const Opnd Bx = opnd(Xl, Dpl, Dpl, M);
+    const Opnd Ah = opnd(DA + (int64_t)B * 8 * H, 8 * H, 4 * H, Kr, 4 * H - (int64_t)B * 8 * H);
+    const Opnd Bh = opnd(Yl, 2 * H, H, Kr, (int64_t)B * 2 * H + H);
     if constexpr (lp) {
-      if (lo.write_dat) {
-        // A: da^T (frame-contiguous, written by the BPTT kernel); B: the layer
-        // input X_l and output h_l as they lie (frame rows).
-        // dW_ih[d] = da_d^T X_l  (4H x D_l, reduction over all frames);
-        // dW_hh[d] = sum_t da_d[t]^T h_d[t_prev] (the forward direction pairs
-        // frame t with t-1, the reverse one t with t+1);
-        // without the side stream also dX_l (below), all in one launch
-        T* DAT = DATl;
-        F32Job g[3];
-        g[0] = F32Job{opnd(DAT, M, (int)M, 4 * H, 4 * H * M), opnd(Xl, Dpl, Dpl, M), 4 * H, Dl, M, 2,
-                      lo.sp_dWih[l], grad + lo.Wih[l][0], Dl, lo.Wih[l][1] - lo.Wih[l][0], part_ih};
-        g[1] = F32Job{opnd(DAT + B, M, (int)Kr, 4 * H, 4 * H * M - B), opnd(Yl, 2 * H, H, Kr, (int64_t)B * 2 * H + H),
-                      4 * H, H, Kr, 2, lo.sp_dWhh[l], grad + lo.Whh[l][0], H, lo.Whh[l][1] - lo.Whh[l][0], part_hh};
-        // the whole k range per tile (the deferred launch has tiles enough;
-        // the side-stream path does the same, so that both sum alike)
-        g[0].splits = g[1].splits = 1;
-        int ng = 2;
-        if (defer) {
-          deferred[nd++] = g[0];
-          deferred[nd++] = g[1];
-          ng = 0;
-        }
-        const bool dx_here = !side && l > 0;
-        if (dx_here)
-          g[ng++] = F32Job{opnd(DA, 8 * H, 8 * H, M), Bw, M, Dl, 8 * H, 1, lo.sp_dX[l], dst_dx, Dl, 0, part_dx};
-        // db_ih = db_hh = sum over frames of da, from the BPTT kernel's
-        // per-row-block partials, in the same reduction launch
-        const int dbp_rows = done ? (int)cdiv(B, rows_wg) : Tn * (int)cdiv(B, 16);
-        const ColSumJob cs{DBPl, dbp_rows, 2, 4 * H, 8 * H, 4 * H,
-                           grad + lo.bih[l][0], grad + lo.bhh[l][0], lo.bih[l][1] - lo.bih[l][0]};
-        const bool with_db = step_fused && colsum_job_ok(cs);
-        if (dy_parts && with_db) {
-          // the bias sums wait for the last BPTT; dX (if any) keeps its
-          // partials for the next BPTT when it is split
-          bias_jobs[nbias++] = cs;
-          db_done = true;
-          ReduceGroup held;
-          if (ng == 0 || gemm_f32_group<true, false>("gemm_bwd_group", ss, ng, g, nullptr, &held)) {
-            if (ng > 0 && held.n == 1) pending_dy = held;
-            else if (ng > 0) reduce_group_launch(ss, held);
-          } else {
-            for (int i = 0; i < ng; ++i)
-              gemm_f32<T, true, false, V, V>(i == ng - 1 && dx_here ? "gemm_dx" : (i == 0 ? "gemm_dwih" : "gemm_dwhh"),
-                                             ss, g[i].A, g[i].B, g[i].M, g[i].N, g[i].K, g[i].batches, g[i].splits,
-                                             g[i].dst, g[i].ld, g[i].dst_zstride, g[i].part);
-          }
-        } else if (ng == 0) {
-          // (layer 0, weight gradients deferred: the bias sums alone, by the
-          // same reduction)
-          db_done = with_db && colsum_job_launch("splitk_reduce_group", ss, cs);
-        } else if (gemm_f32_group<true, false>("gemm_bwd_group", ss, ng, g, with_db ? &cs : nullptr)) {
-          db_done = with_db;
-        } else {
-          for (int i = 0; i < ng; ++i)
-            gemm_f32<T, true, false, V, V>(i == ng - 1 && dx_here ? "gemm_dx" : (i == 0 ? "gemm_dwih" : "gemm_dwhh"),
-                                           ss, g[i].A, g[i].B, g[i].M, g[i].N, g[i].K, g[i].batches, g[i].splits,
-                                           g[i].dst, g[i].ld, g[i].dst_zstride, g[i].part);
-        }
-        dx_done = dx_done || dx_here;
-        dw_done = true;
+      // without the side stream also dX_l (below), in the layer's own launch
+      F32Job g[3];
+      g[0] = F32Job{Aw, Bx, 4 * H, Dl, M, 2, lo.sp_dWih[l], grad + lo.Wih[l][0], Dl, lo.Wih[l][1] - lo.Wih[l][0],
+                    part_ih};
+      g[1] = F32Job{Ah, Bh, 4 * H, H, Kr, 2, lo.sp_dWhh[l], grad + lo.Whh[l][0], H, lo.Whh[l][1] - lo.Whh[l][0],
+                    part_hh};
+      // the whole k range per tile (the deferred launch has tiles enough;
+      // the side-stream path does the same, so that both sum alike)
+      g[0].splits = g[1].splits = 1;
+      const bool dx_here = !side && l > 0;
+      if (dx_here)
+        g[2] = F32Job{opnd(DA, 8 * H, 8 * H, M), Bw, M, Dl, 8 * H, 1, lo.sp_dX[l], dst_dx, Dl, 0, part_dx};
+      // db_ih = db_hh = sum over frames of da, from the BPTT kernel's
+      // per-row-block partials, in a reduction launch
+      const int dbp_rows = done ? (int)cdiv(B, rows_wg) : Tn * (int)cdiv(B, 16);
+      const ColSumJob cs{DBPl, dbp_rows, 2, 4 * H, 8 * H, 4 * H,
+                         grad + lo.bih[l][0], grad + lo.bhh[l][0], lo.bih[l][1] - lo.bih[l][0]};
+      const bool with_db = step_fused && colsum_job_ok(cs);
+      bool held_db = false;
+      if (dy_parts && with_db) {
+        // the bias sums wait for the last BPTT; dX (if any) keeps its
+        // partials for the next BPTT when it is split
+        bias_jobs[nbias++] = cs;
+        db_done = held_db = true;
       }
-    }
-    if (!dw_done) {
-      // dW_ih[d] = da_d^T X_l  (4H x D_l, reduction over all frames)
-      const Opnd A = opnd(DA, 8 * H, 4 * H, M, 4 * H);
-      const Opnd Bx = opnd(Xl, Dpl, Dpl, M);
-      gemm_f32<T, false, false, V, V>("gemm_dwih", s, A, Bx, 4 * H, Dl, M, 2, lo.sp_dWih[l],
+      const ColSumJob* csj = with_db && !held_db ? &cs : nullptr;
+      if (side) {
+        if (gemm_f32_group<false, false>("gemm_bwd_group", ss, 2, g, csj)) {
+          db_done = csj != nullptr;
+        } else {
+          for (int i = 0; i < 2; ++i)
+            gemm_f32<T, false, false, V, V>(i == 0 ? "gemm_dwih" : "gemm_dwhh", ss, g[i].A, g[i].B, g[i].M, g[i].N,
+                                            g[i].K, g[i].batches, 1, g[i].dst, g[i].ld, g[i].dst_zstride, g[i].part);
+        }
+      } else {
+        deferred[nd++] = g[0];
+        deferred[nd++] = g[1];
+        if (dx_here) {
+          ReduceGroup held;
+          if (gemm_f32_group<true, false>("gemm_bwd_group", s, 1, &g[2], csj, held_db ? &held : nullptr)) {
+            db_done = db_done || csj != nullptr;
+            if (held_db && held.n == 1) pending_dy = held;
+            else if (held_db) reduce_group_launch(s, held);
+          } else {
+            gemm_f32<T, true, false, V, V>("gemm_dx", s, g[2].A, g[2].B, g[2].M, g[2].N, g[2].K, 1, g[2].splits,
+                                           g[2].dst, g[2].ld, 0, g[2].part);
+          }
+        } else if (csj) {
+          // (layer 0: the bias sums alone, by the same reduction)
+          db_done = colsum_job_launch("splitk_reduce_group", s, cs);
+        }
+      }
+      dx_done = dx_done || dx_here;
+    } else {
+      gemm_f32<T, false, false, V, V>("gemm_dwih", s, Aw, Bx, 4 * H, Dl, M, 2, lo.sp_dWih[l],
                                       grad + lo.Wih[l][0], Dl, lo.Wih[l][1] - lo.Wih[l][0], part_ih);
-      // dW_hh[d] = sum_t da_d[t]^T h_d[t_prev]: frames shifted by one step, the
-      // forward direction pairing t with t-1 and the reverse direction t with t+1
-      const Opnd Ad = opnd(DA + (int64_t)B * 8 * H, 8 * H, 4 * H, Kr, 4 * H - (int64_t)B * 8 * H);
-      const Opnd Bh = opnd(Yl, 2 * H, H, Kr, (int64_t)B * 2 * H + H);
-      gemm_f32<T, false, false, V, V>("gemm_dwhh", s, Ad, Bh, 4 * H, H, Kr, 2, lo.sp_dWhh[l],
+      gemm_f32<T, false, false, V, V>("gemm_dwhh", s, Ah, Bh, 4 * H, H, Kr, 2, lo.sp_dWhh[l],
                                       grad + lo.Whh[l][0], H, lo.Whh[l][1] - lo.Whh[l][0], part_hh);
     }
     // db_ih = db_hh = sum over frames of da (unless the reduction above did it)
@@ -871,10 +843,10 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
   // the chip is a partial one)
   for (int i0 = 0; i0 < nd; i0 += KC_MAX_GROUP) {
     const int n = std::min(KC_MAX_GROUP, nd - i0);
-    if (!gemm_f32_group<true, false>("gemm_dw_group", s, n, deferred + i0)) {
+    if (!gemm_f32_group<false, false>("gemm_dw_group", s, n, deferred + i0)) {
       for (int i = i0; i < i0 + n; ++i) {
         const F32Job& j = deferred[i];
-        gemm_f32<T, true, false, V, V>((i & 1) ? "gemm_dwhh" : "gemm_dwih", s, j.A, j.B, j.M, j.N, j.K, j.batches,
+        gemm_f32<T, false, false, V, V>((i & 1) ? "gemm_dwhh" : "gemm_dwih", s, j.A, j.B, j.M, j.N, j.K, j.batches,
                                        1, j.dst, j.ld, j.dst_zstride, part);
       }
     }

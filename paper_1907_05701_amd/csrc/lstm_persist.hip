@@ -27,9 +27,8 @@
 // Step-to-step exchange without barriers or cache maintenance.  The values
 // one member needs from the others (h, or partial dh) are published in an
 // exchange buffer as 8-byte words holding four 15-bit values and a 4-bit
-// tag (see h4_tag), written and read with agent-scope relaxed atomic
-// stores and loads.  Atomic accesses to one location are coherent across the
-// whole GPU, so a reader that sees the expected tag in a word also sees that
+// tag (see h4_tag; the accesses: lstm_persist.hpp).  A word is written and
+// read whole, so a reader that sees the expected tag in a word also sees that
 // word's payload; readers poll the words they need (bounded; the status flag
 // is set if a poll ever gives up).  Two slots alternate by step parity: a
 // member overwrites a slot only after it has consumed the next step from
@@ -53,21 +52,17 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 #define PU 64                 // hidden units per member
 #define NTH 512               // threads per workgroup (8 waves)
 #define KH_MAX 8              // forward: 32-deep k-steps per k half at H = 512
-#define SPIN_LIMIT (1u << 18)
 #define STAGE_BYTES (128 * 1024)   // W_hh staging buffer (half of a member's slice)
-#define BWD_DY_LDS (16 * 1024)     // backward: LDS offset of the summed dy (past the step buffers)
-
-__device__ __forceinline__ uint64_t ll_load(const uint64_t* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-__device__ __forceinline__ void ll_store64(uint64_t* p, uint64_t v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
+// backward: LDS offset of the summed dy (past the two da buffers)
+__host__ __device__ constexpr int bwd_dy_lds(int RV) { return 2 * 32 * ((RV > 16 ? 32 : 16) + 1) * 16; }
 
 // the value of lane l ^ 1 (a DPP quad permutation, no LDS round trip)
 __device__ __forceinline__ float lane_xor1(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, false));
+}
+
+__device__ __forceinline__ float lane_xor2(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E, 0xF, 0xF, false));
 }
 
 // the value of lane l ^ 2
@@ -126,7 +121,7 @@ __device__ __forceinline__ uint64_t h4_tag(uint32_t seq, int n) {
 
 // Polls the N words base[j * stride] (want: the expected tag bits; a word
 // already holding `want` is never read) until every word carries the tag;
-// gives up after SPIN_LIMIT polls, or at once when any wait anywhere has
+// gives up after PERSIST_SPIN_LIMIT polls, or at once when any wait anywhere has
 // given up (the status flag is set), so every wave ends.
 template <int N>
 __device__ __forceinline__ void poll_words(uint64_t (&wv)[N], const uint64_t* base, int stride, uint64_t want,
@@ -136,7 +131,7 @@ __device__ __forceinline__ void poll_words(uint64_t (&wv)[N], const uint64_t* ba
 #pragma unroll
     for (int j = 0; j < N; ++j) bad |= (wv[j] & H4_TAG_BITS) != want;
     if (!bad) break;
-    if (it > SPIN_LIMIT ||
+    if (it > PERSIST_SPIN_LIMIT ||
         ((it & 63) == 63 && __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
       __hip_atomic_store(status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       break;
@@ -303,18 +298,21 @@ __device__ __forceinline__ void gx_prologue(const PersistArgs& a, char* lds, int
 // ---------------------------------------------------------------------------
 // Forward.
 //
-// RV rows of the batch per workgroup (8 or 16) on 16-row MFMA tiles.  With
+// RV rows of the batch per workgroup (8, 16 or 32) on 16-row MFMA tiles (with
 // RV = 8 the tiles' rows 8-15 are zeros, and after the k halves meet the
 // owner lanes swap the valid rows of lanes 0-31 into lanes 32-63, so that
-// every lane applies the cell to 2 rows instead of 4 (half the VALU work of
-// the step, which bounds it once the W_hh slice is in registers).
+// every lane applies the cell to 2 rows instead of 4).  With 32 rows the waves
+// of k half kh own row tile kh; with fewer, sharing the cells between both
+// halves measured slower (100.7 -> 127 us per 42 steps at RV = 8).
 // ---------------------------------------------------------------------------
 template <int RV>
 __global__ __launch_bounds__(NTH) void lstm_fwd_persist(const PersistArgs a) {
   extern __shared__ __attribute__((aligned(16))) char lds_raw[];
-  static_assert(RV == 8 || RV == 16, "rows per workgroup");
-  constexpr int R = 16;          // MFMA tile rows
-  constexpr int NR = RV / 4;     // rows per owner lane
+  static_assert(RV == 8 || RV == 16 || RV == 32, "rows per workgroup");
+  constexpr int NT = RV > 16 ? 2 : 1;   // MFMA row tiles
+  constexpr int R = 16 * NT;            // LDS rows of h
+  constexpr bool BOTH = RV == 32;       // both k halves' waves own cells
+  constexpr int NR = RV == 8 ? 2 : 4;   // cell rows per owner lane
   const int H = a.H, B = a.B, Tn = a.Tn;
   const int NG = 2 * a.NS;
   const int g = blockIdx.x % NG, mem = blockIdx.x / NG;
@@ -323,7 +321,8 @@ __global__ __launch_bounds__(NTH) void lstm_fwd_persist(const PersistArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int ub = w & 3, kh = w >> 2;
   const int KH = H / 64;   // 32-deep k-steps per k half
-  const bool owner = kh == 0;
+  const bool owner = BOTH || kh == 0;
+  if (tid == 0) place_announce(a.place, a.seq + 1);
 
   if (a.Xin) gx_prologue<RV>(a, lds_raw, d, u0, a.b0 + s * RV, a.b0 + a.rows);
 
@@ -371,8 +370,8 @@ __global__ __launch_bounds__(NTH) void lstm_fwd_persist(const PersistArgs a) {
   const int rend = a.b0 + a.rows;
   const int rowbase = a.b0 + s * RV;
   bf16* hl = (bf16*)lds_raw;
-  f32x4* red = (f32x4*)(lds_raw + (size_t)(H / 8) * (R + 1) * 16);
-  char* stage0 = (char*)(red + 4 * 4 * 64);
+  f32x4* red = (f32x4*)(lds_raw + (size_t)(H / 8) * (R + 1) * 16);   // [receiving half][4 unit blocks][4 gates][64]
+  char* stage0 = (char*)(red + (BOTH ? 2 : 1) * 4 * 4 * 64);
   constexpr int STEP_STAGE = RV * PU * (4 + 2 + 8);
   auto stC = [&](int par) { return (float*)(stage0 + par * STEP_STAGE); };
   auto stY = [&](int par) { return (bf16*)(stage0 + par * STEP_STAGE + RV * PU * 4); };
@@ -412,8 +411,11 @@ __global__ __launch_bounds__(NTH) void lstm_fwd_persist(const PersistArgs a) {
   const int wpr = H / 4;   // exchange words per row
   const int64_t slot_stride = (int64_t)2 * a.rows * wpr;
   // the slice rows of an owner lane's NR cell rows
-  auto lrow = [&](int r) { return RV == R ? (lane >> 4) * 4 + r : ((lane >> 4) & 1) * 4 + (lane >> 5) * 2 + r; };
+  auto lrow = [&](int r) {
+    return RV == 8 ? ((lane >> 4) & 1) * 4 + (lane >> 5) * 2 + r : (BOTH ? kh * 16 : 0) + (lane >> 4) * 4 + r;
+  };
 
+  const bool local = place_local(a.place, a.seq + 1, g, NG, gridDim.x / NG, a.status);
   float creg[NR];
 #pragma unroll
   for (int r = 0; r < NR; ++r) creg[r] = 0.f;
@@ -432,7 +434,7 @@ __global__ __launch_bounds__(NTH) void lstm_fwd_persist(const PersistArgs a) {
   };
   if (owner) load_gx(d ? Tn - 1 : 0);
 
-  constexpr int NGT = NTH;   // gathering threads (all: measured faster than the owner waves alone)
+  constexpr int NGT = NTH;   // gathering threads
   constexpr int WPT = (RV * 128 + NGT - 1) / NGT;     // gathered words per thread (at H = 512)
   for (int tau = 0; tau < Tn; ++tau) {
     const int t = d ? Tn - 1 - tau : tau;
@@ -443,9 +445,11 @@ __global__ __launch_bounds__(NTH) void lstm_fwd_persist(const PersistArgs a) {
         for (int q = 0; q < 4; ++q) gx[r][q] = gxn[r][q];
     }
 
-    f32x4 acc[4];
+    f32x4 acc[NT][4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc[i][q] = f32x4{0.f, 0.f, 0.f, 0.f};
     if (tau > 0) {
       // h of the previous step (RV rows x H/4 words of this slice, contiguous
       // in the exchange buffer), polled by the gathering threads in whole
@@ -471,40 +475,46 @@ __global__ __launch_bounds__(NTH) void lstm_fwd_persist(const PersistArgs a) {
           *(uint64_t*)&hl[((wc >> 1) * (R + 1) + row) * 8 + 4 * (wc & 1)] = ok ? (wv[j] & ~H4_TAG_BITS) : 0ull;
         }
       }
-      __syncthreads();
+      lds_barrier();
 #pragma unroll
       for (int i = 0; i < KH_MAX; ++i) {
         if (i >= KH) break;
         const int kg = (kh * KH + i) * 4 + (lane >> 4);
-        const bf16x8 af = *(const bf16x8*)&hl[(kg * (R + 1) + (lane & 15)) * 8];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) acc[q] = Mfma<bf16>::mma(af, bw[i][q], acc[q]);
+        for (int tl = 0; tl < NT; ++tl) {
+          const bf16x8 af = *(const bf16x8*)&hl[(kg * (R + 1) + tl * 16 + (lane & 15)) * 8];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) acc[tl][q] = Mfma<bf16>::mma(af, bw[i][q], acc[tl][q]);
+        }
       }
     }
-    // the two k halves meet at the owner (k half 0)
-    if (!owner) {
+    // the two k halves meet at the owner (k half 0; with two row tiles, k half
+    // kh owns tile kh)
+    if (BOTH || !owner) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) red[(ub * 4 + q) * 64 + lane] = acc[q];
+      for (int q = 0; q < 4; ++q)
+        red[((BOTH && kh == 0 ? 16 : 0) + ub * 4 + q) * 64 + lane] = BOTH && kh ? acc[0][q] : acc[NT - 1][q];
     }
-    __syncthreads();
+    lds_barrier();
     if (owner) {
       // cell math of all owned rows, then h published (the other members
       // wait for it), then the saved activations (only read after the launch)
       uint64_t* xo = a.X + (tau & 1) * slot_stride;
+      f32x4 pre[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        acc[q] += red[(ub * 4 + q) * 64 + lane];
-        if constexpr (RV < R) {
+        pre[q] = (BOTH && kh ? acc[NT - 1][q] : acc[0][q]) + red[((BOTH ? kh * 16 : 0) + ub * 4 + q) * 64 + lane];
+        if constexpr (RV == 8) {
           // rows 2, 3 (lanes 0-15) and 6, 7 (lanes 16-31) into lanes 32-63
-          acc[q][0] = upper_from_lower(acc[q][0], acc[q][2]);
-          acc[q][1] = upper_from_lower(acc[q][1], acc[q][3]);
+          pre[q][0] = upper_from_lower(pre[q][0], pre[q][2]);
+          pre[q][1] = upper_from_lower(pre[q][1], pre[q][3]);
         }
       }
       float hv[NR], gv[NR][4];
 #pragma unroll
       for (int r = 0; r < NR; ++r) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) gv[r][q] = acc[q][r] + (float)gx[r][q];
+        for (int q = 0; q < 4; ++q) gv[r][q] = pre[q][r] + (float)gx[r][q];
         const float ig = sigmoidf_(gv[r][0]), fg = sigmoidf_(gv[r][1]);
         const float gg = tanhf_(gv[r][2]), og = sigmoidf_(gv[r][3]);
         const float c = fg * creg[r] + ig * gg;
@@ -524,7 +534,7 @@ __global__ __launch_bounds__(NTH) void lstm_fwd_persist(const PersistArgs a) {
         const uint32_t p4 = lane_xor2(p2);
         if (row < rend && (lane & 3) == 0)
           ll_store64(xo + ((int64_t)d * a.rows + (row - a.b0)) * wpr + unit / 4,
-                     ((((uint64_t)p4 << 32) | p2) & ~H4_TAG_BITS) | h4_tag(a.seq, tau + 1));
+                     ((((uint64_t)p4 << 32) | p2) & ~H4_TAG_BITS) | h4_tag(a.seq, tau + 1), local);
       }
       // into LDS; the whole workgroup writes them out after the barrier
       const int ul = ub * 16 + (lane & 15);
@@ -544,8 +554,8 @@ __global__ __launch_bounds__(NTH) void lstm_fwd_persist(const PersistArgs a) {
       if (tau + 1 < Tn) load_gx(d ? Tn - 2 - tau : tau + 1);
     }
     // the step's saved activations by the whole workgroup (the next step's
-    // gather barrier comes before the owners rewrite this buffer)
-    __syncthreads();
+    // gather barrier comes before this buffer is rewritten)
+    lds_barrier();
     store_step(t, tau & 1, 0, NTH);
   }
 }
@@ -558,22 +568,27 @@ __global__ __launch_bounds__(NTH) void lstm_fwd_persist(const PersistArgs a) {
 // P_m = da[:, own rows] W_hh[own rows, :] for ALL H units from data it
 // already holds (its own da in LDS, its W_hh rows in registers), publishes
 // P_m as exchange words, and gathers for its own 64 units the partials of
-// all members, summed in member order.  An exchange word holds one unit's
-// partials for four adjacent rows; words are ordered (row quad, member,
-// unit), so a member publishes whole cache lines and a reader takes 512
-// contiguous bytes of each member.  RV rows per workgroup (8 or 16) on
-// 16-row MFMA tiles (with RV = 8 the da block's rows 8-15 stay zero).
+// all members.  An exchange word holds one unit's partials for four adjacent
+// rows; words are ordered (row quad, member, unit), so a member publishes
+// whole cache lines and a reader takes 512 contiguous bytes of each member.
+// RV rows per workgroup (8, 16 or 32) on 16-row MFMA tiles (with RV = 8 the
+// da block's rows 8-15 stay zero).
+//
+// Every thread gathers and owns cells: the LPI = 32 / RV adjacent lanes of
+// one (row quad, unit) take 8 / LPI members' words each, add them in member
+// order, and swap partial sums with DPP so that each lane ends with the
+// total of its 4 / LPI rows, whose cells it then computes.  So the gathered
+// sums never pass through LDS and a step has one barrier (own da complete).
 // ---------------------------------------------------------------------------
 template <int RV>
 __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
   extern __shared__ __attribute__((aligned(16))) char lds_raw[];
-  static_assert(RV == 8 || RV == 16, "rows per workgroup");
-  constexpr int R = 16;                 // MFMA tile rows
-  constexpr int ITEMS = RV / 8;         // (row, unit) cell items per thread
-  // waves 0-3 gather (so their polls wait on no store of the step), waves
-  // 4-7 write da out (DA, DAT, bias partials)
-  constexpr int NG_T = NTH / 2;           // gathering threads
-  constexpr int TPI = NG_T / (16 * RV);   // threads per gathered (row quad, unit): member parts
+  static_assert(RV == 8 || RV == 16 || RV == 32, "rows per workgroup");
+  constexpr int NT = RV > 16 ? 2 : 1;   // MFMA row tiles
+  constexpr int R = 16 * NT;            // LDS rows of da
+  constexpr int LPI = 32 / RV;          // lanes per (row quad, unit)
+  constexpr int RPT = 4 / LPI;          // cell rows per lane
+  constexpr int MPL = 8 / LPI;          // members' words per lane (at most)
   const int H = a.H, B = a.B, Tn = a.Tn;
   const int NM = H / PU, NG = 2 * a.NS;
   const int g = blockIdx.x % NG, mem = blockIdx.x / NG;
@@ -581,7 +596,7 @@ __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
   const int u0 = mem * PU;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int NB = H / 16;                // unit blocks of the partial product
-
+  if (tid == 0) place_announce(a.place, a.seq + 1);
 
   // W_hh of the 256 own gate rows as the B operand: k = own row kk (gate
   // (kk>>4)&3, unit u0 + (kk>>6)*16 + (kk&15)), n = unit.  Wave w holds the
@@ -630,51 +645,45 @@ __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
     }
   }
 
-  // LDS during the steps: own da as the A operand [32 k groups][R + 1][8]
-  // (k = own row; rows RV..15 stay zero), gathered dh_rec [TPI][RV][64]
-  // (member parts), and with dy given as partial sums, the summed dy of
-  // every step [T][RV][64] from BWD_DY_LDS
-  bf16* al = (bf16*)lds_raw;
-  float* dhl = (float*)(al + (size_t)32 * (R + 1) * 8);
-  float* dyl = (float*)(lds_raw + BWD_DY_LDS);
-  static_assert((size_t)32 * (R + 1) * 8 * 2 + (size_t)TPI * RV * PU * 4 <= BWD_DY_LDS, "step buffers below dy");
+  // LDS during the steps: own da as the A operand, by step parity
+  // [2][32 k groups][R + 1][8] (k = own row; with RV = 8 rows 8..15 stay
+  // zero), and with dy given as partial sums, the summed dy of every step
+  // [T][RV][64] behind them
+  constexpr int ALS = 32 * (R + 1) * 8;
+  bf16* al0 = (bf16*)lds_raw;
+  float* dyl = (float*)(lds_raw + bwd_dy_lds(RV));
   if constexpr (RV < R) {
-    for (int i = tid; i < 32 * (R - RV); i += NTH)
-      *(uint4*)&al[((i / (R - RV)) * (R + 1) + RV + i % (R - RV)) * 8] = make_uint4(0u, 0u, 0u, 0u);
+    for (int i = tid; i < 2 * 32 * (R - RV); i += NTH)
+      *(uint4*)&al0[((i / (R - RV)) * (R + 1) + RV + i % (R - RV)) * 8] = make_uint4(0u, 0u, 0u, 0u);
   }
 
   const int rend = a.b0 + a.rows;
   const int rowbase = a.b0 + s * RV;
   const int rquads = (a.rows + 3) / 4;             // row quads of this launch
   const int64_t slot_stride = (int64_t)2 * rquads * NM * H;
-  // cell items: unit cu = tid % 64, rows tid/64 + 8*i
-  const int cu = tid & 63;
-  float dcreg[ITEMS];
+  // this lane's item: unit cu of row quad qd, rows rl0 .. rl0 + RPT - 1
+  const int sub = tid % LPI, item = tid / LPI;
+  const int cu = item & 63, qd = item >> 6, rl0 = qd * 4 + sub * RPT;
+  float dcreg[RPT], dbacc[4];
 #pragma unroll
-  for (int i = 0; i < ITEMS; ++i) dcreg[i] = 0.f;
-  // da^T and bias partials (waves 4-7): thread t takes own gate row t - 256
-  // and the RV rows; the bias partial of the slice is summed over the steps
-  // in order and written once
-  const int dkk = tid & 255;
-  const int64_t dgrow = (int64_t)d * 4 * H + (int64_t)((dkk >> 4) & 3) * H + u0 + (dkk >> 6) * 16 + (dkk & 15);
-  const uint32_t odat = (uint32_t)(dgrow * a.M + rowbase);   // DAT element of frame 0
-  float dbacc = 0.f;
+  for (int i = 0; i < RPT; ++i) dcreg[i] = 0.f;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) dbacc[q] = 0.f;
 
   // everything the cell derivative needs besides dh_rec: dy, the gate
   // pre-activations and c at t, c at the step's predecessor in forward time
   // (which is the next step's t).  Fetched one step ahead, right after the
   // previous step's gather, so that no gather waits for them; c at t is the
-  // previous step's predecessor value.  Per-item element offsets are fixed
+  // previous step's predecessor value.  Per-row element offsets are fixed
   // (32-bit, row and unit); a step adds its frame base to the pointers.
-  float dyn[ITEMS], cpn[ITEMS], cc[ITEMS];
-  bf16x4 gtn[ITEMS];
-  uint32_t oc[ITEMS], og[ITEMS];   // item offsets into [B][2H] (C, DY) and [B][8H] (G) frames
+  float dyn[RPT], cpn[RPT], cc[RPT];
+  bf16x4 gtn[RPT];
+  uint32_t oc[RPT];   // cell offsets into [B][2H] frames (C, DY); 4 oc into [B][2H][4] (G)
 #pragma unroll
-  for (int i = 0; i < ITEMS; ++i) {
-    int row = rowbase + (tid >> 6) + 8 * i;
+  for (int i = 0; i < RPT; ++i) {
+    int row = rowbase + rl0 + i;
     row = row < rend ? row : a.b0;
     oc[i] = (uint32_t)(row * 2 * H + d * H + u0 + cu);
-    og[i] = (uint32_t)(row * 8 * H + d * 4 * H + (u0 + cu) * 4);
   }
   const int64_t fc = (int64_t)B * 2 * H, fg = (int64_t)B * 8 * H;   // elements per frame
   if (a.ndy > 0) {
@@ -716,14 +725,6 @@ __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
     }
     __syncthreads();
   }
-  // DA pieces of this thread (waves 4-7; 8 own gate rows of one row per 16-byte piece)
-  constexpr int NDA = 32 * RV / (NTH / 2);
-  uint32_t oda[NDA];
-#pragma unroll
-  for (int c0 = 0; c0 < NDA; ++c0) {
-    const int c = c0 * (NTH / 2) + (tid & 255), kk = (c & 31) * 8, r = c >> 5;
-    oda[c0] = (uint32_t)((rowbase + r) * 8 * H + d * 4 * H + ((kk >> 4) & 3) * H + u0 + (kk >> 6) * 16 + (kk & 15));
-  }
   auto fetch = [&](int tau_) {
     const int t_ = d ? tau_ : Tn - 1 - tau_;
     const int tp_ = d ? t_ + 1 : t_ - 1;
@@ -732,169 +733,180 @@ __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
     const float* cpt = a.C + (hp ? tp_ : 0) * fc;
     const bf16* gt = a.G + t_ * fg;
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-      dyn[i] = a.ndy > 0 ? dyl[(t_ * RV + (tid >> 6) + 8 * i) * PU + cu] : dyt[oc[i]];
+    for (int i = 0; i < RPT; ++i) {
+      dyn[i] = a.ndy > 0 ? dyl[(t_ * RV + rl0 + i) * PU + cu] : dyt[oc[i]];
       cpn[i] = hp ? cpt[oc[i]] : 0.f;
-      gtn[i] = *(const bf16x4*)(gt + og[i]);   // the unit's four gates: one 8-byte load
+      gtn[i] = *(const bf16x4*)(gt + 4 * oc[i]);   // the unit's four gates: one 8-byte load
     }
   };
   {
     const float* ct = a.C + (d ? 0 : Tn - 1) * fc;
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i) cc[i] = ct[oc[i]];
+    for (int i = 0; i < RPT; ++i) cc[i] = ct[oc[i]];
   }
   fetch(0);
 
-  // gathered (row quad, unit) items: 16 RV of them, TPI threads of waves 0-3
-  // each (member parts of MP members, summed in part order by the cell)
-  const int MP = (NM + TPI - 1) / TPI;
-  const int part = (tid & 255) / (16 * RV), item = tid % (16 * RV);
-  const int gqd = item >> 6;   // row quad within the slice
-  const int m0 = part * MP, mcount = max(0, min(NM, m0 + MP) - m0);
-  constexpr int GM = (8 + TPI - 1) / TPI;   // members per part at most (NM <= 8)
-  const uint32_t ogath = (uint32_t)((((int64_t)d * rquads + (rowbase - a.b0) / 4 + gqd) * NM + m0) * H + u0 + (item & 63));
-  // word offsets (within a slot) of the published words per unit block
-  uint32_t opub[4];
+  const int m0 = sub * MPL, mcount = max(0, min(NM, m0 + MPL) - m0);
+  const uint32_t ogath = (uint32_t)((((int64_t)d * rquads + (rowbase - a.b0) / 4 + qd) * NM + m0) * H + u0 + cu);
+  // word offset (within a slot) of the first published word; unit block j and
+  // row tile tl are 128 j units and 4 tl row quads further
+  const uint32_t opub = (uint32_t)((((int64_t)d * rquads + (rowbase - a.b0) / 4 + (lane >> 4)) * NM + mem) * H +
+                                   w * 16 + (lane & 15));
+  // da out: pieces of 8 own gate rows of one row
+  constexpr int NDT = RV == 8 ? NTH / 2 : NTH;   // threads writing DA: waves 4-7 when that is one piece each
+  constexpr int NDA = 32 * RV / NDT;
+  const int dtid = tid - (NTH - NDT);
+  uint32_t oda[NDA];
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
-    opub[j] = (uint32_t)((((int64_t)d * rquads + (rowbase - a.b0) / 4 + (lane >> 4)) * NM + mem) * H +
-                         (w + 8 * j) * 16 + (lane & 15));
+  for (int c0 = 0; c0 < NDA; ++c0) {
+    const int c = c0 * NDT + max(dtid, 0), kk = (c & 31) * 8, r = c >> 5;
+    oda[c0] = (uint32_t)((rowbase + r) * 8 * H + d * 4 * H + ((kk >> 4) & 3) * H + u0 + (kk >> 6) * 16 + (kk & 15));
+  }
 
+  const bool local = place_local(a.place, a.seq + 1, g, NG, NM, a.status);
   for (int tau = 0; tau < Tn; ++tau) {
     const int t = d ? tau : Tn - 1 - tau;
-    float dy[ITEMS], cp[ITEMS];
+    bf16* al = al0 + (tau & 1) * ALS;
     // the step's gate activations from the prefetched pre-activations,
     // before the gather (whose polls wait for the other members anyway)
-    float ga[ITEMS][4];
+    float ga[RPT][4], tc[RPT];
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
+    for (int i = 0; i < RPT; ++i) {
       ga[i][0] = sigmoidf_((float)gtn[i][0]);
       ga[i][1] = sigmoidf_((float)gtn[i][1]);
       ga[i][2] = tanhf_((float)gtn[i][2]);
       ga[i][3] = sigmoidf_((float)gtn[i][3]);
+      tc[i] = tanhf_(cc[i]);
     }
 
+    float dhr[RPT];
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) dhr[i] = 0.f;
     if (tau > 0) {
-      if (tid < NG_T) {
-        const uint64_t* xs = a.X + ((tau - 1) & 1) * slot_stride;
-        const uint64_t want = h4_tag(a.seq, tau);
-        f32x4 sum = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (rowbase + 4 * gqd < rend) {
-          const uint64_t* base = xs + ogath;
-          uint64_t wv[GM];
+      const uint64_t* base = a.X + ((tau - 1) & 1) * slot_stride + ogath;
+      const uint64_t want = h4_tag(a.seq, tau);
+      f32x4 sum = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (rowbase + 4 * qd < rend) {
+        uint64_t wv[MPL];
 #pragma unroll
-          for (int k = 0; k < GM; ++k) wv[k] = k < mcount ? ll_load(base + (int64_t)k * H) : want;
-          poll_words<GM>(wv, base, H, want, a.status);
+        for (int k = 0; k < MPL; ++k) wv[k] = k < mcount ? ll_load(base + (int64_t)k * H) : want;
+        poll_words<MPL>(wv, base, H, want, a.status);
 #pragma unroll
-          for (int k = 0; k < GM; ++k) {
-            if (k >= mcount) break;
-            sum += p15x4_decode_scaled(wv[k]);
-          }
-          sum *= 0x1p64f;
-        }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) dhl[(part * RV + 4 * gqd + r) * PU + (item & 63)] = sum[r];
+        for (int k = 0; k < MPL; ++k)
+          if (k < mcount) sum += p15x4_decode_scaled(wv[k]);
+        sum *= 0x1p64f;
       }
-    } else {
-      for (int i = tid; i < TPI * RV * PU; i += NTH) dhl[i] = 0.f;
-    }
-    __syncthreads();
+      // the lanes of one (row quad, unit) add their members' sums
+      if constexpr (LPI == 1) {
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
+        for (int i = 0; i < 4; ++i) dhr[i] = sum[i];
+      } else if constexpr (LPI == 2) {
+        const bool hi = sub & 1;
+        dhr[0] = (hi ? sum[2] : sum[0]) + lane_xor1(hi ? sum[0] : sum[2]);
+        dhr[1] = (hi ? sum[3] : sum[1]) + lane_xor1(hi ? sum[1] : sum[3]);
+      } else {
+        const bool hi = sub & 2, odd = sub & 1;
+        const float k0 = (hi ? sum[2] : sum[0]) + lane_xor2(hi ? sum[0] : sum[2]);
+        const float k1 = (hi ? sum[3] : sum[1]) + lane_xor2(hi ? sum[1] : sum[3]);
+        dhr[0] = (odd ? k1 : k0) + lane_xor1(odd ? k0 : k1);
+      }
+    }
+    float dy[RPT], cp[RPT];
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
       dy[i] = dyn[i];
       cp[i] = cpn[i];
     }
-    if (tau + 1 < Tn) fetch(tau + 1);
 
-    // cell derivatives; da goes to global memory (weight gradients) and to
-    // LDS (next partial product)
+    // cell derivatives; da goes to LDS (next partial product) and from there
+    // to global memory (weight and input gradients)
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-      const int r = (tid >> 6) + 8 * i;
-      const int row = rowbase + r;
+    for (int i = 0; i < RPT; ++i) {
+      const int r = rl0 + i;
       const float ig = ga[i][0], fg_ = ga[i][1], gg = ga[i][2], og_ = ga[i][3];
-      float dhr = 0.f;
-#pragma unroll
-      for (int pp = 0; pp < TPI; ++pp) dhr += dhl[(pp * RV + r) * PU + cu];
-      const float dh = dhr + dy[i];
-      const float tc = tanhf_(cc[i]);
-      const float dc = dh * og_ * (1.f - tc * tc) + dcreg[i];
+      const float dh = dhr[i] + dy[i];
+      const float dc = dh * og_ * (1.f - tc[i] * tc[i]) + dcreg[i];
       dcreg[i] = dc * fg_;
       float da[4];
       da[0] = dc * gg * ig * (1.f - ig);
       da[1] = dc * cp[i] * fg_ * (1.f - fg_);
       da[2] = dc * ig * (1.f - gg * gg);
-      da[3] = dh * tc * og_ * (1.f - og_);
-      const bool ok = row < rend;
+      da[3] = dh * tc[i] * og_ * (1.f - og_);
+      const bool ok = rowbase + r < rend;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const bf16 v = ok ? (bf16)da[q] : (bf16)0.f;
         // own row kk = (cu >> 4)*64 + q*16 + (cu & 15)
         const int kk = (cu >> 4) * 64 + q * 16 + (cu & 15);
         al[((kk >> 3) * (R + 1) + r) * 8 + (kk & 7)] = v;
+        dbacc[q] += (float)v;
       }
       cc[i] = cp[i];   // c at the next step's t
     }
-    __syncthreads();
+    if (tau + 1 < Tn) fetch(tau + 1);
+    lds_barrier();
 
-    // P = da_own [16 x 256] * W_own [256 x H]; unit blocks w + 8j of this
+    // P = da_own [RV x 256] * W_own [256 x H]; unit blocks w + 8j of this
     // wave.  On the critical path, so before the global copies of da.
     if (tau + 1 < Tn) {
       uint64_t* xo = a.X + (tau & 1) * slot_stride;
-      f32x4 acc[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-      // the A fragments one k-step ahead of the products (two in registers:
-      // the registers holding W_hh leave no room for all eight)
-      const bf16* ab = &al[((lane >> 4) * (R + 1) + (lane & 15)) * 8];
-      bf16x8 af = *(const bf16x8*)ab, an;
-#pragma unroll
-      for (int ks = 0; ks < 8; ++ks) {
-        if (ks + 1 < 8) an = *(const bf16x8*)(ab + (ks + 1) * 4 * (R + 1) * 8);
-        // (unit blocks past H hold zero fragments; their sums are not published)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[j] = Mfma<bf16>::mma(af, bw[ks][j], acc[j]);
-        af = an;
-      }
-      // publish: word (row quad, member, unit), the lane's four rows
       const uint64_t tg = h4_tag(a.seq, tau + 1);
-      const int rl = (lane >> 4) * 4;
+      // one row tile after the other, the first one's words on their way
+      // while the second multiplies
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const uint64_t v = p15x4_encode(acc[j]);
-        if (rl < RV && rowbase + rl < rend && w + 8 * j < NB) ll_store64(xo + opub[j], v | tg);
+      for (int tl = 0; tl < NT; ++tl) {
+        f32x4 acc[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        // the A fragments one k-step ahead of the products (two in registers:
+        // the registers holding W_hh leave no room for all eight)
+        const bf16* ab = &al[((lane >> 4) * (R + 1) + tl * 16 + (lane & 15)) * 8];
+        bf16x8 af = *(const bf16x8*)ab, an;
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) {
+          if (ks + 1 < 8) an = *(const bf16x8*)(ab + (ks + 1) * 4 * (R + 1) * 8);
+          // (unit blocks past H hold zero fragments; their sums are not published)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) acc[j] = Mfma<bf16>::mma(af, bw[ks][j], acc[j]);
+          af = an;
+        }
+        // publish: word (row quad, member, unit), the lane's four rows
+        const int rl = tl * 16 + (lane >> 4) * 4;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const uint64_t v = p15x4_encode(acc[j]);
+          if (rl < RV && rowbase + rl < rend && w + 8 * j < NB)
+            ll_store64(xo + opub + (uint32_t)(tl * 4 * NM * H + j * 128), v | tg, local);
+        }
       }
     }
 
-    // waves 4-7: da in frame-major rows (DA, for dX), 16 bytes of LDS and
-    // of DA per piece (8 own gate rows of one row); frame-contiguous (DAT,
-    // the RV frames of one own gate row); and the bias partial sums (DBP)
-    if (tid >= NTH / 2) {
+    // da in frame-major rows, 16 bytes of LDS and of DA per piece (8 own gate
+    // rows of one row)
+    if (dtid >= 0) {
       bf16* dat = a.DA + (int64_t)t * fg;
 #pragma unroll
       for (int c0 = 0; c0 < NDA; ++c0) {
-        const int c = c0 * (NTH / 2) + (tid & 255), kg = c & 31, r = c >> 5;
+        const int c = c0 * NDT + dtid, kg = c & 31, r = c >> 5;
         if (rowbase + r < rend) *(uint4*)(dat + oda[c0]) = *(const uint4*)&al[(kg * (R + 1) + r) * 8];
-      }
-      if (a.DAT || a.DBP) {
-        bf16 v[RV];
-        float sum = 0.f;
-#pragma unroll
-        for (int j = 0; j < RV; ++j) {
-          v[j] = al[((dkk >> 3) * (R + 1) + j) * 8 + (dkk & 7)];
-          sum += (float)v[j];
-        }
-        if (a.DAT) {
-          bf16* p = a.DAT + (int64_t)t * B + odat;
-#pragma unroll
-          for (int j = 0; j < RV; j += 8)
-            if (rowbase + j < rend) *(uint4*)(p + j) = *(const uint4*)&v[j];
-        }
-        dbacc += sum;   // steps in order
       }
     }
   }
-  if (a.DBP && tid >= NTH / 2 && rowbase < rend) a.DBP[(int64_t)(rowbase / RV) * 8 * H + dgrow] = dbacc;
+  if (a.DBP) {
+    // bias partials: every lane's sum over its rows and steps, added over
+    // the slice's row groups in order
+    float* red = (float*)lds_raw;   // [RV / RPT][64 units][4 gates]
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) red[((qd * LPI + sub) * PU + cu) * 4 + q] = dbacc[q];
+    __syncthreads();
+    if (tid < 4 * PU && rowbase < rend) {
+      float sum = 0.f;
+#pragma unroll
+      for (int r = 0; r < RV / RPT; ++r) sum += red[r * PU * 4 + tid];
+      a.DBP[(int64_t)(rowbase / RV) * 8 * H + (int64_t)d * 4 * H + (int64_t)(tid & 3) * H + u0 + (tid >> 2)] = sum;
+    }
+  }
 }
 
 // The recurrence status block (at the end of the activation workspace): an
@@ -930,8 +942,10 @@ __global__ void status_reset_kernel(int* status) {
 // Host side.
 // ---------------------------------------------------------------------------
 size_t persist_lds_bytes(int H, bool backward, int RV) {
-  const size_t run = backward ? (size_t)32 * 17 * 16 + (size_t)(NTH / (16 * RV)) * RV * PU * 4
-                              : (size_t)(H / 8) * 17 * 16 + (size_t)4 * 4 * 64 * 16 + (size_t)2 * RV * PU * (4 + 2 + 8);
+  const int R = RV > 16 ? 32 : 16;
+  const size_t run = backward ? (size_t)bwd_dy_lds(RV)
+                              : (size_t)(H / 8) * (R + 1) * 16 + (size_t)(RV > 16 ? 2 : 1) * 4 * 4 * 64 * 16 +
+                                    (size_t)2 * RV * PU * (4 + 2 + 8);
   return std::max(std::max(run, (size_t)STAGE_BYTES), backward ? (size_t)0 : gx_lds_bytes);
 }
 
@@ -1027,11 +1041,11 @@ static bool persist_plan(int H, int B, int* RVo, int* chunko) {
   if (NM < 1) return false;
   const int max_ns = std::min(persist_max_wg() / (2 * NM), PERSIST_MAX_SLICES);
   if (max_ns < 1) return false;
-  int RV = (B + 7) / 8 <= max_ns ? 8 : 16;
-  // ADPSGD_BLSTM_ROWS_PER_WG=16 keeps 16 rows per workgroup at any batch
-  // (half the workgroups at B <= 128, for measurements)
+  int RV = (B + 7) / 8 <= max_ns ? 8 : (B + 15) / 16 <= max_ns ? 16 : 32;
+  // ADPSGD_BLSTM_ROWS_PER_WG=16 or 32 keeps that many rows per workgroup at
+  // any batch (fewer workgroups at small batches, for measurements and tests)
   if (const char* e = getenv("ADPSGD_BLSTM_ROWS_PER_WG"))
-    if (atoi(e) == 16) RV = 16;
+    if (atoi(e) == 16 || atoi(e) == 32) RV = atoi(e);
   *RVo = RV;
   *chunko = std::min(B, max_ns * RV);
   return true;
@@ -1045,7 +1059,7 @@ int persist_rows_per_workgroup(int H, int B) {
 bool persist_bwd_dy_partials_ok(int H, int B, int T) {
   int RV, chunk;
   if (!persist_plan(H, B, &RV, &chunk)) return false;
-  return (size_t)BWD_DY_LDS + (size_t)T * RV * PU * 4 <= persist_lds_bytes(H, true, RV);
+  return (size_t)bwd_dy_lds(RV) + (size_t)T * RV * PU * 4 <= persist_lds_bytes(H, true, RV);
 }
 
 bool persist_bwd_needs_wt(int, int) { return false; }
@@ -1055,9 +1069,9 @@ hipError_t persist_clear(bool backward, const PersistArgs& a, hipStream_t s) {
   if (!persist_plan(a.H, a.B, &RV, &chunk)) return hipErrorInvalidValue;
   // both exchange slots start without any valid tag; the forward's clear
   // also initialises the status block of a fresh workspace
-  const int64_t words = backward ? (int64_t)2 * 2 * ((chunk + 3) / 4) * (a.H / PU) * a.H
-                                 : (int64_t)2 * 2 * chunk * (a.H / 4);
-  return persist_clear_words(a.X, words / 2, backward ? nullptr : a.status, s);
+  const int64_t words = PERSIST_PLACE_WORDS + (backward ? (int64_t)2 * 2 * ((chunk + 3) / 4) * (a.H / PU) * a.H
+                                 : (int64_t)2 * 2 * chunk * (a.H / 4));
+  return persist_clear_words(a.place, words / 2, backward ? nullptr : a.status, s);
 }
 
 hipError_t persist_clear_words(void* p, int64_t n16, int* status, hipStream_t s) {
@@ -1084,8 +1098,9 @@ hipError_t persist_layer(bool backward, PersistArgs a, hipStream_t s) {
     // the launch's position in the call (the caller's tag numbers the layers
     // in the order the call runs them)
     c.seq = a.tag * (uint32_t)cdiv(a.B, chunk) + (uint32_t)(b0 / chunk);
-    const hipError_t e = RV == 8 ? (backward ? launch_one<8, true>(c, s) : launch_one<8, false>(c, s))
-                                 : (backward ? launch_one<16, true>(c, s) : launch_one<16, false>(c, s));
+    const hipError_t e = RV == 8    ? (backward ? launch_one<8, true>(c, s) : launch_one<8, false>(c, s))
+                         : RV == 16 ? (backward ? launch_one<16, true>(c, s) : launch_one<16, false>(c, s))
+                                    : (backward ? launch_one<32, true>(c, s) : launch_one<32, false>(c, s));
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

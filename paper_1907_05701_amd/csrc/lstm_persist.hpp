@@ -3,6 +3,65 @@
 
 #include "common.hpp"
 
+// Barrier of the steps: every thread's LDS accesses are done, while its global
+// stores and prefetches stay in flight (the fence of __syncthreads would wait
+// for them at each step).
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+
+// ---------------------------------------------------------------------------
+// Exchange words: agent-scope relaxed 8-byte atomics (coherent per location
+// over the whole GPU).  A member whose group sits on one XCD publishes with
+// plain stores instead: they stay in that XCD's L2, where the readers'
+// agent-scope loads (which pass the CU's own cache by) find them, while an
+// agent-scope store goes through to memory.  Every word carries its tag, so a
+// reader can only be late, never wrong.  Measured at H = 512 per step of the
+// backward: 2.26 -> 2.01 us (8 rows per workgroup), 3.34 -> 2.83 (16), 5.4 ->
+// 4.7 (32); loads with weaker scopes or non-temporal accesses were slower.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ uint64_t ll_load(const uint64_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void ll_store64(uint64_t* p, uint64_t v, bool local) {
+  if (local)
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  else
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+#define PERSIST_SPIN_LIMIT (1u << 18)
+// Placement words in front of the exchange words, one per workgroup of a
+// launch: (launch mark << 32) | XCD.
+#define PERSIST_PLACE_WORDS 1024
+__device__ __forceinline__ uint32_t xcd_id() {
+  return __builtin_amdgcn_s_getreg(20 | (3 << 11));   // HW_REG_XCC_ID, bits 0-3
+}
+// Announces this workgroup's XCD (one thread, at the kernel's start).
+__device__ __forceinline__ void place_announce(uint64_t* place, uint32_t mark) {
+  __hip_atomic_store(place + blockIdx.x, ((uint64_t)mark << 32) | xcd_id(), __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_AGENT);
+}
+// Whether every member of the group (workgroups g, g + ng, ...; at most 64)
+// runs on this XCD; all lanes of every wave call it, and get one answer.
+__device__ __forceinline__ bool place_local(const uint64_t* place, uint32_t mark, int g, int ng, int members,
+                                            int* status) {
+  const int lane = threadIdx.x & 63;
+  const uint64_t* p = place + g + (int64_t)(lane < members ? lane : 0) * ng;
+  uint64_t v = ll_load(p);
+  for (unsigned it = 0; !__all((uint32_t)(v >> 32) == mark); ++it) {
+    if (it > PERSIST_SPIN_LIMIT ||
+        ((it & 63) == 63 && __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
+      __hip_atomic_store(status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return false;
+    }
+    __builtin_amdgcn_s_sleep(1);
+    v = ll_load(p);
+  }
+  return __all((uint32_t)v == xcd_id());
+}
+
 struct PersistArgs {
   bf16* Y;            // layer output [M][2H] (forward: read h_prev, write h)
   const bf16* W;      // bf16 parameter copy (flat layout)
@@ -32,11 +91,10 @@ struct PersistArgs {
   bf16* G;            // gate pre-activations [M][2][H][4] (direction, unit, gate i/f/g/o; forward writes, backward reads)
   bf16* DA;           // backward: gate pre-activation gradients [M][8H]
   const float* DY;    // backward: gradient reaching the layer output [M][2H]
-  uint64_t* X;        // step-exchange words (see lstm_persist.hip), PERSIST_XCH_BYTES
-  bf16* DAT;          // backward, optional: da also frame-contiguous [8H][M] (needs B % 8 == 0)
+  uint64_t* place;    // placement words (PERSIST_PLACE_WORDS)
+  uint64_t* X;        // step-exchange words behind them (see lstm_persist.hip)
   float* DBP;         // backward, optional: sums of da over each workgroup's rows and all steps
                       // [cdiv(B, rows per workgroup)][8H] (see persist_rows_per_workgroup)
-  int64_t M;          // frames, T*B (DAT row length)
   int* status;        // recurrence status block (sticky flag, see persist_status_reset)
   uint32_t tag;       // caller: the layer's position in the order the call runs the layers
   int Tn, B, H;
@@ -44,11 +102,11 @@ struct PersistArgs {
   uint32_t seq;       // the launch's position among the call's launches (filled in by persist_layer)
 };
 
-// At most this many batch slices of 8 or 16 rows per launch, so one launch
-// covers at most PERSIST_MAX_ROWS rows.
+// At most this many batch slices of 8, 16 or 32 rows per launch, so one
+// launch covers at most PERSIST_MAX_ROWS rows.
 #define PERSIST_MAX_SLICES 32
-#define PERSIST_MAX_ROWS (PERSIST_MAX_SLICES * 16)
-// Exchange buffer: 2 slots x 2 directions x row quads x (H/64 members) x H
+#define PERSIST_MAX_ROWS (PERSIST_MAX_SLICES * 32)
+// Exchange buffer: the placement words, then 2 slots x 2 directions x row quads x (H/64 members) x H
 // units words of 8 bytes (the backward's partial sums, four rows per word;
 // the forward uses H/4 words per row, never more).
 static inline size_t persist_xch_bytes(int B, int H) {
@@ -56,7 +114,7 @@ static inline size_t persist_xch_bytes(int B, int H) {
   const size_t members = H / 64 > 0 ? H / 64 : 1;
   const size_t bwd = (size_t)2 * 2 * ((rows + 3) / 4) * members * H * 8;
   const size_t fwd = (size_t)2 * 2 * rows * (H / 4 > 0 ? H / 4 : 1) * 8;
-  return bwd > fwd ? bwd : fwd;
+  return (bwd > fwd ? bwd : fwd) + PERSIST_PLACE_WORDS * 8;
 }
 
 // Whether the backward can take dy as split-K partials (its summed dy of all
@@ -105,7 +163,8 @@ struct Persist32Args {
   const float* DY;      // backward: gradient reaching the layer output [M][2H]
   float* DBP;           // backward: sums of da over each workgroup's rows and all steps
                         // [cdiv(B, persist32_rows_per_workgroup)][8H]
-  uint64_t* X;          // step-exchange words, persist32_xch_bytes
+  uint64_t* place;      // placement words (PERSIST_PLACE_WORDS)
+  uint64_t* X;          // step-exchange words behind them
   int* status;          // recurrence status block
   uint32_t tag0;        // caller: the layer's position in the call; per launch: the tag before its first step's
   int Tn, B, H;

@@ -23,10 +23,9 @@
 //             W_hh for 64 hidden units: partial sums of dh_rec for all H
 //             units, summed by the owner of each unit in part order.
 // Steps exchange h (forward) and the partial sums (backward) as 8-byte words
-// holding one float32 and a 32-bit tag (launch position and step), written
-// and polled with agent-scope relaxed atomics, in two slots alternating by
-// step; the reasoning about slot reuse, residency and bounded waits is that
-// of the bf16 kernels (lstm_persist.hip).
+// holding one float32 and a 32-bit tag (launch position and step), in two
+// slots alternating by step; the reasoning about slot reuse, residency and
+// bounded waits is that of the bf16 kernels (lstm_persist.hip).
 //
 // What bounds it: at 4 rows the step's exchange round trip (about 1 us) and
 // the products (0.9 us of matrix-core time per 4 rows) about equally; at 16
@@ -40,7 +39,6 @@
 
 #define P32_THREADS 512
 #define P32_KW 128                 // k values of W_hh per wave (registers per lane)
-#define P32_SPIN_LIMIT (1u << 18)
 
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
@@ -67,16 +65,12 @@ __device__ __forceinline__ f32x4 mfma_rows4(float a, const float* w, f32x4 acc) 
   return acc;
 }
 
-__device__ __forceinline__ uint64_t p32_load(const uint64_t* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void p32_publish(uint64_t* p, float v, uint32_t tag) {
-  __hip_atomic_store(p, ((uint64_t)tag << 32) | __builtin_bit_cast(uint32_t, v), __ATOMIC_RELAXED,
-                     __HIP_MEMORY_SCOPE_AGENT);
+__device__ __forceinline__ void p32_publish(uint64_t* p, float v, uint32_t tag, bool local) {
+  ll_store64(p, ((uint64_t)tag << 32) | __builtin_bit_cast(uint32_t, v), local);
 }
 
 // Polls word j at base[off[j]] until all carry `want` (one already holding
-// it is not read again); gives up after P32_SPIN_LIMIT polls, or at once when
+// it is not read again); gives up after PERSIST_SPIN_LIMIT polls, or at once when
 // any wait anywhere has given up, so every wave ends.
 template <int N>
 __device__ __forceinline__ void p32_poll(uint64_t (&wv)[N], const uint64_t* base, const uint32_t (&off)[N],
@@ -86,7 +80,7 @@ __device__ __forceinline__ void p32_poll(uint64_t (&wv)[N], const uint64_t* base
 #pragma unroll
     for (int j = 0; j < N; ++j) bad |= (uint32_t)(wv[j] >> 32) != want;
     if (!bad) break;
-    if (it > P32_SPIN_LIMIT ||
+    if (it > PERSIST_SPIN_LIMIT ||
         ((it & 63) == 63 && __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
       __hip_atomic_store(status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       break;
@@ -94,15 +88,8 @@ __device__ __forceinline__ void p32_poll(uint64_t (&wv)[N], const uint64_t* base
     __builtin_amdgcn_s_sleep(1);
 #pragma unroll
     for (int j = 0; j < N; ++j)
-      if ((uint32_t)(wv[j] >> 32) != want) wv[j] = p32_load(base + off[j]);
+      if ((uint32_t)(wv[j] >> 32) != want) wv[j] = ll_load(base + off[j]);
   }
-}
-
-// Barrier of the steps: every thread's LDS accesses are done, while its global
-// stores and prefetches stay in flight (the fence of __syncthreads would wait
-// for them at each step).
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
 // LDS row pitch (floats) of a row operand of n k values: the 4 rows x 16 k
@@ -128,6 +115,7 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_fwd_persist32(const Persist3
   const int cb = w % NCB, ks = w / NCB;
   const int KQ = (H + 16 * KS - 1) / (16 * KS) * 16;   // k values per part (whole groups of 16)
   const int k0 = ks * KQ;
+  if (!SOLO && tid == 0) place_announce(a.place, a.tag0 + 1);
 
   // W_hh rows of this lane's gate column, k0 .. k0 + KQ (zeros past H), through
   // a wave's own piece of LDS so that the global loads take whole lines (8
@@ -184,6 +172,7 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_fwd_persist32(const Persist3
 #pragma unroll
   for (int i = 0; i < IT; ++i) creg[i] = 0.f;
   load_gx(d ? Tn - 1 : 0);
+  const bool local = !SOLO && place_local(a.place, a.tag0 + 1, g, NG, gridDim.x / NG, a.status);
 
   for (int tau = 0; tau < Tn; ++tau) {
     const int t = d ? Tn - 1 - tau : tau;
@@ -205,7 +194,7 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_fwd_persist32(const Persist3
           for (int j = 0; j < GB; ++j) {
             const int idx = j0 + j * P32_THREADS;
             off[j] = (uint32_t)idx;
-            wv[j] = idx < nwords && rowbase + idx / H < rend ? p32_load(src + idx) : (uint64_t)want << 32;
+            wv[j] = idx < nwords && rowbase + idx / H < rend ? ll_load(src + idx) : (uint64_t)want << 32;
           }
           p32_poll<GB>(wv, src, off, want, a.status);
 #pragma unroll
@@ -259,7 +248,7 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_fwd_persist32(const Persist3
           // of the last one here, meets zero weights)
           if (tau + 1 < Tn) hl[rl * HS + unit] = hv[i];
         } else if (uok && row < rend) {
-          p32_publish(xo + ((int64_t)d * a.rows + (row - a.b0)) * H + unit, hv[i], a.tag0 + tau + 1);
+          p32_publish(xo + ((int64_t)d * a.rows + (row - a.b0)) * H + unit, hv[i], a.tag0 + tau + 1, local);
         }
       }
     }
@@ -300,6 +289,7 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_bwd_persist32(const Persist3
   const int cb = w % CBS, ks = w / CBS;
   const int hu = cb * 64 + lane;   // hidden unit of this lane's product column
   const int parts = nmem * KS;
+  if (!SOLO && tid == 0) place_announce(a.place, a.tag0 + 1);
 
   // W_hh[own gate row][hu], own row 4 (unit - u0) + gate, the KW rows of part ks
   float bw[KW];
@@ -342,6 +332,7 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_bwd_persist32(const Persist3
     cc[i] = a.C[((int64_t)(d ? 0 : Tn - 1) * B + rowc(i)) * 2 * H + (int64_t)d * H + unitc];
   }
   fetch(0);
+  const bool local = !SOLO && place_local(a.place, a.tag0 + 1, g, NG, nmem, a.status);
 
   for (int tau = 0; tau < Tn; ++tau) {
     const int t = d ? tau : Tn - 1 - tau;
@@ -365,7 +356,7 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_bwd_persist32(const Persist3
             const int row = rowbase + r0 + RPI * (i0 + j / MPP), p = q * MPP + j % MPP;
             const bool ok = uok && row < rend && p < parts;
             off[j] = (uint32_t)((((int64_t)d * parts + (ok ? p : 0)) * a.rows + (ok ? row - a.b0 : 0)) * H + unitc);
-            wv[j] = ok ? p32_load(src + off[j]) : (uint64_t)want << 32;
+            wv[j] = ok ? ll_load(src + off[j]) : (uint64_t)want << 32;
           }
           p32_poll<IB * MPP>(wv, src, off, want, a.status);
 #pragma unroll
@@ -422,7 +413,7 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_bwd_persist32(const Persist3
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             const int row = rowbase + rt * 4 + r;
-            if (hu < H && row < rend) p32_publish(xo + (int64_t)(row - a.b0) * H, acc[rt][r], a.tag0 + tau + 1);
+            if (hu < H && row < rend) p32_publish(xo + (int64_t)(row - a.b0) * H, acc[rt][r], a.tag0 + tau + 1, local);
           }
       } else {
 #pragma unroll
@@ -498,16 +489,17 @@ size_t persist32_xch_bytes(int B, int H) {
   const int ncb = H <= 256 ? 4 : 2;
   const int64_t members = cdiv(H, 16 * ncb);
   const int64_t rows = std::min<int64_t>(B, 256 / (2 * members) * (ncb == 2 ? 16 : 8));
-  return (size_t)2 * 2 * members * (ncb / 2) * rows * H * 8;
+  return (size_t)2 * 2 * members * (ncb / 2) * rows * H * 8 + PERSIST_PLACE_WORDS * 8;
 }
 
 hipError_t persist32_clear(bool backward, const Persist32Args& a, hipStream_t s) {
   Plan32 p;
   if (!plan32(a.H, a.B, &p)) return hipErrorInvalidValue;
   int64_t words = 0;   // one member exchanges nothing
-  if (p.members > 1) words = (int64_t)2 * 2 * (backward ? p.members * p.bks : 1) * p.chunk * a.H;
+  if (p.members > 1)
+    words = PERSIST_PLACE_WORDS + (int64_t)2 * 2 * (backward ? p.members * p.bks : 1) * p.chunk * a.H;
   if (backward && words == 0) return hipSuccess;
-  return persist_clear_words(a.X, words / 2, backward ? nullptr : a.status, s);
+  return persist_clear_words(a.place, words / 2, backward ? nullptr : a.status, s);
 }
 
 template <int NCB, int RT, int BKS, bool SOLO>
