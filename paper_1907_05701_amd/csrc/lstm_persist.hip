@@ -314,8 +314,9 @@ __global__ __launch_bounds__(NTH) void lstm_fwd_persist(const PersistArgs a) {
   constexpr bool BOTH = RV == 32;       // both k halves' waves own cells
   constexpr int NR = RV == 8 ? 2 : 4;   // cell rows per owner lane
   const int H = a.H, B = a.B, Tn = a.Tn;
-  const int NG = 2 * a.NS;
+  const int NG = a.NG;
   const int g = blockIdx.x % NG, mem = blockIdx.x / NG;
+  if (g >= 2 * a.NS) return;   // padding (see persist_groups)
   const int d = g & 1, s = g >> 1;
   const int u0 = mem * PU;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -333,6 +334,7 @@ __global__ __launch_bounds__(NTH) void lstm_fwd_persist(const PersistArgs a) {
   // 16-byte chunk c of row lr in slot c ^ (lr & 15) so that the 16 rows of
   // one fragment read fall in distinct bank groups.
   bf16x8 bw[KH_MAX][4];
+  bool local = false;   // the group's members share an XCD (asked for while the staging loads are in flight)
   {
     char* stg = lds_raw;
     const __amdgpu_buffer_rsrc_t rw = dma_rsrc(a.W + (d ? a.whh1 : a.whh0));
@@ -347,6 +349,7 @@ __global__ __launch_bounds__(NTH) void lstm_fwd_persist(const PersistArgs a) {
         const bool ok = c * 8 < H / 2;
         dma16(rw, ok ? (uint32_t)((grow * H + p * (H / 2) + c * 8) * 2) : DMA_OFF_NONE, stg + ins * 1024);
       }
+      if (p == 0) local = place_local(a.place, a.seq + 1, g, NG, H / PU, a.status);
       dma_wait_all();
       __syncthreads();
       if (kh == p) {
@@ -415,7 +418,6 @@ __global__ __launch_bounds__(NTH) void lstm_fwd_persist(const PersistArgs a) {
     return RV == 8 ? ((lane >> 4) & 1) * 4 + (lane >> 5) * 2 + r : (BOTH ? kh * 16 : 0) + (lane >> 4) * 4 + r;
   };
 
-  const bool local = place_local(a.place, a.seq + 1, g, NG, gridDim.x / NG, a.status);
   float creg[NR];
 #pragma unroll
   for (int r = 0; r < NR; ++r) creg[r] = 0.f;
@@ -590,8 +592,9 @@ __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
   constexpr int RPT = 4 / LPI;          // cell rows per lane
   constexpr int MPL = 8 / LPI;          // members' words per lane (at most)
   const int H = a.H, B = a.B, Tn = a.Tn;
-  const int NM = H / PU, NG = 2 * a.NS;
+  const int NM = H / PU, NG = a.NG;
   const int g = blockIdx.x % NG, mem = blockIdx.x / NG;
+  if (g >= 2 * a.NS) return;   // padding (see persist_groups)
   const int d = g & 1, s = g >> 1;
   const int u0 = mem * PU;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -610,6 +613,7 @@ __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
   // MFMA B operand).  The swizzle spreads the 16 rows of one read over
   // distinct chunk pairs.
   bf16x8 bw[8][4];
+  bool local = false;
   {
     auto wswz = [](int k) { return 2 * ((k & 3) | (((k >> 3) & 1) << 2)); };
     char* stg = lds_raw;
@@ -625,6 +629,7 @@ __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
         const int64_t grow = (int64_t)((kk >> 4) & 3) * H + u0 + (kk >> 6) * 16 + (kk & 15);
         dma16(rw, c * 8 < H ? (uint32_t)((grow * H + c * 8) * 2) : DMA_OFF_NONE, stg + kl * 1024);
       }
+      if (p == 0) local = place_local(a.place, a.seq + 1, g, NG, NM, a.status);
       dma_wait_all();
       __syncthreads();
 #pragma unroll
@@ -763,7 +768,6 @@ __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
     oda[c0] = (uint32_t)((rowbase + r) * 8 * H + d * 4 * H + ((kk >> 4) & 3) * H + u0 + (kk >> 6) * 16 + (kk & 15));
   }
 
-  const bool local = place_local(a.place, a.seq + 1, g, NG, NM, a.status);
   for (int tau = 0; tau < Tn; ++tau) {
     const int t = d ? tau : Tn - 1 - tau;
     bf16* al = al0 + (tau & 1) * ALS;
@@ -1023,12 +1027,17 @@ hipError_t persist_launch(const char* name, const void* fn, dim3 grid, int threa
   return e;
 }
 
+int persist_groups(int groups, int members) {
+  const int padded = (int)rup(groups, 8);
+  return padded * members <= persist_max_wg() ? padded : groups;
+}
+
 template <int RV, bool BWD>
 static hipError_t launch_one(PersistArgs a, hipStream_t s) {
   const void* fn;
   if constexpr (BWD) fn = (const void*)lstm_bwd_persist<RV>;
   else fn = (const void*)lstm_fwd_persist<RV>;
-  return persist_launch(BWD ? "lstm_rec_bwd_persist" : "lstm_rec_fwd_persist", fn, dim3(2 * a.NS * (a.H / PU)), NTH,
+  return persist_launch(BWD ? "lstm_rec_bwd_persist" : "lstm_rec_fwd_persist", fn, dim3(a.NG * (a.H / PU)), NTH,
                         persist_lds_bytes(a.H, BWD, RV), &a, s);
 }
 
@@ -1095,6 +1104,7 @@ hipError_t persist_layer(bool backward, PersistArgs a, hipStream_t s) {
     c.b0 = b0;
     c.rows = std::min(chunk, a.B - b0);
     c.NS = (c.rows + RV - 1) / RV;
+    c.NG = persist_groups(2 * c.NS, a.H / PU);
     // the launch's position in the call (the caller's tag numbers the layers
     // in the order the call runs them)
     c.seq = a.tag * (uint32_t)cdiv(a.B, chunk) + (uint32_t)(b0 / chunk);

@@ -99,6 +99,7 @@ struct PersistArgs {
   uint32_t tag;       // caller: the layer's position in the order the call runs the layers
   int Tn, B, H;
   int b0, rows, NS;   // batch chunk handled by one launch (filled in by persist_layer)
+  int NG;             // groups of the launch: 2 NS, or more with padding (persist_groups)
   uint32_t seq;       // the launch's position among the call's launches (filled in by persist_layer)
 };
 
@@ -168,7 +169,7 @@ struct Persist32Args {
   int* status;          // recurrence status block
   uint32_t tag0;        // caller: the layer's position in the call; per launch: the tag before its first step's
   int Tn, B, H;
-  int b0, rows, NS;     // filled in by persist32_layer
+  int b0, rows, NS, NG; // filled in by persist32_layer
 };
 
 // True if these kernels handle this H (a multiple of 16 up to 512).
@@ -181,6 +182,12 @@ hipError_t persist32_layer(bool backward, Persist32Args a, hipStream_t s);
 // Compute units of the current device (0: unknown); one persistent workgroup
 // runs on each.
 int persist_max_wg();
+// Groups a launch of `groups` groups of `members` workgroups is laid out for.
+// Member m of group g is workgroup g + m NG, and workgroup i runs on XCD i % 8
+// (measured; the kernels check), so an NG of a multiple of 8 puts a group on
+// one XCD: workgroups of the groups past the real ones return at once.  Not
+// padded where the padding would not fit the chip at one workgroup per CU.
+int persist_groups(int groups, int members);
 // Launches a kernel whose workgroups wait for each other: plain when the
 // occupancy query shows the whole grid resident at once, else cooperative.
 // args: the kernel's only argument.

@@ -107,8 +107,9 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_fwd_persist32(const Persist3
   constexpr int IT = RV * NCOL / P32_THREADS;   // gate values per thread
   constexpr int RPI = P32_THREADS / NCOL;       // rows between a thread's items
   const int H = a.H, B = a.B, Tn = a.Tn;
-  const int NG = 2 * a.NS;
+  const int NG = a.NG;
   const int g = blockIdx.x % NG, mem = blockIdx.x / NG;
+  if (g >= 2 * a.NS) return;   // padding (see persist_groups)
   const int d = g & 1, s = g >> 1;
   const int u0 = mem * PU;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -281,8 +282,9 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_bwd_persist32(const Persist3
   constexpr int MPP = (MEMS * KS + 3) / 4;                     // partial sums per thread of a quad
   constexpr int AS = (NCOL + 63) / 64 * 64 + 16;
   const int H = a.H, B = a.B, Tn = a.Tn;
-  const int NG = 2 * a.NS;
+  const int NG = a.NG;
   const int g = blockIdx.x % NG, mem = blockIdx.x / NG, nmem = gridDim.x / NG;
+  if (g >= 2 * a.NS) return;   // padding (see persist_groups)
   const int d = g & 1, s = g >> 1;
   const int u0 = mem * PU;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -536,11 +538,12 @@ hipError_t persist32_layer(bool backward, Persist32Args a, hipStream_t s) {
     c.b0 = b0;
     c.rows = std::min(p.chunk, a.B - b0);
     c.NS = (int)cdiv(c.rows, RV);
+    c.NG = solo ? 2 * c.NS : persist_groups(2 * c.NS, p.members);
     // tags of one call's launches never meet: the launch's position times T,
     // plus the step (1 .. T); T B <= 2^24 keeps the product below 2^32
     c.tag0 = (a.tag0 * (uint32_t)cdiv(a.B, p.chunk) + (uint32_t)(b0 / p.chunk)) * (uint32_t)a.Tn;
     const hipError_t e = persist_launch(backward ? "lstm_rec_bwd_persist32" : "lstm_rec_fwd_persist32", fn,
-                                        dim3(2 * c.NS * p.members), P32_THREADS, lds, &c, s);
+                                        dim3(c.NG * p.members), P32_THREADS, lds, &c, s);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
