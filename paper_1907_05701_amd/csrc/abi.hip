@@ -9,7 +9,7 @@
 #include <vector>
 
 #include "common.hpp"
-#include "gemm.hpp"
+#include "gemm_kc.hpp"
 #include "lstm_persist.hpp"
 
 static thread_local char g_err[512] = "";
@@ -46,6 +46,49 @@ int plan_splits(int64_t Mo, int64_t No, int64_t Kr, int BMt, int BNt, int BK, in
   s = std::min<int64_t>(s, std::max<int64_t>(kt / 4, 1));
   s = std::min<int64_t>(s, 16);
   return (int)std::max<int64_t>(s, 1);
+}
+
+// Tiles and splits of the deferred weight gradients (one grouped launch of
+// every layer's dW_ih and dW_hh): 256x256 blocks when they are 5 % faster by
+// the estimate of kc_plan.  One such block runs on a CU at a time and all are
+// about as long, so the blocks past the last whole round would take a round
+// of their own: the first products in launch order stay whole and the last
+// ones (layer 0 is the last) are split so that their shorter blocks fill it.
+static void plan_dw(const blstm_dims* d, Layout& L) {
+  const int64_t H = d->H, M = L.M, kt = cdiv(M, 64);
+  const int n = 2 * d->L;
+  int64_t tiles[2 * MAX_LAYERS], small = 0, total = 0;
+  double elems[2 * MAX_LAYERS];
+  for (int i = 0; i < n; ++i) {   // launch order: top layer first, dW_ih then dW_hh
+    const int l = d->L - 1 - i / 2;
+    const int64_t N = (i & 1) ? H : L.layer_in(l);
+    tiles[i] = 2 * cdiv(4 * H, 256) * cdiv(N, 256);
+    elems[i] = 2.0 * 4 * H * N;
+    small += 2 * cdiv(4 * H, 128) * cdiv(N, 128);
+    total += tiles[i];
+    L.sp_dw[i] = 1;
+  }
+  double lim = 0.95 * kc_us_small(small, kt);
+  if (4 * H < 192 || H < 192) return;
+  for (int j = 0; j <= n; ++j) {   // the products from j on are split
+    int64_t whole = 0, rest = 0;
+    double e = 0;
+    for (int i = 0; i < n; ++i) (i < j ? whole : rest) += tiles[i];
+    for (int i = j; i < n; ++i) e += elems[i];
+    for (int s = 2; s <= 8 && kt / s >= 8; ++s) {
+      if (j == n && s > 2) break;
+      const int64_t in_last = whole % 256 ? 256 - whole % 256 : 0;   // CUs idle in the whole blocks' last round
+      const int64_t left = rest * s - in_last * s;
+      const double t = kc_us_big((double)cdiv(whole, 256), kt) +
+                       (left > 0 ? kc_us_big((double)cdiv(left, 256), cdiv(kt, s)) : 0) +
+                       (j < n ? kc_us_partials(e, s) : 0);
+      if (t < lim) {
+        lim = t;
+        L.big_dw = true;
+        for (int i = 0; i < n; ++i) L.sp_dw[i] = i < j ? 1 : s;
+      }
+    }
+  }
 }
 
 static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -138,10 +181,25 @@ int make_layout(const blstm_dims* d, Layout* lo) {
     L.sp_dWhh[l] = lp ? 1 : plan_splits(4 * H, H, (int64_t)(d->T - 1) * d->B, BMt, BNt, BKt, 2, lp, false);
     const size_t hh_bytes = L.sp_dWhh[l] > 1 ? align256((size_t)L.sp_dWhh[l] * 2 * 4 * H * H * 4) : 0;
     L.sp_dX[l] = with_dx ? plan_splits(M, Dl, 8 * H, BMt, BNt, BKt, 1, lp, lp) : 1;
+    if (lp && with_dx) {
+      const KcPlan p = kc_plan(M, Dl, 8 * H, 1, L.sp_dX[l]);
+      L.big_dX[l] = p.big;
+      L.sp_dX[l] = p.splits;
+    }
     const size_t dx_bytes = L.sp_dX[l] > 1 ? align256((size_t)L.sp_dX[l] * M * Dl * 4) : 0;
     L.skp_hh[l] = ih_bytes;
     L.skp_dx[l] = ih_bytes + hh_bytes;
     skp = std::max(skp, ih_bytes + hh_bytes + dx_bytes);
+  }
+  if (lp) {
+    plan_dw(d, L);
+    size_t dw = 0;   // the deferred launch's partials (after the last dX)
+    for (int i = 0; i < 2 * d->L; ++i) {
+      const int64_t Nw = (i & 1) ? H : L.layer_in(d->L - 1 - i / 2);
+      L.skp_dw[i] = dw;
+      if (L.sp_dw[i] > 1) dw += align256((size_t)L.sp_dw[i] * 2 * 4 * H * Nw * 4);
+    }
+    skp = std::max(skp, dw);
   }
   L.SKP = a; a = align256(a + skp);
   L.SKP2 = a; a = align256(a + skp);   // split-K partials of the side-stream products
@@ -172,8 +230,18 @@ int make_layout(const blstm_dims* d, Layout* lo) {
   L.sp_z = es == 2 ? plan_splits(M, P, 2 * H, BMt, BNt, BKt, 1, true, true) : 1;
   if (L.sp_z > 1) hsk = std::max(hsk, (size_t)L.sp_z * M * P * 4);
   L.sp_dz = plan_splits(M, P, d->K, BMt, BNt, BKt, 1, es == 2, true);
+  if (es == 2) {
+    const KcPlan p = kc_plan(M, P, d->K, 1, L.sp_dz);
+    L.big_dz = p.big;
+    L.sp_dz = p.splits;
+  }
   hsk = std::max(hsk, (size_t)L.sp_dz * M * P * 4);  // dz always goes through partials
   L.sp_dWs = plan_splits(d->K, P, M, BMt, BNt, BKt, 1, es == 2, true);
+  if (es == 2) {
+    const KcPlan p = kc_plan(d->K, P, M, 1, L.sp_dWs);
+    L.big_dWs = p.big;
+    L.sp_dWs = p.splits;
+  }
   if (L.sp_dWs > 1) hsk = std::max(hsk, (size_t)L.sp_dWs * d->K * P * 4);
   L.sp_dWl = plan_splits(P, 2 * H, M, BMt, BNt, BKt, 1, es == 2, true);
   if (L.sp_dWl > 1) hsk = std::max(hsk, (size_t)L.sp_dWl * P * 2 * H * 4);

@@ -90,6 +90,11 @@ struct Layout {
   // split-K factors of the weight/input-gradient GEMMs (1 = direct store)
   int sp_dWih[MAX_LAYERS], sp_dWhh[MAX_LAYERS], sp_dX[MAX_LAYERS], sp_z, sp_dz, sp_dWs, sp_dWl, sp_dy;
   size_t skp_hh[MAX_LAYERS], skp_dx[MAX_LAYERS];   // byte offsets of the dW_hh / dX partials in SKP
+  // bf16: products in 256x256 blocks, and of the deferred weight gradients
+  // (dW_ih, dW_hh of each layer) the splits and byte offsets of the partials in SKP
+  bool big_dX[MAX_LAYERS], big_dw, big_dz, big_dWs;
+  int sp_dw[2 * MAX_LAYERS];
+  size_t skp_dw[2 * MAX_LAYERS];
   int layer_in(int l) const { return l == 0 ? D : 2 * H; }
   int layer_in_pitch(int l) const { return l == 0 ? Dp0 : 2 * H; }
 };

@@ -332,6 +332,9 @@ struct EpiStore {
   }
 };
 
+template <class E> struct EpiIsStore : std::false_type {};
+template <typename TO> struct EpiIsStore<EpiStore<TO>> : std::true_type {};
+
 template <typename TO>
 static inline EpiStore<TO> epi_store(TO* out, int64_t ld, int64_t M, int64_t N, int64_t zstride = 0,
                                      int64_t sstride = 0, const float* bias = nullptr,

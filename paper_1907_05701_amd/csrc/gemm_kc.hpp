@@ -373,7 +373,57 @@ typedef KcCfg<128, 128, 2, 4, 2> KcTile;
 // products with more 128x128 tiles than one round of two blocks per CU
 // (the gate projection, 448 instead of 672 blocks, and the logits)
 typedef KcCfg<192, 128, 2, 4, 2> KcTileTall;
+// 256x256 blocks (128 KB of LDS, one per CU, 128x64 per wave): each operand
+// byte staged and each fragment read feeds twice the products, 0.94 of the LDS
+// traffic a 128x128 block needs per product against 2.0.  Measured on one box,
+// 128x128 / 256x256: 8192^3 953 / 1134 TFLOP/s, weight gradients over 65536
+// frames (2048 x 1024 of both directions, split four ways) 598 / 1057, dz over
+// 65536 frames 826 / 989, dX there 907 / 982.  32-deep tiles in 3, 4 or 5
+// stages and 64x128 per wave: within 5 % or slower.
+typedef KcCfg<256, 256, 2, 4, 2> KcTileBig;
 static constexpr int64_t kc_round_blocks = 2 * 256;   // two blocks on each of 256 CUs
+
+// Estimated microseconds of a product, for choosing its tile and split: one
+// 128x128 block takes 0.565 us of a CU per 64-deep k-tile (two run at a time),
+// a 256x256 one 2.03 and 15 us for its start and its 256 KB of results, which
+// no other block of the CU covers; the last round of the chip counts whole, or
+// 0.35 of a round when many rounds let it overlap; split-K partials cost their
+// bytes at 4.5 TB/s and a launch.  (Predicted / measured, us: weight gradients
+// of six layers over 2688 frames 218 / 215 in 192-row blocks and 219 / 226 in
+// 256x256 ones, of two layers over 65536 frames 2310 / 2200 and 1420 / 1495,
+// dX there 578 / 563 and 580 / 585.)
+static inline double kc_rounds(int64_t blocks, int64_t slots) {
+  return std::min((double)cdiv(blocks, slots), (double)blocks / (double)slots + 0.35);
+}
+static inline double kc_us_small(int64_t blocks, int64_t ktiles) {
+  return kc_rounds(blocks, kc_round_blocks) * 2 * (double)ktiles * 0.565;
+}
+static inline double kc_us_big(double rounds, int64_t ktiles) { return rounds * ((double)ktiles * 2.03 + 15); }
+static inline double kc_us_partials(double elems, int splits) {
+  return splits > 1 ? (splits + 1) * elems * 4 / 4.5e6 + 3 : 0;
+}
+
+struct KcPlan {
+  bool big;     // 256x256 blocks
+  int splits;
+};
+// Tile and split of one product launched alone, given the split that
+// 128x128 blocks would take: 256x256 blocks where they are at least 5 % faster
+// by the estimate above.
+static inline KcPlan kc_plan(int64_t M, int64_t N, int64_t K, int batches, int small_splits) {
+  KcPlan best{false, small_splits};
+  if (M < 192 || N < 192) return best;
+  const int64_t kt = cdiv(K, 64);
+  const double elems = (double)batches * (double)M * (double)N;
+  double lim = 0.95 * (kc_us_small(cdiv(M, 128) * cdiv(N, 128) * batches * small_splits, cdiv(kt, small_splits)) +
+                       kc_us_partials(elems, small_splits));
+  const int64_t n = cdiv(M, 256) * cdiv(N, 256) * batches;
+  for (int s = 1; s <= 8 && kt / s >= 8; ++s) {
+    const double t = kc_us_big(kc_rounds(n * s, 256), cdiv(kt, s)) + kc_us_partials(elems, s);
+    if (t < lim) { lim = t; best = KcPlan{true, s}; }
+  }
+  return best;
+}
 
 // Whether a product with K-contiguous A goes to the 192-row blocks.
 static inline bool kc_tall(int64_t M, int64_t N, int batches, int splits) {
@@ -389,9 +439,16 @@ static inline bool kc_eligible(const Opnd& A, const Opnd& B, int64_t K, bool akc
 template <typename T, bool AKC, bool BKC, int VA, int VB, class Epi>
 static inline void gemm_launch(const char* name, hipStream_t s, const Opnd& A, const Opnd& B,
                                int64_t M, int64_t N, int64_t K, int batches, int splits,
-                               const Epi& epi) {
+                               const Epi& epi, bool big = false) {
   if constexpr (std::is_same<T, bf16>::value) {
     if (kc_eligible(A, B, K, AKC, BKC)) {
+      // (the logits epilogues count on the strips of the smaller tiles)
+      if constexpr (EpiIsStore<Epi>::value) {
+        if (big) {
+          gemm_kc_launch<KcTileBig, AKC, BKC>(name, s, A, B, M, N, K, batches, splits, epi);
+          return;
+        }
+      }
       if constexpr (AKC) {
         if (kc_tall(M, N, batches, splits)) {
           gemm_kc_launch<KcTileTall, AKC, BKC>(name, s, A, B, M, N, K, batches, splits, epi);
@@ -466,8 +523,11 @@ static inline bool gemm_kc_group_launch_cfg(const char* name, hipStream_t s, int
 // single product does) and a k range of at most 16384 (measured: the
 // weight gradients over 2688 frames 225 -> 204 us, dX at 65536 frames
 // 3.11 -> 2.75 ms; but the weight gradients over 65536 frames 5.5 -> 6.1 ms).
+// big: 256x256 blocks (the caller's plan).
 template <bool AKC, bool BKC, class Epi>
-static inline bool gemm_kc_group_launch(const char* name, hipStream_t s, int n, const KcItem* it, const Epi* epi) {
+static inline bool gemm_kc_group_launch(const char* name, hipStream_t s, int n, const KcItem* it, const Epi* epi,
+                                        bool big) {
+  if (big) return gemm_kc_group_launch_cfg<KcTileBig, AKC, BKC>(name, s, n, it, epi);
   int64_t blocks = 0;
   bool tall = n >= 1 && n <= KC_MAX_GROUP;
   for (int i = 0; tall && i < n; ++i) {

@@ -1084,15 +1084,16 @@ static int head_impl(const Layout& lo, const float* theta, const T* W, const T* 
   const Opnd Az = opnd(DS, Kp, Kp, M), Bz2 = opnd(W + lo.Ws, P, P, K);
   bool paired = false;
   if constexpr (lp) {
-    if (lo.sp_dWs == 1 && lo.sp_dz > 1)
+    if (lo.sp_dWs == 1 && lo.sp_dz > 1 && !lo.big_dWs && !lo.big_dz)
       paired = gemm_kc_pair_launch<false, false, true, false>(
           "gemm_dws_dz", s, As, Bs, K, P, M, 1, epi_store<float>(grad + lo.Ws, P, K, P, 0), Az, Bz2, M, P, K,
           lo.sp_dz, epi_store<float>(part, P, M, P, (int64_t)lo.sp_dz * M * P, M * P));
     if (paired) splitk_reduce_launch<T>(s, part, lo.sp_dz, 1, M, P, DZ, P, 0, DZT, P);
   }
   if (!paired) {
-    gemm_f32<T, false, false, V, V>("gemm_dws", s, As, Bs, K, P, M, 1, lo.sp_dWs, grad + lo.Ws, P, 0, part);
-    gemm_f32<T, true, false, V, V>("gemm_dz", s, Az, Bz2, M, P, K, 1, lo.sp_dz, DZ, P, 0, part, DZT, P);
+    gemm_f32<T, false, false, V, V>("gemm_dws", s, As, Bs, K, P, M, 1, lo.sp_dWs, grad + lo.Ws, P, 0, part,
+                                        nullptr, 0, lo.big_dWs);
+    gemm_f32<T, true, false, V, V>("gemm_dz", s, Az, Bz2, M, P, K, 1, lo.sp_dz, DZ, P, 0, part, DZT, P, lo.big_dz);
   }
   // db_l = sum over frames of dz (bf16: already summed with db_s)
   if constexpr (!lp) colsum<float>("colsum_dbl", s, DZ, M, P, P, csp, P, 0, grad + lo.bl, nullptr);

@@ -751,8 +751,7 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
                     part_ih};
       g[1] = F32Job{Ah, Bh, 4 * H, H, Kr, 2, lo.sp_dWhh[l], grad + lo.Whh[l][0], H, lo.Whh[l][1] - lo.Whh[l][0],
                     part_hh};
-      // the whole k range per tile (the deferred launch has tiles enough;
-      // the side-stream path does the same, so that both sum alike)
+      // the side stream's products take the whole k range per tile
       g[0].splits = g[1].splits = 1;
       const bool dx_here = !side && l > 0;
       if (dx_here)
@@ -780,11 +779,15 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
                                             g[i].K, g[i].batches, 1, g[i].dst, g[i].ld, g[i].dst_zstride, g[i].part);
         }
       } else {
-        deferred[nd++] = g[0];
-        deferred[nd++] = g[1];
+        for (int i = 0; i < 2; ++i) {
+          g[i].splits = lo.sp_dw[nd];
+          g[i].part = (float*)((char*)part + lo.skp_dw[nd]);
+          deferred[nd++] = g[i];
+        }
         if (dx_here) {
           ReduceGroup held;
-          if (gemm_f32_group<true, false>("gemm_bwd_group", s, 1, &g[2], csj, held_db ? &held : nullptr)) {
+          if (gemm_f32_group<true, false>("gemm_bwd_group", s, 1, &g[2], csj, held_db ? &held : nullptr,
+                                          lo.big_dX[l])) {
             db_done = db_done || csj != nullptr;
             if (held_db && held.n == 1) pending_dy = held;
             else if (held_db) reduce_group_launch(s, held);
@@ -843,11 +846,11 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
   // the chip is a partial one)
   for (int i0 = 0; i0 < nd; i0 += KC_MAX_GROUP) {
     const int n = std::min(KC_MAX_GROUP, nd - i0);
-    if (!gemm_f32_group<false, false>("gemm_dw_group", s, n, deferred + i0)) {
+    if (!gemm_f32_group<false, false>("gemm_dw_group", s, n, deferred + i0, nullptr, nullptr, lo.big_dw)) {
       for (int i = i0; i < i0 + n; ++i) {
         const F32Job& j = deferred[i];
         gemm_f32<T, false, false, V, V>((i & 1) ? "gemm_dwhh" : "gemm_dwih", s, j.A, j.B, j.M, j.N, j.K, j.batches,
-                                       1, j.dst, j.ld, j.dst_zstride, part);
+                                       j.splits, j.dst, j.ld, j.dst_zstride, j.part);
       }
     }
   }

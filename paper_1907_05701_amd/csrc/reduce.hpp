@@ -146,14 +146,15 @@ static inline void splitk_reduce_launch(hipStream_t s, float* part, int splits, 
 template <typename T, bool AKC, bool BKC, int VA, int VB>
 static inline void gemm_f32(const char* name, hipStream_t s, const Opnd& A, const Opnd& B, int64_t M,
                             int64_t N, int64_t K, int batches, int splits, float* dst, int64_t ld,
-                            int64_t dst_zstride, float* part, T* dstc = nullptr, int64_t ldc = 0) {
+                            int64_t dst_zstride, float* part, T* dstc = nullptr, int64_t ldc = 0,
+                            bool big = false) {
   if (splits == 1 && !dstc) {
     gemm_launch<T, AKC, BKC, VA, VB>(name, s, A, B, M, N, K, batches, 1,
-                                     epi_store<float>(dst, ld, M, N, dst_zstride));
+                                     epi_store<float>(dst, ld, M, N, dst_zstride), big);
     return;
   }
   gemm_launch<T, AKC, BKC, VA, VB>(name, s, A, B, M, N, K, batches, splits,
-                                   epi_store<float>(part, N, M, N, (int64_t)splits * M * N, M * N));
+                                   epi_store<float>(part, N, M, N, (int64_t)splits * M * N, M * N), big);
   splitk_reduce_launch<T>(s, part, splits, batches, M, N, dst, ld, dst_zstride, dstc, ldc);
 }
 
@@ -272,7 +273,7 @@ static inline bool colsum_job_launch(const char* name, hipStream_t s, const ColS
 // the caller to launch later or to leave to a consumer of the partials.
 template <bool AKC, bool BKC>
 static inline bool gemm_f32_group(const char* name, hipStream_t s, int n, const F32Job* jb,
-                                  const ColSumJob* cs = nullptr, ReduceGroup* held = nullptr) {
+                                  const ColSumJob* cs = nullptr, ReduceGroup* held = nullptr, bool big = false) {
   if (n < 1 || n > KC_MAX_GROUP || (cs && (n == KC_MAX_GROUP || !colsum_job_ok(*cs)))) return false;
   KcItem it[KC_MAX_GROUP];
   EpiStore<float> e[KC_MAX_GROUP];
@@ -304,7 +305,7 @@ static inline bool gemm_f32_group(const char* name, hipStream_t s, int n, const 
     rg.j[rg.n] = colsum_reduce_job(*cs, rblocks);
     rblocks += (int)cdiv((int64_t)rg.j[rg.n++].count, 256);
   }
-  if (!gemm_kc_group_launch<AKC, BKC>(name, s, n, it, e)) return false;
+  if (!gemm_kc_group_launch<AKC, BKC>(name, s, n, it, e, big)) return false;
   if (held) *held = rg;
   else if (rg.n) reduce_group_launch(s, rg);
   return true;
