@@ -440,9 +440,13 @@ __device__ __forceinline__ void dma4(__amdgpu_buffer_rsrc_t r, uint32_t byte_off
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr_t)lds_wave_base, 4, byte_off, 0, 0, 0);
 }
 // buffer resource over rows [0, rows) of rowbytes bytes from base (none
-// when rows <= 0; the caller keeps rows * rowbytes below 2^31 - 16)
+// when rows <= 0; the caller keeps rows * rowbytes below 2^31 - 16), or with
+// CLIP over the first chunk of them only: for matrices past 2^31 bytes (at
+// 2688 frames the clipped form costs 72 -> 79 and 82 -> 96 us per pass)
+template <bool CLIP>
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_rows(const void* base, int rows, int rowbytes) {
-  return __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, max(rows, 0) * rowbytes, 0x00020000);
+  const int n = CLIP ? min(max(rows, 0), LF) : max(rows, 0);
+  return __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, n * rowbytes, 0x00020000);
 }
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -488,7 +492,7 @@ __device__ __forceinline__ float sum16x32(float x) {
 // s_getreg operand: HW_ID (register 4), bits 4-5 (the SIMD)
 #define HWREG_HW_ID_SIMD ((1 << 11) | (4 << 6) | 4)
 
-template <int PASS, bool FOLD>
+template <int PASS, bool FOLD, bool CLIP>
 __global__ __launch_bounds__(512) void logits_block_kernel(const LogitsArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -528,12 +532,12 @@ __global__ __launch_bounds__(512) void logits_block_kernel(const LogitsArgs a) {
   auto issue = [&](int j) {
     const int f0 = j * LF, left = M - f0;
     char* st = lds + (j % LSL) * LSLOT;
-    const __amdgpu_buffer_rsrc_t rz = rsrc_rows(a.Z + (int64_t)f0 * P, left, P * 2);
+    const __amdgpu_buffer_rsrc_t rz = rsrc_rows<CLIP>(a.Z + (int64_t)f0 * P, left, P * 2);
 #pragma unroll
     for (int q = 0; q < 4; ++q) dma16(rz, zoff[q], st + (q * 8 + w) * LBLK);
     if constexpr (PASS == 2) {
-      if (w == 0) dma4(rsrc_rows(a.lse + f0, left, 4), lane * 4, lds + LG_LSE + (j % LSL) * LF * 4);
-      else if (w == 1) dma4(rsrc_rows(a.labels + f0, left, 4), lane * 4, lds + LG_LAB + (j % LSL) * LF * 4);
+      if (w == 0) dma4(rsrc_rows<CLIP>(a.lse + f0, left, 4), lane * 4, lds + LG_LSE + (j % LSL) * LF * 4);
+      else if (w == 1) dma4(rsrc_rows<CLIP>(a.labels + f0, left, 4), lane * 4, lds + LG_LAB + (j % LSL) * LF * 4);
       else dma4(rz, DMA_OFF_NONE, lds + LG_SCRATCH);
     }
   };
@@ -588,7 +592,7 @@ __global__ __launch_bounds__(512) void logits_block_kernel(const LogitsArgs a) {
       v = make_float2(m, sm);
     }
     const int f0 = j * LF;
-    const __amdgpu_buffer_rsrc_t rs = rsrc_rows(a.stats + (int64_t)f0 * a.nstrip, M - f0, a.nstrip * 8);
+    const __amdgpu_buffer_rsrc_t rs = rsrc_rows<CLIP>(a.stats + (int64_t)f0 * a.nstrip, M - f0, a.nstrip * 8);
     const uint32_t off = w == 0 && j >= 0 ? (uint32_t)((lane * a.nstrip + (int)blockIdx.x) * 8) : DMA_OFF_NONE;
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2u32, v), rs, (int)off, 0, 0);
   };
@@ -622,8 +626,8 @@ __global__ __launch_bounds__(512) void logits_block_kernel(const LogitsArgs a) {
       }
     } else {
       const int f0 = j * LF;
-      const __amdgpu_buffer_rsrc_t rd = rsrc_rows(a.ds + (int64_t)f0 * a.Kp, M - f0, a.Kp * 2);
-      const __amdgpu_buffer_rsrc_t rr = rsrc_rows(a.rowloss + f0, M - f0, 4);
+      const __amdgpu_buffer_rsrc_t rd = rsrc_rows<CLIP>(a.ds + (int64_t)f0 * a.Kp, M - f0, a.Kp * 2);
+      const __amdgpu_buffer_rsrc_t rr = rsrc_rows<CLIP>(a.rowloss + f0, M - f0, 4);
 #pragma unroll
       for (int jn = 0; jn < 2; ++jn) {
         const float Lc = FOLD ? fmaf(L[jn], LOG2E_F, -a.l2s) : L[jn] * LOG2E_F;
@@ -670,7 +674,7 @@ __global__ __launch_bounds__(512) void logits_block_kernel(const LogitsArgs a) {
   // chunk j
   // NST store instructions that write nothing (every offset out of range)
   auto no_stores = [&]() {
-    const __amdgpu_buffer_rsrc_t rr = rsrc_rows(a.rowloss, 0, 4);
+    const __amdgpu_buffer_rsrc_t rr = rsrc_rows<CLIP>(a.rowloss, 0, 4);
 #pragma unroll
     for (int q = 0; q < NST; ++q) __builtin_amdgcn_raw_buffer_store_b32(0u, rr, (int)DMA_OFF_NONE, 0, 0);
   };
@@ -1017,26 +1021,29 @@ static int head_impl(const Layout& lo, const float* theta, const T* W, const T* 
     // (the buffer resource's range), 16-byte aligned rows
     const int nblk = (int)cdiv(K, LB);
     const bool blk = logits_block() && P % 8 == 0 && P <= 8 * LKS * 4 && M > 0 &&
-                     (int64_t)rup(K, LB) * P * 2 < 0x7ffffff0 && M * P * 2 < 0x7ffffff0 &&
-                     M * Kp * 2 < 0x7ffffff0 && M * nblk * 8 < 0x7ffffff0 && M * 4 < 0x7ffffff0 &&
+                     (int64_t)rup(K, LB) * P * 2 < 0x7ffffff0 && (int64_t)LF * Kp * 2 < 0x7ffffff0 &&
+                     (int64_t)LF * nblk * 8 < 0x7ffffff0 &&
                      ((uintptr_t)(W + lo.Ws) & 15) == 0 && ((uintptr_t)Z & 15) == 0 && ((uintptr_t)DS & 15) == 0;
     int nrows_dbp;
     if (blk) {
-      static std::atomic<uint64_t> raised1{0}, raised2{0}, raised3{0};
+      // the whole of each matrix within a buffer resource's 31 bits, else one chunk of it
+      const bool clip = M * Kp * 2 >= 0x7ffffff0 || M * P * 2 >= 0x7ffffff0 || M * nblk * 8 >= 0x7ffffff0 ||
+                        M * 4 >= 0x7ffffff0;
       const bool fold = l2s == l2s;
-      const void* k2 = fold ? (const void*)logits_block_kernel<2, true> : (const void*)logits_block_kernel<2, false>;
-      kc_raise_lds_limit((const void*)logits_block_kernel<1, true>, LG_LDS, raised1);
-      kc_raise_lds_limit(k2, LG_LDS, fold ? raised2 : raised3);
+      typedef void (*Logits)(const LogitsArgs);
+      const Logits k1 = clip ? logits_block_kernel<1, true, true> : logits_block_kernel<1, true, false>;
+      const Logits k2 = clip ? (fold ? logits_block_kernel<2, true, true> : logits_block_kernel<2, false, true>)
+                             : (fold ? logits_block_kernel<2, true, false> : logits_block_kernel<2, false, false>);
+      static std::atomic<uint64_t> raised1[2], raised2[4];
+      kc_raise_lds_limit((const void*)k1, LG_LDS, raised1[clip]);
+      kc_raise_lds_limit((const void*)k2, LG_LDS, raised2[2 * clip + fold]);
       static_assert(LB == HB_STRIP, "one share row per class block");
       LogitsArgs la{(const bf16*)(W + lo.Ws), (const bf16*)Z, theta + lo.bs, K, (int)M, P, stats, nblk, lse, labels,
                     (bf16*)DS, Kp, RL, grad + lo.bs, (float*)(hws + lo.DBLP), scale, l2s};
-      BLSTM_LAUNCH("logits_blk", (logits_block_kernel<1, true>), dim3((unsigned)nblk), dim3(512), LG_LDS, s, la);
+      BLSTM_LAUNCH("logits_blk", k1, dim3((unsigned)nblk), dim3(512), LG_LDS, s, la);
       BLSTM_LAUNCH("logit_lse", logit_lse_kernel, dim3((unsigned)cdiv(M, 4)), dim3(256), 0, s, stats, nblk, M, labels,
                    K, lse, RL);
-      if (fold)
-        BLSTM_LAUNCH("logits_ds_blk", (logits_block_kernel<2, true>), dim3((unsigned)nblk), dim3(512), LG_LDS, s, la);
-      else
-        BLSTM_LAUNCH("logits_ds_blk", (logits_block_kernel<2, false>), dim3((unsigned)nblk), dim3(512), LG_LDS, s, la);
+      BLSTM_LAUNCH("logits_ds_blk", k2, dim3((unsigned)nblk), dim3(512), LG_LDS, s, la);
       nrows_dbp = 1;
     } else {
       const int nstrip = (int)cdiv(K, srows);
