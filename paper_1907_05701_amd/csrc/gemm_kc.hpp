@@ -373,6 +373,13 @@ typedef KcCfg<128, 128, 2, 4, 2> KcTile;
 // products with more 128x128 tiles than one round of two blocks per CU
 // (the gate projection, 448 instead of 672 blocks, and the logits)
 typedef KcCfg<192, 128, 2, 4, 2> KcTileTall;
+// 64-row blocks (48 KB, three per CU) for products with at most one 128x128
+// block per CU: twice the workgroups, each with three quarters of the bytes
+// per k-tile (a launch this small is bound by the 64 bytes per clock that one
+// CU takes in).  Measured 128x128 / 64x128: the input projection of 336 frames
+// at 1024 wide (96 blocks) 16.2 / 12.6 us, weight gradients of 320 cells over
+// 3700 frames (200 blocks) 49 / 40; with 504 blocks (dX at 2688 frames) 33 / 41.
+typedef KcCfg<64, 128, 2, 4, 2> KcTileLow;
 // 256x256 blocks (128 KB of LDS, one per CU, 128x64 per wave): each operand
 // byte staged and each fragment read feeds twice the products, 0.94 of the LDS
 // traffic a 128x128 block needs per product against 2.0.  Measured on one box,
@@ -429,6 +436,7 @@ static inline KcPlan kc_plan(int64_t M, int64_t N, int64_t K, int batches, int s
 static inline bool kc_tall(int64_t M, int64_t N, int batches, int splits) {
   return M >= KcTileTall::BM && cdiv(M, 128) * cdiv(N, 128) * batches * splits > kc_round_blocks;
 }
+static inline bool kc_low(int64_t blocks) { return blocks <= 256; }
 // Whether a product can take the direct-to-LDS kernel.
 static inline bool kc_eligible(const Opnd& A, const Opnd& B, int64_t K, bool akc, bool bkc) {
   return kc_operand_ok(A, K, akc) && kc_operand_ok(B, K, bkc);
@@ -446,6 +454,10 @@ static inline void gemm_launch(const char* name, hipStream_t s, const Opnd& A, c
       if constexpr (EpiIsStore<Epi>::value) {
         if (big) {
           gemm_kc_launch<KcTileBig, AKC, BKC>(name, s, A, B, M, N, K, batches, splits, epi);
+          return;
+        }
+        if (kc_low(cdiv(M, 128) * cdiv(N, 128) * batches * splits)) {
+          gemm_kc_launch<KcTileLow, AKC, BKC>(name, s, A, B, M, N, K, batches, splits, epi);
           return;
         }
       }
@@ -529,11 +541,12 @@ static inline bool gemm_kc_group_launch(const char* name, hipStream_t s, int n, 
                                         bool big) {
   if (big) return gemm_kc_group_launch_cfg<KcTileBig, AKC, BKC>(name, s, n, it, epi);
   int64_t blocks = 0;
-  bool tall = n >= 1 && n <= KC_MAX_GROUP;
-  for (int i = 0; tall && i < n; ++i) {
+  bool tall = true;
+  for (int i = 0; i < n; ++i) {
     blocks += cdiv(it[i].M, 128) * cdiv(it[i].N, 128) * it[i].batches * it[i].splits;
-    tall = it[i].M >= KcTileTall::BM && it[i].K <= 16384;
+    tall = tall && it[i].M >= KcTileTall::BM && it[i].K <= 16384;
   }
+  if (kc_low(blocks)) return gemm_kc_group_launch_cfg<KcTileLow, AKC, BKC>(name, s, n, it, epi);
   if (tall && blocks > kc_round_blocks) return gemm_kc_group_launch_cfg<KcTileTall, AKC, BKC>(name, s, n, it, epi);
   return gemm_kc_group_launch_cfg<KcTile, AKC, BKC>(name, s, n, it, epi);
 }

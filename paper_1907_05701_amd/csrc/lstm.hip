@@ -448,11 +448,16 @@ static bool fuse_dy() {
   return !(e && e[0] == '0');
 }
 
-// Whether the persistent forward computes the input projection itself
-// (ADPSGD_BLSTM_FUSE_GX=0: a separate product launch, for comparisons).
-static bool fuse_gx() {
+// Whether the persistent forward computes the input projection itself: when
+// its workgroups fill most of the chip (a launch of a few workgroups leaves
+// the projection to them alone: full model, B = 16 431 us fused, 411 as a
+// separate product; H = 320, B = 100 with 130 workgroups 415 / 402; at B = 128,
+// 256 workgroups, 1538 / 1550).  ADPSGD_BLSTM_FUSE_GX=0 or 1 forces either, for
+// comparisons (bit-identical).
+static bool fuse_gx(int H, int B) {
   const char* e = getenv("ADPSGD_BLSTM_FUSE_GX");
-  return !(e && e[0] == '0');
+  if (e && (e[0] == '0' || e[0] == '1')) return e[0] == '1';
+  return persist_workgroups(H, B) >= 192;
 }
 
 template <typename T>
@@ -497,7 +502,7 @@ static int fwd_impl(const Layout& lo, const float* theta, const T* W, const floa
     const int64_t ldw = (l == 0 && WP0) ? Dpl : Dl;
     const int64_t wih_d = (l == 0 && WP0) ? (int64_t)4 * H * Dpl : lo.Wih[l][1] - lo.Wih[l][0];
     const int kin = (l == 0 && WP0) ? Dpl : Dl;
-    const bool fuse = persist && std::is_same<T, bf16>::value && fuse_gx() && kin % 8 == 0 && Dpl % 8 == 0 &&
+    const bool fuse = persist && std::is_same<T, bf16>::value && fuse_gx(H, B) && kin % 8 == 0 && Dpl % 8 == 0 &&
                       ldw % 8 == 0 && wih_d % 8 == 0 && ((uintptr_t)Xl & 15) == 0 && ((uintptr_t)wih & 15) == 0;
     auto launch_gx = [&]() {
       if (l == 0 && WP0) {

@@ -1065,6 +1065,11 @@ int persist_rows_per_workgroup(int H, int B) {
   return persist_plan(H, B, &RV, &chunk) ? RV : 16;
 }
 
+int persist_workgroups(int H, int B) {
+  int RV, chunk;
+  return persist_plan(H, B, &RV, &chunk) ? 2 * (int)cdiv(chunk, RV) * (H / PU) : 0;
+}
+
 bool persist_bwd_dy_partials_ok(int H, int B, int T) {
   int RV, chunk;
   if (!persist_plan(H, B, &RV, &chunk)) return false;

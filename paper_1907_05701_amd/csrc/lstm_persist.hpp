@@ -124,6 +124,8 @@ bool persist_bwd_dy_partials_ok(int H, int B, int T);
 // True if the persistent kernels handle this H (a multiple of 64, at most
 // 512: a member's 256 W_hh rows fit in its registers); any T.
 bool persist_supported(int H, int T);
+// Workgroups of a layer's largest launch for this H and B.
+int persist_workgroups(int H, int B);
 // Batch rows per persistent workgroup (8 or 16) for this H and B: the row
 // block of the BPTT's bias partial sums (PersistArgs::DBP).
 int persist_rows_per_workgroup(int H, int B);
