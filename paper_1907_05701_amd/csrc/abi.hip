@@ -31,18 +31,31 @@ int blstm_check_launch(const char* what) {
 extern "C" const char* blstm_last_error(void) { return g_err; }
 
 // Split-K factor of a product with Mo x No outputs (per batch) and Kr-long
-// reductions: enough workgroups to cover the chip, at least 4 k-tiles per
-// split, below 256 tiles.  bf16 (direct-to-LDS kernel) aims at 256
-// workgroups (measured: more splits cost more in the partial reduction than
-// they gain), float32 at 512.
+// reductions.
+// bf16 (direct-to-LDS kernel): enough workgroups to cover the chip, at least 4
+// k-tiles per split, below 256 tiles; aims at 256 workgroups (measured: more
+// splits cost more in the partial reduction than they gain).
+// float32: the split of least estimated time; a 64x64 block takes 0.25 us of a
+// CU per 16-deep k-step, and partials cost their bytes at 4.5 TB/s and a
+// launch.
 int plan_splits(int64_t Mo, int64_t No, int64_t Kr, int BMt, int BNt, int BK, int batches, bool lp, bool alone) {
   const int64_t tiles = cdiv(Mo, BMt) * cdiv(No, BNt) * batches;
-  if (tiles >= 256) return 1;
-  // a product launched alone (bf16) fills one round of two blocks per CU
-  // without starting a second; the backward layer products share a grouped
-  // launch and split to half a round each
-  int64_t s = lp && alone ? std::max<int64_t>(512 / tiles, 1) : cdiv(lp ? 256 : 512, tiles);
   const int64_t kt = cdiv(Kr, BK);
+  if (!lp) {
+    int best = 1;
+    double lim = 0;
+    for (int s = 1; s <= 16 && (s == 1 || kt / s >= 4); ++s) {
+      const double t = (double)cdiv(tiles * s, 256) * (double)cdiv(kt, s) * 0.25 +
+                       kc_us_partials((double)batches * (double)Mo * (double)No, s);
+      if (s == 1 || t < 0.95 * lim) { best = s; lim = t; }
+    }
+    return best;
+  }
+  if (tiles >= 256) return 1;
+  // a product launched alone fills one round of two blocks per CU without
+  // starting a second; the backward layer products share a grouped launch and
+  // split to half a round each
+  int64_t s = alone ? std::max<int64_t>(512 / tiles, 1) : cdiv(256, tiles);
   s = std::min<int64_t>(s, std::max<int64_t>(kt / 4, 1));
   s = std::min<int64_t>(s, 16);
   return (int)std::max<int64_t>(s, 1);

@@ -51,18 +51,19 @@ struct KcArgs {
 
 // Workgroup w runs on XCD w % 8.  The first 8*(total/8) workgroups are dealt
 // so that XCD x takes logical tiles [x*q, (x+1)*q) in order; logical tiles
-// run in groups of `gm` tile rows with the rows fastest, so the workgroups an
+// run in groups of `group` tile rows with the rows fastest, so the workgroups an
 // XCD holds at once cover a compact block of A and B rows (L2 reuse).
-__device__ __forceinline__ void kc_tile_of(const KcArgs& p, int w, int& zs, int& tm, int& tn) {
+template <class Args>
+__device__ __forceinline__ void kc_tile_of(const Args& p, int w, int group, int& zs, int& tm, int& tn) {
   const int q = p.total / 8;
   const int L = w < 8 * q ? (w % 8) * q + w / 8 : w;
   const int per = p.ntm * p.ntn;
   zs = L / per;
   const int t = L % per;
-  const int grp = t / (p.gm * p.ntn);
-  const int gm = min(p.gm, p.ntm - grp * p.gm);
-  const int in = t - grp * p.gm * p.ntn;
-  tm = grp * p.gm + in % gm;
+  const int grp = t / (group * p.ntn);
+  const int gm = min(group, p.ntm - grp * group);
+  const int in = t - grp * group * p.ntn;
+  tm = grp * group + in % gm;
   tn = in / gm;
 }
 
@@ -120,6 +121,8 @@ __device__ __forceinline__ void kc_lds_wait(bf16x8 (&f)[N]) {
 #pragma unroll
   for (int i = 0; i < N; ++i) asm volatile("" : "+v"(f[i]));
 }
+
+#include "gemm_f32.hpp"
 
 // Staging and fragment reads of one operand (rows BMN of the tile's M or N
 // side, BK deep), K-contiguous (KC) or MN-contiguous.
@@ -203,7 +206,7 @@ __device__ __forceinline__ void kc_gemm_tile(const KcArgs& p, const Epi& epi, in
   const int wm = wid % WM, wn = wid / WM;
   if (w >= p.total) return;
   int zs, tm, tn;
-  kc_tile_of(p, w, zs, tm, tn);
+  kc_tile_of(p, w, p.gm, zs, tm, tn);
   const int z = zs / p.splits, sp = zs % p.splits;
   const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
   const int64_t kbeg = (int64_t)sp * p.ksplit;
@@ -474,6 +477,9 @@ static inline void gemm_launch(const char* name, hipStream_t s, const Opnd& A, c
       gemm_launch_cfg<T, GemmCfgK32, AKC, BKC, VA, VB>(name, s, A, B, M, N, K, batches, splits, epi);
       return;
     }
+  }
+  if constexpr (std::is_same<T, float>::value) {
+    if (gemm_f32_dma<AKC, BKC>(name, s, A, B, M, N, K, batches, splits, epi)) return;
   }
   gemm_launch_cfg<T, GemmCfg<T>, AKC, BKC, VA, VB>(name, s, A, B, M, N, K, batches, splits, epi);
 }

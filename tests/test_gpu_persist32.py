@@ -23,3 +23,12 @@ def test_float32_recurrence_plan_edges(gpu_lib, H, T, B):
 
 def test_float32_recurrence_many_steps(gpu_lib):
     run_step_and_compare(dict(L=1, D=8, H=288, P=8, K=10, T=70, B=7), "fp32", FP32_TOL, seed=18, check_update=False)
+
+
+@pytest.mark.parametrize("shape", [
+    dict(L=2, D=12, H=80, P=72, K=133, T=7, B=11),      # 77 frames, 133 classes (136 padded): partial blocks, k past whole chunks
+    dict(L=2, D=36, H=144, P=40, K=260, T=33, B=2),     # 66 frames: a two-row block, k of two and a bit k-tiles
+    dict(L=2, D=260, H=256, P=128, K=600, T=9, B=64),   # split dX and dz, whole blocks
+], ids=lambda s: f"H{s['H']}_M{s['T'] * s['B']}")
+def test_float32_products_at_block_edges(gpu_lib, shape):
+    run_step_and_compare(shape, "fp32", FP32_TOL, seed=19)
