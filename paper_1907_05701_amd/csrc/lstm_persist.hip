@@ -5,7 +5,7 @@
 // Work split.  The batch is cut into slices of RV rows (8 when all the
 // batch's 8-row slices fit one launch at one workgroup per CU, else 16,
 // with launches of up to 16 slices), each on 16-row MFMA tiles;
-// a group of NM = H/64 workgroups ("members") owns one (direction, slice)
+// a group of NM = ceil(H/64) workgroups ("members") owns one (direction, slice)
 // pair, and member m owns hidden units [64m, 64m + 64), i.e. 256 gate rows
 // of W_hh (256 KB at H = 512: 128 VGPRs in each of the workgroup's 8
 // waves).  Eight members per group instead of sixteen halves the chip-wide
@@ -196,17 +196,17 @@ __device__ __forceinline__ void gx_prologue(const PersistArgs& a, char* lds, int
   // W_ih rows of this lane's loads (instruction q 8 + w fills tile rows
   // RPI ins .. RPI ins + RPI - 1; tile row br is gate br / 64 of unit
   // u0 + br % 64)
-  int64_t wrow[QB];
+  int64_t wrow[QB];   // negative: a unit past H (reads as zeros)
 #pragma unroll
   for (int q = 0; q < QB; ++q) {
     const int br = (q * 8 + w) * RPI + lr;
-    wrow[q] = ((int64_t)(br >> 6) * H + u0 + (br & 63)) * a.ldw;
+    wrow[q] = u0 + (br & 63) < H ? ((int64_t)(br >> 6) * H + u0 + (br & 63)) * a.ldw : -1;
   }
   float bv[FN];
 #pragma unroll
   for (int jn = 0; jn < FN; ++jn) {
     const int n = 32 * w + jn * 16 + fr;
-    const int64_t gi = (d ? a.b_d : 0) + (int64_t)(n >> 6) * H + u0 + (n & 63);
+    const int64_t gi = (d ? a.b_d : 0) + (int64_t)(n >> 6) * H + min(u0 + (n & 63), H - 1);
     float v = 0.f;
     v += a.bih[gi];
     v += a.bhh[gi];
@@ -238,7 +238,7 @@ __device__ __forceinline__ void gx_prologue(const PersistArgs& a, char* lds, int
       for (int q = 0; q < QB; ++q) {
         const int ins = q * 8 + w;
         const int64_t k = k0 + kc_slot<BK>(ls, ins * RPI + lr) * 8;
-        dma16(rw, k < K ? (uint32_t)((wrow[q] + k) * 2) : DMA_OFF_NONE, st + TA + ins * 1024);
+        dma16(rw, k < K && wrow[q] >= 0 ? (uint32_t)((wrow[q] + k) * 2) : DMA_OFF_NONE, st + TA + ins * 1024);
       }
     };
     f32x4 acc[FM][FN];
@@ -285,7 +285,7 @@ __device__ __forceinline__ void gx_prologue(const PersistArgs& a, char* lds, int
 #pragma unroll
           for (int jn = 0; jn < FN; ++jn) {
             const int n = 32 * w + jn * 16 + fr;
-            o[(n >> 6) * H + (n & 63)] = (bf16)(acc[i][jn][rr] + bv[jn]);
+            if (u0 + (n & 63) < H) o[(n >> 6) * H + (n & 63)] = (bf16)(acc[i][jn][rr] + bv[jn]);
           }
         }
       }
@@ -321,7 +321,8 @@ __global__ __launch_bounds__(NTH) void lstm_fwd_persist(const PersistArgs a) {
   const int u0 = mem * PU;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int ub = w & 3, kh = w >> 2;
-  const int KH = H / 64;   // 32-deep k-steps per k half
+  const int NM = (H + PU - 1) / PU, HP = NM * PU;   // members; units with the last member's padding
+  const int KH = NM;                                // 32-deep k-steps per k half
   const bool owner = BOTH || kh == 0;
   if (tid == 0) place_announce(a.place, a.seq + 1);
 
@@ -345,11 +346,12 @@ __global__ __launch_bounds__(NTH) void lstm_fwd_persist(const PersistArgs a) {
         const int ins = q * 8 + w;                  // one instruction fills rows 2 ins, 2 ins + 1
         const int lr = ins * 2 + (lane >> 5);
         const int c = (lane & 31) ^ (lr & 15);      // chunk held by this lane's slot
-        const int64_t grow = (int64_t)(lr >> 6) * H + u0 + ((lr >> 4) & 3) * 16 + (lr & 15);
-        const bool ok = c * 8 < H / 2;
-        dma16(rw, ok ? (uint32_t)((grow * H + p * (H / 2) + c * 8) * 2) : DMA_OFF_NONE, stg + ins * 1024);
+        const int un = u0 + ((lr >> 4) & 3) * 16 + (lr & 15), k = p * (HP / 2) + c * 8;
+        const int64_t grow = (int64_t)(lr >> 6) * H + un;
+        const bool ok = c * 8 < HP / 2 && k < H && un < H;
+        dma16(rw, ok ? (uint32_t)((grow * H + k) * 2) : DMA_OFF_NONE, stg + ins * 1024);
       }
-      if (p == 0) local = place_local(a.place, a.seq + 1, g, NG, H / PU, a.status);
+      if (p == 0) local = place_local(a.place, a.seq + 1, g, NG, NM, a.status);
       dma_wait_all();
       __syncthreads();
       if (kh == p) {
@@ -366,14 +368,14 @@ __global__ __launch_bounds__(NTH) void lstm_fwd_persist(const PersistArgs a) {
     }
   }
 
-  // LDS during the steps: gathered h [H/8][R + 1][8] (MFMA A layout; rows
-  // RV..15 stay zero), the k-half partial sums, and step buffers (by step
+  // LDS during the steps: gathered h [HP/8][R + 1][8] (MFMA A layout; rows
+  // RV..15 and units past H stay zero), the k-half partial sums, and step buffers (by step
   // parity) of c [RV][64] (float), h [RV][64] and gate pre-activations
   // [RV][64][4] (bf16), staged for 16-byte stores
   const int rend = a.b0 + a.rows;
   const int rowbase = a.b0 + s * RV;
   bf16* hl = (bf16*)lds_raw;
-  f32x4* red = (f32x4*)(lds_raw + (size_t)(H / 8) * (R + 1) * 16);   // [receiving half][4 unit blocks][4 gates][64]
+  f32x4* red = (f32x4*)(lds_raw + (size_t)(HP / 8) * (R + 1) * 16);   // [receiving half][4 unit blocks][4 gates][64]
   char* stage0 = (char*)(red + (BOTH ? 2 : 1) * 4 * 4 * 64);
   constexpr int STEP_STAGE = RV * PU * (4 + 2 + 8);
   auto stC = [&](int par) { return (float*)(stage0 + par * STEP_STAGE); };
@@ -389,26 +391,25 @@ __global__ __launch_bounds__(NTH) void lstm_fwd_persist(const PersistArgs a) {
     for (int pc = tid - first; pc < RV * 56; pc += nt) {
       if (pc < RV * 32) {
         const int rl = pc >> 5, c = pc & 31;
-        if (rowbase + rl < rend)
+        if (rowbase + rl < rend && u0 + c * 2 < H)
           *(uint4*)(a.G + ((int64_t)tt * B + rowbase + rl) * 8 * H + (int64_t)d * 4 * H + (int64_t)u0 * 4 + c * 8) =
               *(const uint4*)&sG[rl * PU * 4 + c * 8];
       } else if (pc < RV * 48) {
         const int rl = (pc - RV * 32) >> 4, c = (pc - RV * 32) & 15;
-        if (rowbase + rl < rend)
+        if (rowbase + rl < rend && u0 + c * 4 < H)
           *(float4*)(a.C + ((int64_t)tt * B + rowbase + rl) * 2 * H + (int64_t)d * H + u0 + c * 4) =
               *(const float4*)&sC[rl * PU + c * 4];
       } else {
         const int rl = (pc - RV * 48) >> 3, c = (pc - RV * 48) & 7;
-        if (rowbase + rl < rend)
+        if (rowbase + rl < rend && u0 + c * 8 < H)
           *(uint4*)(a.Y + ((int64_t)tt * B + rowbase + rl) * 2 * H + (int64_t)d * H + u0 + c * 8) =
               *(const uint4*)&sY[rl * PU + c * 8];
       }
     }
   };
-  if constexpr (RV < R) {
-    for (int i = tid; i < (H / 8) * (R - RV); i += NTH)
-      *(uint4*)&hl[((i / (R - RV)) * (R + 1) + RV + i % (R - RV)) * 8] = make_uint4(0u, 0u, 0u, 0u);
-  }
+  if (RV < R || HP > H)
+    for (int i = tid; i < (HP / 8) * (R + 1); i += NTH) *(uint4*)&hl[i * 8] = make_uint4(0u, 0u, 0u, 0u);
+  __syncthreads();
 
   const int unit = u0 + ub * 16 + (lane & 15);
   const int wpr = H / 4;   // exchange words per row
@@ -429,7 +430,8 @@ __global__ __launch_bounds__(NTH) void lstm_fwd_persist(const PersistArgs a) {
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
       const int row = rowbase + lrow(r);
-      const bf16* p = a.Gx + ((int64_t)tt * B + (row < rend ? row : a.b0)) * 8 * H + (int64_t)d * 4 * H + unit;
+      const bf16* p =
+          a.Gx + ((int64_t)tt * B + (row < rend ? row : a.b0)) * 8 * H + (int64_t)d * 4 * H + min(unit, H - 1);
 #pragma unroll
       for (int q = 0; q < 4; ++q) gxn[r][q] = p[q * H];
     }
@@ -534,7 +536,7 @@ __global__ __launch_bounds__(NTH) void lstm_fwd_persist(const PersistArgs a) {
         // lane 4i stores units 4i .. 4i+3 (the pairs of lanes 4i and 4i+2)
         const uint32_t p2 = pack_bf16x2(hv[r], h_next_unit);
         const uint32_t p4 = lane_xor2(p2);
-        if (row < rend && (lane & 3) == 0)
+        if (row < rend && unit < H && (lane & 3) == 0)
           ll_store64(xo + ((int64_t)d * a.rows + (row - a.b0)) * wpr + unit / 4,
                      ((((uint64_t)p4 << 32) | p2) & ~H4_TAG_BITS) | h4_tag(a.seq, tau + 1), local);
       }
@@ -592,7 +594,7 @@ __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
   constexpr int RPT = 4 / LPI;          // cell rows per lane
   constexpr int MPL = 8 / LPI;          // members' words per lane (at most)
   const int H = a.H, B = a.B, Tn = a.Tn;
-  const int NM = H / PU, NG = a.NG;
+  const int NM = (H + PU - 1) / PU, NG = a.NG;
   const int g = blockIdx.x % NG, mem = blockIdx.x / NG;
   if (g >= 2 * a.NS) return;   // padding (see persist_groups)
   const int d = g & 1, s = g >> 1;
@@ -626,8 +628,9 @@ __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
         const int kl = q * 8 + w;   // one 1 KB row per load instruction
         const int kk = p * 128 + kl;
         const int c = lane ^ wswz(kl);
-        const int64_t grow = (int64_t)((kk >> 4) & 3) * H + u0 + (kk >> 6) * 16 + (kk & 15);
-        dma16(rw, c * 8 < H ? (uint32_t)((grow * H + c * 8) * 2) : DMA_OFF_NONE, stg + kl * 1024);
+        const int un = u0 + (kk >> 6) * 16 + (kk & 15);
+        const int64_t grow = (int64_t)((kk >> 4) & 3) * H + un;
+        dma16(rw, c * 8 < H && un < H ? (uint32_t)((grow * H + c * 8) * 2) : DMA_OFF_NONE, stg + kl * 1024);
       }
       if (p == 0) local = place_local(a.place, a.seq + 1, g, NG, NM, a.status);
       dma_wait_all();
@@ -688,7 +691,7 @@ __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
   for (int i = 0; i < RPT; ++i) {
     int row = rowbase + rl0 + i;
     row = row < rend ? row : a.b0;
-    oc[i] = (uint32_t)(row * 2 * H + d * H + u0 + cu);
+    oc[i] = (uint32_t)(row * 2 * H + d * H + min(u0 + cu, H - 1));
   }
   const int64_t fc = (int64_t)B * 2 * H, fg = (int64_t)B * 8 * H;   // elements per frame
   if (a.ndy > 0) {
@@ -705,7 +708,7 @@ __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
         const int it = min(i0 + j * NTH + tid, nitems - 1);
         const int rs = it >> 4, t_ = rs / RV, r = rs % RV;
         const int row = rowbase + r < rend ? rowbase + r : a.b0;
-        const float* p = a.DYP + (int64_t)t_ * fc + (int64_t)row * 2 * H + d * H + u0 + (it & 15) * 4;
+        const float* p = a.DYP + (int64_t)t_ * fc + (int64_t)row * 2 * H + d * H + min(u0 + (it & 15) * 4, H - 4);
 #pragma unroll
         for (int k = 0; k < 3; ++k) v[j][k] = *(const float4*)(p + (int64_t)min(k, a.ndy - 1) * a.dy_kstride);
       }
@@ -721,7 +724,7 @@ __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
         for (int k = 3; k < a.ndy; ++k) {
           const int row = rowbase + r < rend ? rowbase + r : a.b0;
           const float4 w4 = *(const float4*)(a.DYP + (int64_t)k * a.dy_kstride + (int64_t)t_ * fc +
-                                             (int64_t)row * 2 * H + d * H + u0 + (it & 15) * 4);
+                                             (int64_t)row * 2 * H + d * H + min(u0 + (it & 15) * 4, H - 4));
           sum.x += w4.x; sum.y += w4.y; sum.z += w4.z; sum.w += w4.w;
         }
         if (!(rowbase + r < rend)) sum = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -790,7 +793,7 @@ __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
       const uint64_t* base = a.X + ((tau - 1) & 1) * slot_stride + ogath;
       const uint64_t want = h4_tag(a.seq, tau);
       f32x4 sum = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (rowbase + 4 * qd < rend) {
+      if (rowbase + 4 * qd < rend && u0 + cu < H) {
         uint64_t wv[MPL];
 #pragma unroll
         for (int k = 0; k < MPL; ++k) wv[k] = k < mcount ? ll_load(base + (int64_t)k * H) : want;
@@ -836,7 +839,7 @@ __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
       da[1] = dc * cp[i] * fg_ * (1.f - fg_);
       da[2] = dc * ig * (1.f - gg * gg);
       da[3] = dh * tc[i] * og_ * (1.f - og_);
-      const bool ok = rowbase + r < rend;
+      const bool ok = rowbase + r < rend && u0 + cu < H;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const bf16 v = ok ? (bf16)da[q] : (bf16)0.f;
@@ -892,7 +895,8 @@ __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
 #pragma unroll
       for (int c0 = 0; c0 < NDA; ++c0) {
         const int c = c0 * NDT + dtid, kg = c & 31, r = c >> 5;
-        if (rowbase + r < rend) *(uint4*)(dat + oda[c0]) = *(const uint4*)&al[(kg * (R + 1) + r) * 8];
+        if (rowbase + r < rend && u0 + (kg >> 3) * 16 + (kg & 1) * 8 < H)
+          *(uint4*)(dat + oda[c0]) = *(const uint4*)&al[(kg * (R + 1) + r) * 8];
       }
     }
   }
@@ -904,7 +908,7 @@ __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) red[((qd * LPI + sub) * PU + cu) * 4 + q] = dbacc[q];
     __syncthreads();
-    if (tid < 4 * PU && rowbase < rend) {
+    if (tid < 4 * PU && rowbase < rend && u0 + (tid >> 2) < H) {
       float sum = 0.f;
 #pragma unroll
       for (int r = 0; r < RV / RPT; ++r) sum += red[r * PU * 4 + tid];
@@ -945,10 +949,12 @@ __global__ void status_reset_kernel(int* status) {
 // ---------------------------------------------------------------------------
 // Host side.
 // ---------------------------------------------------------------------------
+static int members(int H) { return (int)cdiv(H, PU); }
+
 size_t persist_lds_bytes(int H, bool backward, int RV) {
   const int R = RV > 16 ? 32 : 16;
   const size_t run = backward ? (size_t)bwd_dy_lds(RV)
-                              : (size_t)(H / 8) * (R + 1) * 16 + (size_t)(RV > 16 ? 2 : 1) * 4 * 4 * 64 * 16 +
+                              : (size_t)(rup(H, PU) / 8) * (R + 1) * 16 + (size_t)(RV > 16 ? 2 : 1) * 4 * 4 * 64 * 16 +
                                     (size_t)2 * RV * PU * (4 + 2 + 8);
   return std::max(std::max(run, (size_t)STAGE_BYTES), backward ? (size_t)0 : gx_lds_bytes);
 }
@@ -965,7 +971,7 @@ int persist_max_wg() {
 
 bool persist_supported(int H, int T) {
   (void)T;   // any length: the tag holds only bit 1 of the step number
-  return H % PU == 0 && H >= PU && H <= 512;
+  return H % 32 == 0 && H >= 32 && H <= 512;
 }
 
 // Launch mode.  Every workgroup of a launch waits for the others, so all
@@ -1037,7 +1043,7 @@ static hipError_t launch_one(PersistArgs a, hipStream_t s) {
   const void* fn;
   if constexpr (BWD) fn = (const void*)lstm_bwd_persist<RV>;
   else fn = (const void*)lstm_fwd_persist<RV>;
-  return persist_launch(BWD ? "lstm_rec_bwd_persist" : "lstm_rec_fwd_persist", fn, dim3(a.NG * (a.H / PU)), NTH,
+  return persist_launch(BWD ? "lstm_rec_bwd_persist" : "lstm_rec_fwd_persist", fn, dim3(a.NG * members(a.H)), NTH,
                         persist_lds_bytes(a.H, BWD, RV), &a, s);
 }
 
@@ -1046,8 +1052,7 @@ static hipError_t launch_one(PersistArgs a, hipStream_t s) {
 // the chip that way (one workgroup per CU), else 16; more rows by chunking.
 // False if no launch fits.
 static bool persist_plan(int H, int B, int* RVo, int* chunko) {
-  const int NM = H / PU;
-  if (NM < 1) return false;
+  const int NM = members(H);
   const int max_ns = std::min(persist_max_wg() / (2 * NM), PERSIST_MAX_SLICES);
   if (max_ns < 1) return false;
   int RV = (B + 7) / 8 <= max_ns ? 8 : (B + 15) / 16 <= max_ns ? 16 : 32;
@@ -1067,7 +1072,7 @@ int persist_rows_per_workgroup(int H, int B) {
 
 int persist_workgroups(int H, int B) {
   int RV, chunk;
-  return persist_plan(H, B, &RV, &chunk) ? 2 * (int)cdiv(chunk, RV) * (H / PU) : 0;
+  return persist_plan(H, B, &RV, &chunk) ? 2 * (int)cdiv(chunk, RV) * members(H) : 0;
 }
 
 bool persist_bwd_dy_partials_ok(int H, int B, int T) {
@@ -1083,7 +1088,7 @@ hipError_t persist_clear(bool backward, const PersistArgs& a, hipStream_t s) {
   if (!persist_plan(a.H, a.B, &RV, &chunk)) return hipErrorInvalidValue;
   // both exchange slots start without any valid tag; the forward's clear
   // also initialises the status block of a fresh workspace
-  const int64_t words = PERSIST_PLACE_WORDS + (backward ? (int64_t)2 * 2 * ((chunk + 3) / 4) * (a.H / PU) * a.H
+  const int64_t words = PERSIST_PLACE_WORDS + (backward ? (int64_t)2 * 2 * ((chunk + 3) / 4) * members(a.H) * a.H
                                  : (int64_t)2 * 2 * chunk * (a.H / 4));
   return persist_clear_words(a.place, words / 2, backward ? nullptr : a.status, s);
 }
@@ -1109,7 +1114,7 @@ hipError_t persist_layer(bool backward, PersistArgs a, hipStream_t s) {
     c.b0 = b0;
     c.rows = std::min(chunk, a.B - b0);
     c.NS = (c.rows + RV - 1) / RV;
-    c.NG = persist_groups(2 * c.NS, a.H / PU);
+    c.NG = persist_groups(2 * c.NS, members(a.H));
     // the launch's position in the call (the caller's tag numbers the layers
     // in the order the call runs them)
     c.seq = a.tag * (uint32_t)cdiv(a.B, chunk) + (uint32_t)(b0 / chunk);

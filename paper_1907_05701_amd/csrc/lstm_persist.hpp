@@ -107,12 +107,12 @@ struct PersistArgs {
 // launch covers at most PERSIST_MAX_ROWS rows.
 #define PERSIST_MAX_SLICES 32
 #define PERSIST_MAX_ROWS (PERSIST_MAX_SLICES * 32)
-// Exchange buffer: the placement words, then 2 slots x 2 directions x row quads x (H/64 members) x H
+// Exchange buffer: the placement words, then 2 slots x 2 directions x row quads x (H/64 members, rounded up) x H
 // units words of 8 bytes (the backward's partial sums, four rows per word;
 // the forward uses H/4 words per row, never more).
 static inline size_t persist_xch_bytes(int B, int H) {
   const size_t rows = B < PERSIST_MAX_ROWS ? B : PERSIST_MAX_ROWS;
-  const size_t members = H / 64 > 0 ? H / 64 : 1;
+  const size_t members = (H + 63) / 64;
   const size_t bwd = (size_t)2 * 2 * ((rows + 3) / 4) * members * H * 8;
   const size_t fwd = (size_t)2 * 2 * rows * (H / 4 > 0 ? H / 4 : 1) * 8;
   return (bwd > fwd ? bwd : fwd) + PERSIST_PLACE_WORDS * 8;
@@ -121,8 +121,9 @@ static inline size_t persist_xch_bytes(int B, int H) {
 // Whether the backward can take dy as split-K partials (its summed dy of all
 // steps must fit the LDS beside the step buffers).
 bool persist_bwd_dy_partials_ok(int H, int B, int T);
-// True if the persistent kernels handle this H (a multiple of 64, at most
-// 512: a member's 256 W_hh rows fit in its registers); any T.
+// True if the persistent kernels handle this H (a multiple of 32, at most
+// 512: a member's 256 W_hh rows fit in its registers; the last member may own
+// 32 units); any T.
 bool persist_supported(int H, int T);
 // Workgroups of a layer's largest launch for this H and B.
 int persist_workgroups(int H, int B);
