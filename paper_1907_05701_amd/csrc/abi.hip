@@ -44,7 +44,11 @@ int plan_splits(int64_t Mo, int64_t No, int64_t Kr, int BMt, int BNt, int BK, in
   if (!lp) {
     int best = 1;
     double lim = 0;
-    for (int s = 1; s <= 16 && (s == 1 || kt / s >= 4); ++s) {
+    // the head's products (alone) split no further than 512 workgroups ask
+    // for, and not at all from 256: the static entry point takes dims by the
+    // size of the head workspace, which the partials are part of
+    const int64_t most = !alone ? 16 : tiles >= 256 ? 1 : cdiv(512, tiles);
+    for (int s = 1; s <= 16 && s <= most && (s == 1 || kt / s >= 4); ++s) {
       const double t = (double)cdiv(tiles * s, 256) * (double)cdiv(kt, s) * 0.25 +
                        kc_us_partials((double)batches * (double)Mo * (double)No, s);
       if (s == 1 || t < 0.95 * lim) { best = s; lim = t; }
@@ -102,6 +106,25 @@ static void plan_dw(const blstm_dims* d, Layout& L) {
       }
     }
   }
+}
+
+// The float32 form: one split for all of them, of least estimated time (as
+// plan_splits; one launch of all products, so their blocks count together).
+static void plan_dw32(const blstm_dims* d, Layout& L) {
+  const int64_t H = d->H, kt = cdiv(L.M, 16);
+  int64_t tiles = 0;
+  double elems = 0, lim = 0;
+  for (int l = 0; l < d->L; ++l)
+    for (int64_t N : {(int64_t)L.layer_in(l), H}) {
+      tiles += 2 * cdiv(4 * H, 64) * cdiv(N, 64);
+      elems += 2.0 * 4 * H * N;
+    }
+  int best = 1;
+  for (int s = 1; s <= 16 && (s == 1 || kt / s >= 4); ++s) {
+    const double t = (double)cdiv(tiles * s, 256) * (double)cdiv(kt, s) * 0.25 + kc_us_partials(elems, s);
+    if (s == 1 || t < 0.95 * lim) { best = s; lim = t; }
+  }
+  for (int i = 0; i < 2 * d->L; ++i) L.sp_dw[i] = best;
 }
 
 static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -163,9 +186,9 @@ int make_layout(const blstm_dims* d, Layout* lo) {
   L.WT = a; a = align256(a + (size_t)2 * d->L * 4 * H * H * es);
   L.WP0_bytes = es == 2 && d->D % 8 != 0 ? (size_t)2 * 4 * H * L.Dp0 * es : 0;
   L.WP0 = a; a = align256(a + L.WP0_bytes);
-  // bf16: da [M][8H], one per layer (the weight gradients of every layer run
-  // after the last BPTT); float32 uses the G_x scratch
-  L.da_bytes = es == 2 ? align256((size_t)M * 8 * H * es) : 0;
+  // da [M][8H], one per layer (the weight gradients of every layer run after
+  // the last BPTT)
+  L.da_bytes = align256((size_t)M * 8 * H * es);
   L.DA = a; a += (size_t)d->L * L.da_bytes;
   // per-step 16-row partials (per-step BPTT) or per-workgroup partials over
   // all steps (persistent BPTT)
@@ -173,49 +196,34 @@ int make_layout(const blstm_dims* d, Layout* lo) {
   L.dbp_bytes = align256((size_t)std::max<int64_t>((int64_t)d->T * cdiv(d->B, 16), cdiv(d->B, es == 2 ? 8 : 4)) * 8 * H * 4);
   L.DBP = a; a += (size_t)std::max(2, d->L) * L.dbp_bytes;   // per layer when the bias sums wait for the last BPTT
   L.CSP = a; a = align256(a + (size_t)COLSUM_MAX_CHUNKS * 8 * H * 4);
-  // split-K plans and partial buffers of the backward GEMMs
+  // split-K plans and partial buffers of the backward GEMMs: a layer's dX, and
+  // after the last dX the deferred weight gradients (disjoint regions within
+  // their one launch)
   const int BMt = es == 2 ? GemmCfg<bf16>::BM : GemmCfg<float>::BM;
   const int BNt = es == 2 ? GemmCfg<bf16>::BN : GemmCfg<float>::BN;
   const int BKt = es == 2 ? GemmCfg<bf16>::BK : GemmCfg<float>::BK;
-  // each layer's three products own disjoint partial regions (dW_ih, dW_hh,
-  // dX), so that they can run as one grouped launch.  bf16, measured on
-  // MI355X at the learner-step shapes: dX splits to fill one round of two
-  // blocks per CU by itself and dW_hh is not split (its partial pass costs
-  // more than the parallelism gains: 1.207 -> 1.253 M frames/s); dW_ih keeps
-  // half a round.  A sweep of the other products' splits and of the tile
-  // order's row grouping found the defaults at the optimum.
   size_t skp = 0;
   const bool lp = es == 2;
   for (int l = 0; l < d->L; ++l) {
     const int64_t Dl = l == 0 ? d->D : 2 * H;
-    const bool with_dx = l > 0;
-    L.sp_dWih[l] = plan_splits(4 * H, Dl, M, BMt, BNt, BKt, 2, lp, false);
-    const size_t ih_bytes = L.sp_dWih[l] > 1 ? align256((size_t)L.sp_dWih[l] * 2 * 4 * H * Dl * 4) : 0;
-    L.sp_dWhh[l] = lp ? 1 : plan_splits(4 * H, H, (int64_t)(d->T - 1) * d->B, BMt, BNt, BKt, 2, lp, false);
-    const size_t hh_bytes = L.sp_dWhh[l] > 1 ? align256((size_t)L.sp_dWhh[l] * 2 * 4 * H * H * 4) : 0;
-    L.sp_dX[l] = with_dx ? plan_splits(M, Dl, 8 * H, BMt, BNt, BKt, 1, lp, lp) : 1;
-    if (lp && with_dx) {
+    L.sp_dX[l] = l > 0 ? plan_splits(M, Dl, 8 * H, BMt, BNt, BKt, 1, lp, lp) : 1;
+    if (lp && l > 0) {
       const KcPlan p = kc_plan(M, Dl, 8 * H, 1, L.sp_dX[l]);
       L.big_dX[l] = p.big;
       L.sp_dX[l] = p.splits;
     }
-    const size_t dx_bytes = L.sp_dX[l] > 1 ? align256((size_t)L.sp_dX[l] * M * Dl * 4) : 0;
-    L.skp_hh[l] = ih_bytes;
-    L.skp_dx[l] = ih_bytes + hh_bytes;
-    skp = std::max(skp, ih_bytes + hh_bytes + dx_bytes);
+    if (L.sp_dX[l] > 1) skp = std::max(skp, (size_t)L.sp_dX[l] * M * Dl * 4);
   }
-  if (lp) {
-    plan_dw(d, L);
-    size_t dw = 0;   // the deferred launch's partials (after the last dX)
-    for (int i = 0; i < 2 * d->L; ++i) {
-      const int64_t Nw = (i & 1) ? H : L.layer_in(d->L - 1 - i / 2);
-      L.skp_dw[i] = dw;
-      if (L.sp_dw[i] > 1) dw += align256((size_t)L.sp_dw[i] * 2 * 4 * H * Nw * 4);
-    }
-    skp = std::max(skp, dw);
+  if (lp) plan_dw(d, L);
+  else plan_dw32(d, L);
+  size_t dw = 0;
+  for (int i = 0; i < 2 * d->L; ++i) {
+    const int64_t Nw = (i & 1) ? H : L.layer_in(d->L - 1 - i / 2);
+    L.skp_dw[i] = dw;
+    if (L.sp_dw[i] > 1) dw += align256((size_t)L.sp_dw[i] * 2 * 4 * H * Nw * 4);
   }
+  skp = std::max(skp, dw);
   L.SKP = a; a = align256(a + skp);
-  L.SKP2 = a; a = align256(a + skp);   // split-K partials of the side-stream products
   L.XCH = a; a = align256(a + (es == 2 ? persist_xch_bytes(d->B, d->H) : persist32_xch_bytes(d->B, d->H)));   // recurrent step exchange
   // recurrence status block, the last PERSIST_STATUS_BYTES of act_ws
   L.SYNC = a; a += PERSIST_STATUS_BYTES;
@@ -237,8 +245,8 @@ int make_layout(const blstm_dims* d, Layout* lo) {
   L.RL = h; h = align256(h + (size_t)M * 4);
   L.DZ = h; h = align256(h + (size_t)M * P * 4);
   L.DZT = h; h = align256(h + (size_t)M * P * es);
-  // column-sum partials: db_l (P columns), and db_s on the float32 path
-  L.HCSP = h; h = align256(h + (size_t)COLSUM_MAX_CHUNKS * (es == 2 ? P : std::max<int64_t>(L.Kp, P)) * 4);
+  // float32: column-sum partials of db_s (those of db_l in HSKP)
+  L.HCSP = h; h = align256(h + (es == 2 ? 0 : (size_t)COLSUM_MAX_CHUNKS * std::max<int64_t>(L.Kp, P) * 4));
   size_t hsk = 0;
   L.sp_z = es == 2 ? plan_splits(M, P, 2 * H, BMt, BNt, BKt, 1, true, true) : 1;
   if (L.sp_z > 1) hsk = std::max(hsk, (size_t)L.sp_z * M * P * 4);

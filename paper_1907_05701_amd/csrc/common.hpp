@@ -79,19 +79,19 @@ struct Layout {
   int64_t Wih[MAX_LAYERS][2], Whh[MAX_LAYERS][2], bih[MAX_LAYERS][2], bhh[MAX_LAYERS][2];
   int64_t Wl, bl, Ws, bs;
   // act_ws byte offsets
-  size_t X0, Y[MAX_LAYERS], G[MAX_LAYERS], C[MAX_LAYERS], GX, DYa, DYb, DC, WT, DA, DBP, CSP, SKP, SKP2, SYNC, XCH;
+  size_t X0, Y[MAX_LAYERS], G[MAX_LAYERS], C[MAX_LAYERS], GX, DYa, DYb, DC, WT, DA, DBP, CSP, SKP, SYNC, XCH;
   size_t WP0, WP0_bytes;   // bf16 with D % 8 != 0: layer-0 W_ih padded to Dp0 columns (else 0 bytes)
-  size_t da_bytes, dbp_bytes;   // one layer's da (bf16) / bias partials
+  size_t da_bytes, dbp_bytes;   // one layer's da / bias partials
   size_t act_bytes;
   // head_ws byte offsets
   size_t Z, S, LST, LSE, LDB, RL, DZ, DZT, HCSP, HSKP, DBLP;
   size_t head_bytes;
   size_t ytop_bytes;
   // split-K factors of the weight/input-gradient GEMMs (1 = direct store)
-  int sp_dWih[MAX_LAYERS], sp_dWhh[MAX_LAYERS], sp_dX[MAX_LAYERS], sp_z, sp_dz, sp_dWs, sp_dWl, sp_dy;
-  size_t skp_hh[MAX_LAYERS], skp_dx[MAX_LAYERS];   // byte offsets of the dW_hh / dX partials in SKP
-  // bf16: products in 256x256 blocks, and of the deferred weight gradients
-  // (dW_ih, dW_hh of each layer) the splits and byte offsets of the partials in SKP
+  int sp_dX[MAX_LAYERS], sp_z, sp_dz, sp_dWs, sp_dWl, sp_dy;
+  // the deferred weight gradients (dW_ih, dW_hh of each layer, top layer
+  // first): splits and byte offsets of their partials in SKP; bf16: products
+  // in 256x256 blocks
   bool big_dX[MAX_LAYERS], big_dw, big_dz, big_dWs;
   int sp_dw[2 * MAX_LAYERS];
   size_t skp_dw[2 * MAX_LAYERS];

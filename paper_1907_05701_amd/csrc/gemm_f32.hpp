@@ -37,6 +37,7 @@ struct F32Args {
 #define F32_BT 64
 #define F32_BK 32
 #define F32_ST 3
+#define F32_RUN 8
 static constexpr size_t f32_lds_bytes = (size_t)F32_ST * 2 * F32_BT * F32_BK * 4;
 
 template <bool KC>
@@ -77,16 +78,19 @@ struct F32Operand {
   }
 };
 
+// One output block of one product; w is the workgroup's index within the
+// product's workgroups (those at or past p.total have no block).
 template <bool AKC, bool BKC, class Epi>
-__global__ __launch_bounds__(256, 3) void gemm_f32_kernel(const F32Args p, const Epi epi) {
+__device__ __forceinline__ void gemm_f32_tile(const F32Args& p, const Epi& epi, int w) {
   typedef F32Operand<AKC> OA;
   typedef F32Operand<BKC> OB;
   constexpr int TA = F32_BT * F32_BK * 4, STAGE = 2 * TA;
   extern __shared__ __attribute__((aligned(1024))) char f32_lds[];
+  if (w >= p.total) return;
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   const int wm = wid & 1, wn = wid >> 1;
   int zs, tm, tn;
-  kc_tile_of(p, blockIdx.x, 4, zs, tm, tn);
+  kc_tile_of(p, w, 4, zs, tm, tn);
   const int z = zs / p.splits, sp = zs % p.splits;
   const int64_t m0 = (int64_t)tm * F32_BT, n0 = (int64_t)tn * F32_BT;
   const int64_t kbeg = (int64_t)sp * p.ksplit, kend = min(p.K, kbeg + p.ksplit);
@@ -99,16 +103,27 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_kernel(const F32Args p, const
     OA::issue(ab, p.lda, 0, 0, m0, p.arows - m0, k0, kend, st, wid, lane);
     OB::issue(bb, p.ldb, p.bseg, p.bsegs, n0, p.brows - n0, k0, kend, st + TA, wid, lane);
   };
-  // two sums per output, of the even and the odd 16-deep steps: half as long
-  // a chain of roundings (the split-K partials of small products used to
-  // shorten it)
-  f32x4 acc[2][2][2];
-#pragma unroll
-  for (int h = 0; h < 2; ++h)
+  // two sums per output, of the even and the odd 16-deep steps, moved into a
+  // total every F32_RUN k-tiles: chains of roundings of at most K / 256 + 32
+  // steps instead of K / 4 (the split-K partials used to shorten them)
+  f32x4 acc[2][2][2], total[2][2];
+  auto clear = [&](f32x4 (&v)[2][2]) {
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) acc[h][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int j = 0; j < 2; ++j) v[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  auto flush = [&]() {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) total[i][j] += acc[0][i][j] + acc[1][i][j];
+    clear(acc[0]);
+    clear(acc[1]);
+  };
+  clear(total);
+  clear(acc[0]);
+  clear(acc[1]);
 #pragma unroll
   for (int j = 0; j < F32_ST - 1; ++j)
     if (j < ntiles) issue(j);
@@ -134,29 +149,63 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_kernel(const F32Args p, const
 #pragma unroll
           for (int j = 0; j < 2; ++j) acc[ks & 1][i][j] = Mfma<float>::mma(a[i][s], b[j][s], acc[ks & 1][i][j]);
     }
+    if (it % F32_RUN == F32_RUN - 1) flush();
   }
+  flush();
+  epi.template apply<2, 2>(z, sp, m0 + wm * 32, n0 + wn * 32, total, lane);
+}
+
+template <bool AKC, bool BKC, class Epi>
+__global__ __launch_bounds__(256, 3) void gemm_f32_kernel(const F32Args p, const Epi epi) {
+  gemm_f32_tile<AKC, BKC, Epi>(p, epi, blockIdx.x);
+}
+
+// Several products of one layout in one launch (product i owns workgroups
+// [start[i], start[i + 1]), starts multiples of 8), and two of different
+// layouts (the first owns [0, n1)): one launch and one partial round of the
+// chip instead of several.
+#define F32_MAX_GROUP 12
+template <class Epi>
+struct F32Group {
+  F32Args p[F32_MAX_GROUP];
+  Epi e[F32_MAX_GROUP];
+  int start[F32_MAX_GROUP + 1];
+  int n;
+};
+template <bool AKC, bool BKC, class Epi>
+__global__ __launch_bounds__(256, 3) void gemm_f32_group_kernel(const F32Group<Epi> g) {
+  int i = 0;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[0][i][j] += acc[1][i][j];
-  epi.template apply<2, 2>(z, sp, m0 + wm * 32, n0 + wn * 32, acc[0], lane);
+  for (int k = 1; k < F32_MAX_GROUP; ++k) i += (k < g.n && (int)blockIdx.x >= g.start[k]);
+  gemm_f32_tile<AKC, BKC, Epi>(g.p[i], g.e[i], (int)blockIdx.x - g.start[i]);
+}
+template <bool AKC1, bool BKC1, bool AKC2, bool BKC2, class Epi>
+__global__ __launch_bounds__(256, 3) void gemm_f32_pair_kernel(const F32Args p1, const Epi e1, const F32Args p2,
+                                                               const Epi e2, int n1) {
+  if ((int)blockIdx.x < n1)
+    gemm_f32_tile<AKC1, BKC1, Epi>(p1, e1, (int)blockIdx.x);
+  else
+    gemm_f32_tile<AKC2, BKC2, Epi>(p2, e2, (int)blockIdx.x - n1);
 }
 
 // Whether an operand can be staged: 16-byte aligned rows, batches and
-// segments, the whole k range inside it (K-contiguous: in whole chunks).
+// segments, the whole k range inside it (K-contiguous: to the end of its last
+// chunk, with finite values there that meet the MN-contiguous other operand's
+// zeros).
 static inline bool f32_operand_ok(const Opnd& o, int64_t K, bool kc, bool seg_ok) {
   if (o.ilH != 0 || o.ld % 4 != 0 || o.zstride % 4 != 0 || ((uintptr_t)o.base & 15) != 0) return false;
-  if (kc) return o.seg == 0 && K % 4 == 0 && o.ext >= K && 64 * o.ld * 4 < 0x7ffffff0;
+  if (kc) return o.seg == 0 && o.ext >= rup(K, 4) && 64 * o.ld * 4 < 0x7ffffff0;
   if (o.seg != 0 && !(seg_ok && o.seg % F32_BK == 0 && K <= 2 * o.seg && o.segstride % 4 == 0)) return false;
   return o.rows >= K && o.ext % 4 == 0 && F32_BK * o.ld * 4 < 0x7ffffff0;
 }
 
-// False (and nothing launched) if an operand cannot be staged.
-template <bool AKC, bool BKC, class Epi>
-static inline bool gemm_f32_dma(const char* name, hipStream_t s, const Opnd& A, const Opnd& B, int64_t M, int64_t N,
-                                int64_t K, int batches, int splits, const Epi& epi) {
+// False if an operand cannot be staged.
+template <bool AKC, bool BKC>
+static inline bool f32_args(const Opnd& A, const Opnd& B, int64_t M, int64_t N, int64_t K, int batches, int splits,
+                            F32Args* q) {
+  if (AKC && BKC && K % 4 != 0) return false;
   if (!f32_operand_ok(A, K, AKC, false) || !f32_operand_ok(B, K, BKC, true)) return false;
-  F32Args p;
+  F32Args& p = *q;
   p.A = (const float*)A.base; p.lda = A.ld; p.azs = A.zstride; p.arows = AKC ? std::min<int64_t>(A.rows, M) : A.ext;
   p.B = (const float*)B.base; p.ldb = B.ld; p.bzs = B.zstride; p.brows = BKC ? std::min<int64_t>(B.rows, N) : B.ext;
   p.bseg = BKC ? 0 : B.seg; p.bsegs = B.segstride;
@@ -166,8 +215,16 @@ static inline bool gemm_f32_dma(const char* name, hipStream_t s, const Opnd& A, 
   p.ntm = (int)cdiv(M, F32_BT);
   p.ntn = (int)cdiv(N, F32_BT);
   const int64_t total = (int64_t)batches * splits * p.ntm * p.ntn;
-  if (total > 0x7fffffff) return false;
   p.total = (int)total;
+  return total <= (1 << 30);
+}
+
+// One product; false (and nothing launched) if an operand cannot be staged.
+template <bool AKC, bool BKC, class Epi>
+static inline bool gemm_f32_dma(const char* name, hipStream_t s, const Opnd& A, const Opnd& B, int64_t M, int64_t N,
+                                int64_t K, int batches, int splits, const Epi& epi) {
+  F32Args p;
+  if (!f32_args<AKC, BKC>(A, B, M, N, K, batches, splits, &p)) return false;
   auto fn = gemm_f32_kernel<AKC, BKC, Epi>;
   BLSTM_LAUNCH(name, fn, dim3((unsigned)p.total), dim3(256), f32_lds_bytes, s, p, epi);
   return true;

@@ -314,11 +314,14 @@ __global__ __launch_bounds__(WM * WN * 64, (KcOcc<BM, BN, WM, WN, STAGES, BK>::v
 // interleave, 16-byte aligned rows and batch strides, the whole k range inside
 // the operand; MN-contiguous operands also need an MN extent that is a
 // multiple of 8 (whole 16-byte chunks), and may come in two k segments, the
-// first of a multiple of 64 rows (whole k-tiles); K-contiguous ones need a k
-// range of whole chunks and may not be segmented.
+// first of a multiple of 64 rows (whole k-tiles); K-contiguous ones may not be
+// segmented, and where the k range ends inside a chunk (an odd number of
+// classes) the row must go on to the chunk's end: those values meet the other
+// operand's zeros past the range, so that one must be MN-contiguous, and they
+// must be finite (ds holds zeros there).
 static inline bool kc_operand_ok(const Opnd& o, int64_t K, bool kc) {
   const bool plain = o.ilH == 0 && o.ld % 8 == 0 && o.zstride % 8 == 0 && ((uintptr_t)o.base & 15) == 0;
-  if (kc) return plain && K % 8 == 0 && o.seg == 0 && o.ext >= K;
+  if (kc) return plain && o.seg == 0 && o.ext >= rup(K, 8);
   const bool segok = o.seg == 0 || (o.seg % 64 == 0 && K <= 2 * o.seg && o.segstride % 8 == 0);
   return plain && o.rows >= K && o.ext % 8 == 0 && segok;
 }
@@ -442,7 +445,7 @@ static inline bool kc_tall(int64_t M, int64_t N, int batches, int splits) {
 static inline bool kc_low(int64_t blocks) { return blocks <= 256; }
 // Whether a product can take the direct-to-LDS kernel.
 static inline bool kc_eligible(const Opnd& A, const Opnd& B, int64_t K, bool akc, bool bkc) {
-  return kc_operand_ok(A, K, akc) && kc_operand_ok(B, K, bkc);
+  return !(akc && bkc && K % 8 != 0) && kc_operand_ok(A, K, akc) && kc_operand_ok(B, K, bkc);
 }
 
 // GEMM dispatch: bf16 operands with 16-byte aligned rows go to the
@@ -555,4 +558,39 @@ static inline bool gemm_kc_group_launch(const char* name, hipStream_t s, int n, 
   if (kc_low(blocks)) return gemm_kc_group_launch_cfg<KcTileLow, AKC, BKC>(name, s, n, it, epi);
   if (tall && blocks > kc_round_blocks) return gemm_kc_group_launch_cfg<KcTileTall, AKC, BKC>(name, s, n, it, epi);
   return gemm_kc_group_launch_cfg<KcTile, AKC, BKC>(name, s, n, it, epi);
+}
+
+// The float32 forms of the two launches above.
+template <bool AKC, bool BKC, class Epi>
+static inline bool gemm_f32_group_launch(const char* name, hipStream_t s, int n, const KcItem* it, const Epi* epi) {
+  if (n < 1 || n > F32_MAX_GROUP) return false;
+  F32Group<Epi> g;
+  std::memset((void*)&g, 0, sizeof g);
+  g.n = n;
+  int64_t start = 0;
+  for (int i = 0; i < n; ++i) {
+    if (!f32_args<AKC, BKC>(it[i].A, it[i].B, it[i].M, it[i].N, it[i].K, it[i].batches, it[i].splits, &g.p[i]))
+      return false;
+    g.e[i] = epi[i];
+    g.start[i] = (int)start;
+    start += rup(g.p[i].total, 8);
+    if (start > (1 << 30)) return false;
+  }
+  g.start[n] = (int)start;
+  auto fn = gemm_f32_group_kernel<AKC, BKC, Epi>;
+  BLSTM_LAUNCH(name, fn, dim3((unsigned)start), dim3(256), f32_lds_bytes, s, g);
+  return true;
+}
+template <bool AKC1, bool BKC1, bool AKC2, bool BKC2, class Epi>
+static inline bool gemm_f32_pair_launch(const char* name, hipStream_t s, const Opnd& A1, const Opnd& B1, int64_t M1,
+                                        int64_t N1, int64_t K1, int splits1, const Epi& e1, const Opnd& A2,
+                                        const Opnd& B2, int64_t M2, int64_t N2, int64_t K2, int splits2,
+                                        const Epi& e2) {
+  F32Args p1, p2;
+  if (!f32_args<AKC1, BKC1>(A1, B1, M1, N1, K1, 1, splits1, &p1)) return false;
+  if (!f32_args<AKC2, BKC2>(A2, B2, M2, N2, K2, 1, splits2, &p2)) return false;
+  const int n1 = (int)rup(p1.total, 8);
+  auto fn = gemm_f32_pair_kernel<AKC1, BKC1, AKC2, BKC2, Epi>;
+  BLSTM_LAUNCH(name, fn, dim3((unsigned)(n1 + p2.total)), dim3(256), f32_lds_bytes, s, p1, e1, p2, e2, n1);
+  return true;
 }

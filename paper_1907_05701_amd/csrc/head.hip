@@ -990,7 +990,8 @@ static int head_impl(const Layout& lo, const float* theta, const T* W, const T* 
   float* part = (float*)(hws + lo.HSKP);
 
   // z = y W_l^T + b_l.  bf16: split over k (only P/128 column blocks), the
-  // fixed-order reduction adds b_l and writes the bf16 z
+  // fixed-order reduction adds b_l and writes the bf16 z (at 2688 frames the
+  // unsplit product in 64-row blocks saves the reduction but gains nothing)
   if (std::is_same<T, bf16>::value && lo.sp_z > 1) {
     gemm_launch<T, true, true, V, V>("gemm_z", s, opnd(ytop, H2, H2, M), opnd(W + lo.Wl, H2, H2, P), M, P, H2, 1,
                                      lo.sp_z, epi_store<float>(part, P, M, P, (int64_t)lo.sp_z * M * P, M * P));
@@ -1078,8 +1079,6 @@ static int head_impl(const Layout& lo, const float* theta, const T* W, const T* 
     BLSTM_LAUNCH("softmax_ce_rows", softmax_ce_rows_kernel<T>, dim3((unsigned)M), dim3(256), 0, s, S, K, Kp, labels,
                  scale, RL);
     BLSTM_LAUNCH("loss_sum", loss_sum_kernel, dim3(1), dim3(256), 0, s, RL, M, scale, loss);
-    // db_s = sum over frames of ds
-    colsum<T>("colsum_dbs", s, DS, M, K, Kp, csp, K, 0, grad + lo.bs, nullptr);
   }
   // dW_s = ds^T z, and dz = ds W_s (float32 and a low-precision copy for
   // the next products); W_s [K][P] is the MN-contiguous operand as it lies
@@ -1091,33 +1090,71 @@ static int head_impl(const Layout& lo, const float* theta, const T* W, const T* 
   const Opnd Az = opnd(DS, Kp, Kp, M), Bz2 = opnd(W + lo.Ws, P, P, K);
   bool paired = false;
   if constexpr (lp) {
-    if (lo.sp_dWs == 1 && lo.sp_dz > 1 && !lo.big_dWs && !lo.big_dz)
-      paired = gemm_kc_pair_launch<false, false, true, false>(
-          "gemm_dws_dz", s, As, Bs, K, P, M, 1, epi_store<float>(grad + lo.Ws, P, K, P, 0), Az, Bz2, M, P, K,
-          lo.sp_dz, epi_store<float>(part, P, M, P, (int64_t)lo.sp_dz * M * P, M * P));
+    if (lo.sp_dWs == 1 && lo.sp_dz > 1 && !lo.big_dWs && !lo.big_dz) {
+      // the product of longer blocks first: a few long ones behind many short
+      // ones would run alone at the end (336 frames: 39 -> 28.5 us)
+      const auto ew = epi_store<float>(grad + lo.Ws, P, K, P, 0);
+      const auto ez = epi_store<float>(part, P, M, P, (int64_t)lo.sp_dz * M * P, M * P);
+      if (cdiv(K, lo.sp_dz) > M)
+        paired = gemm_kc_pair_launch<true, false, false, false>("gemm_dws_dz", s, Az, Bz2, M, P, K, lo.sp_dz, ez, As, Bs,
+                                                                K, P, M, 1, ew);
+      else
+        paired = gemm_kc_pair_launch<false, false, true, false>("gemm_dws_dz", s, As, Bs, K, P, M, 1, ew, Az, Bz2, M, P,
+                                                                K, lo.sp_dz, ez);
+    }
     if (paired) splitk_reduce_launch<T>(s, part, lo.sp_dz, 1, M, P, DZ, P, 0, DZT, P);
+  } else {
+    // float32: one launch of both, an unsplit dz stored as it is
+    if (lo.sp_dWs == 1) {
+      const bool split = lo.sp_dz > 1;
+      paired = gemm_f32_pair_launch<true, false, false, false>(
+          "gemm_dz_dws", s, Az, Bz2, M, P, K, lo.sp_dz,
+          split ? epi_store<float>(part, P, M, P, (int64_t)lo.sp_dz * M * P, M * P) : epi_store<float>(DZ, P, M, P, 0),
+          As, Bs, K, P, M, 1, epi_store<float>(grad + lo.Ws, P, K, P, 0));
+      if (paired && split)
+        splitk_reduce_launch<T>(s, part, lo.sp_dz, 1, M, P, DZ, P, 0, (T*)nullptr, 0);
+    }
   }
   if (!paired) {
     gemm_f32<T, false, false, V, V>("gemm_dws", s, As, Bs, K, P, M, 1, lo.sp_dWs, grad + lo.Ws, P, 0, part,
                                         nullptr, 0, lo.big_dWs);
-    gemm_f32<T, true, false, V, V>("gemm_dz", s, Az, Bz2, M, P, K, 1, lo.sp_dz, DZ, P, 0, part, DZT, P, lo.big_dz);
+    gemm_f32<T, true, false, V, V>("gemm_dz", s, Az, Bz2, M, P, K, 1, lo.sp_dz, DZ, P, 0, part, lp ? DZT : nullptr, P,
+                                   lo.big_dz);
   }
-  // db_l = sum over frames of dz (bf16: already summed with db_s)
-  if constexpr (!lp) colsum<float>("colsum_dbl", s, DZ, M, P, P, csp, P, 0, grad + lo.bl, nullptr);
+  // db_s and db_l, the sums over frames of ds and dz (bf16: already done)
+  if constexpr (!lp) {
+    float* csl = part;   // at most M row ranges of P columns: within dz's partials, summed by now
+    if (K % 4 != 0 || !colsum2(s, DS, M, K, Kp, csp, grad + lo.bs, DZ, M, P, P, csl, grad + lo.bl)) {
+      colsum<T>("colsum_dbs", s, DS, M, K, Kp, csp, K, 0, grad + lo.bs, nullptr);
+      colsum<float>("colsum_dbl", s, DZ, M, P, P, csl, P, 0, grad + lo.bl, nullptr);
+    }
+  }
   // dW_l = dz^T y, and dy = dz W_l (W_l [P][2H] MN-contiguous as it lies);
   // bf16: one launch for both (dW_l through its split-K partials, dy stored
   // directly)
-  const Opnd Al = opnd(DZT, P, P, M), Bl = opnd(ytop, H2, H2, M);
-  const Opnd Ay = opnd(DZT, P, P, M), By = opnd(W + lo.Wl, H2, H2, P);
+  const T* dzl;   // dz in the operand type
+  if constexpr (lp) dzl = DZT;
+  else dzl = DZ;
+  const Opnd Al = opnd(dzl, P, P, M), Bl = opnd(ytop, H2, H2, M);
+  const Opnd Ay = opnd(dzl, P, P, M), By = opnd(W + lo.Wl, H2, H2, P);
   bool paired_l = false;
   if constexpr (lp) {
-    if (lo.sp_dWl > 1 && lo.sp_dy == 1)
+    if (lo.sp_dy == 1)
       paired_l = gemm_kc_pair_launch<false, false, true, false>(
           "gemm_dwl_dy", s, Al, Bl, P, H2, M, lo.sp_dWl,
-          epi_store<float>(part, H2, P, H2, (int64_t)lo.sp_dWl * P * H2, P * H2), Ay, By, M, H2, P, 1,
-          epi_store<float>(dytop, H2, M, H2, 0));
-    if (paired_l) splitk_reduce_launch<T>(s, part, lo.sp_dWl, 1, P, H2, grad + lo.Wl, H2, 0, (T*)nullptr, 0);
+          lo.sp_dWl > 1 ? epi_store<float>(part, H2, P, H2, (int64_t)lo.sp_dWl * P * H2, P * H2)
+                        : epi_store<float>(grad + lo.Wl, H2, P, H2, 0),
+          Ay, By, M, H2, P, 1, epi_store<float>(dytop, H2, M, H2, 0));
+  } else {
+    if (lo.sp_dy == 1)
+      paired_l = gemm_f32_pair_launch<false, false, true, false>(
+          "gemm_dwl_dy", s, Al, Bl, P, H2, M, lo.sp_dWl,
+          lo.sp_dWl > 1 ? epi_store<float>(part, H2, P, H2, (int64_t)lo.sp_dWl * P * H2, P * H2)
+                        : epi_store<float>(grad + lo.Wl, H2, P, H2, 0),
+          Ay, By, M, H2, P, 1, epi_store<float>(dytop, H2, M, H2, 0));
   }
+  if (paired_l && lo.sp_dWl > 1)
+    splitk_reduce_launch<T>(s, part, lo.sp_dWl, 1, P, H2, grad + lo.Wl, H2, 0, (T*)nullptr, 0);
   if (!paired_l) {
     gemm_f32<T, false, false, V, V>("gemm_dwl", s, Al, Bl, P, H2, M, 1, lo.sp_dWl, grad + lo.Wl, H2, 0, part);
     gemm_f32<T, true, false, V, V>("gemm_dy", s, Ay, By, M, H2, P, 1, lo.sp_dy, dytop, H2, 0, part);

@@ -649,20 +649,21 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
   if (lp && cap == hipStreamCaptureStatusNone && !use_persistent<T>(H, lo.T, true, s))
     side = side_stream();
   hipStream_t ss = side ? side->st : s;
-  float* part_side = side ? (float*)(ws + lo.SKP2) : part;
-  // bf16 without the side stream: each layer's weight-gradient products wait
+  // without the side stream each layer's weight-gradient products wait
   // for one grouped launch after the last BPTT (da is kept per layer), so a layer's own launch after its BPTT holds only dX, the
   // product the next BPTT needs; the deferred products all have about the
   // same k length and fill whole rounds of the chip together
-  const bool defer = lp && !side;
+  const bool defer = !side;
   F32Job deferred[2 * MAX_LAYERS];
   int nd = 0;
   // with the persistent BPTT, a layer's dX stays as its split-K partial
   // sums, which the next BPTT adds itself (in the reduction's order) before
   // its steps; the bias sums of every layer then wait for one reduction
   // launch after the last BPTT (on per-layer bias partials)
-  const bool dy_parts = defer && fuse_dy() && use_persistent<T>(H, lo.T, true, s) &&
+  const bool dy_parts = lp && defer && fuse_dy() && use_persistent<T>(H, lo.T, true, s) &&
                         persist_bwd_dy_partials_ok(H, B, lo.T);
+  // (float32 holds the bias sums for that launch too)
+  const bool hold_bias = dy_parts || (!lp && defer);
   // the row block of the persistent BPTT's bias partials
   const int rows_wg = lp ? persist_rows_per_workgroup(H, B) : persist32_rows_per_workgroup(H, B);
   ReduceGroup pending_dy;   // the held dX reduction the next BPTT takes over
@@ -672,8 +673,8 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
   const float* dY = dytop;
   for (int l = lo.L - 1; l >= 0; --l) {
     const int par = side ? (l & 1) : 0;
-    T* DA = lp ? (T*)(ws + lo.DA + l * lo.da_bytes) : (T*)(ws + lo.GX);
-    float* DBPl = (float*)(ws + lo.DBP + (dy_parts ? l : par) * lo.dbp_bytes);
+    T* DA = (T*)(ws + lo.DA + l * lo.da_bytes);
+    float* DBPl = (float*)(ws + lo.DBP + (hold_bias ? l : par) * lo.dbp_bytes);
     if (side && l + 2 < lo.L) (void)hipStreamWaitEvent(s, side->dw_done[l + 2], 0);
     const T* Xl = l == 0 ? (const T*)(ws + lo.X0) : (const T*)(ws + lo.Y[l - 1]);
     const int Dl = lo.layer_in(l), Dpl = lo.layer_in_pitch(l);
@@ -731,9 +732,6 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
       (void)hipStreamWaitEvent(ss, side->bptt_done[l], 0);
     }
     const int64_t Kr = (int64_t)(Tn - 1) * B;
-    float* part_ih = part_side;
-    float* part_hh = (float*)((char*)part_side + lo.skp_hh[l]);
-    float* part_dx = (float*)((char*)part + lo.skp_dx[l]);
     float* dst_dx = (dY == (const float*)(ws + lo.DYa)) ? (float*)(ws + lo.DYb) : (float*)(ws + lo.DYa);
     bool dx_done = l == 0, db_done = false;
     // W_ih of both directions as the dX product's B operand, read as it lies
@@ -749,26 +747,23 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
     const Opnd Bx = opnd(Xl, Dpl, Dpl, M);
     const Opnd Ah = opnd(DA + (int64_t)B * 8 * H, 8 * H, 4 * H, Kr, 4 * H - (int64_t)B * 8 * H);
     const Opnd Bh = opnd(Yl, 2 * H, H, Kr, (int64_t)B * 2 * H + H);
-    if constexpr (lp) {
+    {
       // without the side stream also dX_l (below), in the layer's own launch
       F32Job g[3];
-      g[0] = F32Job{Aw, Bx, 4 * H, Dl, M, 2, lo.sp_dWih[l], grad + lo.Wih[l][0], Dl, lo.Wih[l][1] - lo.Wih[l][0],
-                    part_ih};
-      g[1] = F32Job{Ah, Bh, 4 * H, H, Kr, 2, lo.sp_dWhh[l], grad + lo.Whh[l][0], H, lo.Whh[l][1] - lo.Whh[l][0],
-                    part_hh};
-      // the side stream's products take the whole k range per tile
-      g[0].splits = g[1].splits = 1;
+      // (the side stream's weight gradients take the whole k range per tile)
+      g[0] = F32Job{Aw, Bx, 4 * H, Dl, M, 2, 1, grad + lo.Wih[l][0], Dl, lo.Wih[l][1] - lo.Wih[l][0], nullptr};
+      g[1] = F32Job{Ah, Bh, 4 * H, H, Kr, 2, 1, grad + lo.Whh[l][0], H, lo.Whh[l][1] - lo.Whh[l][0], nullptr};
       const bool dx_here = !side && l > 0;
       if (dx_here)
-        g[2] = F32Job{opnd(DA, 8 * H, 8 * H, M), Bw, M, Dl, 8 * H, 1, lo.sp_dX[l], dst_dx, Dl, 0, part_dx};
+        g[2] = F32Job{opnd(DA, 8 * H, 8 * H, M), Bw, M, Dl, 8 * H, 1, lo.sp_dX[l], dst_dx, Dl, 0, part};
       // db_ih = db_hh = sum over frames of da, from the BPTT kernel's
       // per-row-block partials, in a reduction launch
       const int dbp_rows = done ? (int)cdiv(B, rows_wg) : Tn * (int)cdiv(B, 16);
       const ColSumJob cs{DBPl, dbp_rows, 2, 4 * H, 8 * H, 4 * H,
                          grad + lo.bih[l][0], grad + lo.bhh[l][0], lo.bih[l][1] - lo.bih[l][0]};
-      const bool with_db = step_fused && colsum_job_ok(cs);
+      const bool with_db = step_fused && (lp || done) && colsum_job_ok(cs);
       bool held_db = false;
-      if (dy_parts && with_db) {
+      if (hold_bias && with_db) {
         // the bias sums wait for the last BPTT; dX (if any) keeps its
         // partials for the next BPTT when it is split
         bias_jobs[nbias++] = cs;
@@ -776,7 +771,7 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
       }
       const ColSumJob* csj = with_db && !held_db ? &cs : nullptr;
       if (side) {
-        if (gemm_f32_group<false, false>("gemm_bwd_group", ss, 2, g, csj)) {
+        if (gemm_f32_group<T, false, false>("gemm_bwd_group", ss, 2, g, csj)) {
           db_done = csj != nullptr;
         } else {
           for (int i = 0; i < 2; ++i)
@@ -791,11 +786,11 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
         }
         if (dx_here) {
           ReduceGroup held;
-          if (gemm_f32_group<true, false>("gemm_bwd_group", s, 1, &g[2], csj, held_db ? &held : nullptr,
-                                          lo.big_dX[l])) {
+          if (gemm_f32_group<T, true, false>("gemm_bwd_group", s, 1, &g[2], csj,
+                                             dy_parts && held_db ? &held : nullptr, lo.big_dX[l])) {
             db_done = db_done || csj != nullptr;
-            if (held_db && held.n == 1) pending_dy = held;
-            else if (held_db) reduce_group_launch(s, held);
+            if (dy_parts && held_db && held.n == 1) pending_dy = held;
+            else if (dy_parts && held_db) reduce_group_launch(s, held);
           } else {
             gemm_f32<T, true, false, V, V>("gemm_dx", s, g[2].A, g[2].B, g[2].M, g[2].N, g[2].K, 1, g[2].splits,
                                            g[2].dst, g[2].ld, 0, g[2].part);
@@ -806,11 +801,6 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
         }
       }
       dx_done = dx_done || dx_here;
-    } else {
-      gemm_f32<T, false, false, V, V>("gemm_dwih", s, Aw, Bx, 4 * H, Dl, M, 2, lo.sp_dWih[l],
-                                      grad + lo.Wih[l][0], Dl, lo.Wih[l][1] - lo.Wih[l][0], part_ih);
-      gemm_f32<T, false, false, V, V>("gemm_dwhh", s, Ah, Bh, 4 * H, H, Kr, 2, lo.sp_dWhh[l],
-                                      grad + lo.Whh[l][0], H, lo.Whh[l][1] - lo.Whh[l][0], part_hh);
     }
     // db_ih = db_hh = sum over frames of da (unless the reduction above did it)
     if (!db_done) {
@@ -826,7 +816,7 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
     // dX_l = sum_d da_d W_ih[d]  (the gradient reaching the layer below)
     if (!dx_done) {
       const Opnd A = opnd(DA, 8 * H, 8 * H, M);
-      gemm_f32<T, true, false, V, V>("gemm_dx", s, A, Bw, M, Dl, 8 * H, 1, lo.sp_dX[l], dst_dx, Dl, 0, part_dx);
+      gemm_f32<T, true, false, V, V>("gemm_dx", s, A, Bw, M, Dl, 8 * H, 1, lo.sp_dX[l], dst_dx, Dl, 0, part);
     }
     if (l > 0) dY = dst_dx;
   }
@@ -851,7 +841,7 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
   // the chip is a partial one)
   for (int i0 = 0; i0 < nd; i0 += KC_MAX_GROUP) {
     const int n = std::min(KC_MAX_GROUP, nd - i0);
-    if (!gemm_f32_group<false, false>("gemm_dw_group", s, n, deferred + i0, nullptr, nullptr, lo.big_dw)) {
+    if (!gemm_f32_group<T, false, false>("gemm_dw_group", s, n, deferred + i0, nullptr, nullptr, lo.big_dw)) {
       for (int i = i0; i < i0 + n; ++i) {
         const F32Job& j = deferred[i];
         gemm_f32<T, false, false, V, V>((i & 1) ? "gemm_dwhh" : "gemm_dwih", s, j.A, j.B, j.M, j.N, j.K, j.batches,

@@ -89,6 +89,64 @@ static inline void colsum(const char* name, hipStream_t s, const T* X, int64_t M
   colsum_parts("colsum_final", s, part, chunks, N, seg, segstride, out1, out2);
 }
 
+// The column sums of two float32 matrices (16-byte aligned rows, widths of
+// whole chunks) in one launch of each pass.
+struct ColSum2 {
+  const float* X[2];
+  int64_t M[2], N[2], ld[2];
+  float* part[2];
+  float* out[2];
+  int chunks[2], xb[2];   // row ranges; blocks of 1024 columns (first pass), of 64 (second)
+};
+__global__ __launch_bounds__(256) static void colsum2_partial_kernel(const ColSum2 a) {
+  const int i = (int)blockIdx.x >= a.xb[0] * a.chunks[0];
+  const int b = (int)blockIdx.x - (i ? a.xb[0] * a.chunks[0] : 0);
+  const int64_t c = ((int64_t)(b % a.xb[i]) * 256 + threadIdx.x) * 4;
+  const int ch = b / a.xb[i];
+  if (c >= a.N[i]) return;
+  const int64_t rpc = cdiv(a.M[i], a.chunks[i]);
+  const int64_t r0 = ch * rpc, r1 = min(a.M[i], r0 + rpc);
+  f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+  for (int64_t r = r0; r < r1; ++r) s += *(const f32x4*)(a.X[i] + r * a.ld[i] + c);
+  float* o = a.part[i] + (int64_t)ch * a.N[i] + c;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) o[v] = s[v];
+}
+__global__ __launch_bounds__(256) static void colsum2_final_kernel(const ColSum2 a) {
+  __shared__ float q4[4][64];
+  const int nb = (int)cdiv(a.N[0], 64);
+  const int i = (int)blockIdx.x >= nb;
+  const int cl = threadIdx.x & 63, q = threadIdx.x >> 6;
+  const int64_t c = (int64_t)((int)blockIdx.x - (i ? nb : 0)) * 64 + cl;
+  const int per = (a.chunks[i] + 3) / 4;
+  const int p0 = q * per, p1 = min(a.chunks[i], p0 + per);
+  float s = 0.f;
+  if (c < a.N[i]) {
+#pragma unroll 8
+    for (int k = p0; k < p1; ++k) s += a.part[i][(int64_t)k * a.N[i] + c];
+  }
+  q4[q][cl] = s;
+  __syncthreads();
+  if (q == 0 && c < a.N[i]) a.out[i][c] = ((q4[0][cl] + q4[1][cl]) + q4[2][cl]) + q4[3][cl];
+}
+// False (and nothing launched) if a matrix does not fit the form above.
+static inline bool colsum2(hipStream_t s, const float* X0, int64_t M0, int64_t N0, int64_t ld0, float* part0,
+                           float* out0, const float* X1, int64_t M1, int64_t N1, int64_t ld1, float* part1,
+                           float* out1) {
+  ColSum2 a{{X0, X1}, {M0, M1}, {N0, N1}, {ld0, ld1}, {part0, part1}, {out0, out1}, {0, 0}, {0, 0}};
+  for (int i = 0; i < 2; ++i) {
+    if (a.N[i] % 4 != 0 || a.ld[i] % 4 != 0 || ((uintptr_t)a.X[i] & 15) != 0) return false;
+    a.xb[i] = (int)cdiv(a.N[i], 1024);
+    a.chunks[i] = (int)std::min<int64_t>(COLSUM_MAX_CHUNKS, std::max<int64_t>(16, cdiv(256, a.xb[i])));
+    a.chunks[i] = (int)std::max<int64_t>(1, std::min<int64_t>(a.chunks[i], a.M[i]));
+  }
+  BLSTM_LAUNCH("colsum", colsum2_partial_kernel, dim3((unsigned)(a.xb[0] * a.chunks[0] + a.xb[1] * a.chunks[1])),
+               dim3(256), 0, s, a);
+  BLSTM_LAUNCH("colsum_final", colsum2_final_kernel, dim3((unsigned)(cdiv(N0, 64) + cdiv(N1, 64))), dim3(256), 0, s, a);
+  return true;
+}
+
 // The same reduction, 4 adjacent columns per thread: block (m, column block
 // of 256, batch), 64 threads.  Needs N, ld, ldc multiples of 4 and aligned
 // destinations.  Optional: a per-column bias added to the sum, and no
@@ -271,7 +329,7 @@ static inline bool colsum_job_launch(const char* name, hipStream_t s, const ColS
 // cs (optional): column sums added to the reduction launch.
 // held (optional): the reduction is not launched but returned there, for
 // the caller to launch later or to leave to a consumer of the partials.
-template <bool AKC, bool BKC>
+template <typename T, bool AKC, bool BKC>
 static inline bool gemm_f32_group(const char* name, hipStream_t s, int n, const F32Job* jb,
                                   const ColSumJob* cs = nullptr, ReduceGroup* held = nullptr, bool big = false) {
   if (n < 1 || n > KC_MAX_GROUP || (cs && (n == KC_MAX_GROUP || !colsum_job_ok(*cs)))) return false;
@@ -305,7 +363,10 @@ static inline bool gemm_f32_group(const char* name, hipStream_t s, int n, const 
     rg.j[rg.n] = colsum_reduce_job(*cs, rblocks);
     rblocks += (int)cdiv((int64_t)rg.j[rg.n++].count, 256);
   }
-  if (!gemm_kc_group_launch<AKC, BKC>(name, s, n, it, e, big)) return false;
+  bool ok;
+  if constexpr (std::is_same<T, float>::value) ok = gemm_f32_group_launch<AKC, BKC>(name, s, n, it, e);
+  else ok = gemm_kc_group_launch<AKC, BKC>(name, s, n, it, e, big);
+  if (!ok) return false;
   if (held) *held = rg;
   else if (rg.n) reduce_group_launch(s, rg);
   return true;
