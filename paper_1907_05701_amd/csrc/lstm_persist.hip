@@ -2,10 +2,9 @@
 // of one layer, for both directions at once, and each workgroup keeps its
 // slice of W_hh in registers for the whole chunk.
 //
-// Work split.  The batch is cut into slices of RV rows (8 when all the
-// batch's 8-row slices fit one launch at one workgroup per CU, else 16,
-// with launches of up to 16 slices), each on 16-row MFMA tiles;
-// a group of NM = ceil(H/64) workgroups ("members") owns one (direction, slice)
+// Work split.  The batch is cut into slices of RV rows (8 or 16 when all the
+// batch's slices of that size fit one launch at one workgroup per CU, else
+// 32: persist_plan), each on 16-row MFMA tiles; a group of NM = ceil(H/64) workgroups ("members") owns one (direction, slice)
 // pair, and member m owns hidden units [64m, 64m + 64), i.e. 256 gate rows
 // of W_hh (256 KB at H = 512: 128 VGPRs in each of the workgroup's 8
 // waves).  Eight members per group instead of sixteen halves the chip-wide
@@ -583,8 +582,14 @@ __global__ __launch_bounds__(NTH) void lstm_fwd_persist(const PersistArgs a) {
 // order, and swap partial sums with DPP so that each lane ends with the
 // total of its 4 / LPI rows, whose cells it then computes.  So the gathered
 // sums never pass through LDS and a step has one barrier (own da complete).
+//
+// F32X: the partial sums travel as float32, one word each (row quad, member,
+// row, unit; a 32-bit tag): four times the words, for the widths that 64 does
+// not divide, whose recurrence has always kept them in float32 (the per-step
+// kernels, which ran these widths before at 6.1 / 11.9 us a step for H = 96 /
+// 480, B = 128, T = 21; now 2.2 / 4.1, and the forward 5.3 / 7.4 -> 1.9 / 2.8).
 // ---------------------------------------------------------------------------
-template <int RV>
+template <int RV, bool F32X>
 __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
   extern __shared__ __attribute__((aligned(16))) char lds_raw[];
   static_assert(RV == 8 || RV == 16 || RV == 32, "rows per workgroup");
@@ -668,7 +673,8 @@ __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
   const int rend = a.b0 + a.rows;
   const int rowbase = a.b0 + s * RV;
   const int rquads = (a.rows + 3) / 4;             // row quads of this launch
-  const int64_t slot_stride = (int64_t)2 * rquads * NM * H;
+  constexpr int WPQ = F32X ? 4 : 1;                // words per (row quad, member, unit)
+  const int64_t slot_stride = (int64_t)2 * rquads * NM * H * WPQ;
   // this lane's item: unit cu of row quad qd, rows rl0 .. rl0 + RPT - 1
   const int sub = tid % LPI, item = tid / LPI;
   const int cu = item & 63, qd = item >> 6, rl0 = qd * 4 + sub * RPT;
@@ -755,11 +761,13 @@ __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
   fetch(0);
 
   const int m0 = sub * MPL, mcount = max(0, min(NM, m0 + MPL) - m0);
-  const uint32_t ogath = (uint32_t)((((int64_t)d * rquads + (rowbase - a.b0) / 4 + qd) * NM + m0) * H + u0 + cu);
+  const uint32_t ogath =
+      (uint32_t)((((int64_t)d * rquads + (rowbase - a.b0) / 4 + qd) * NM + m0) * WPQ * H + u0 + cu);
   // word offset (within a slot) of the first published word; unit block j and
   // row tile tl are 128 j units and 4 tl row quads further
-  const uint32_t opub = (uint32_t)((((int64_t)d * rquads + (rowbase - a.b0) / 4 + (lane >> 4)) * NM + mem) * H +
+  const uint32_t opub = (uint32_t)((((int64_t)d * rquads + (rowbase - a.b0) / 4 + (lane >> 4)) * NM + mem) * WPQ * H +
                                    w * 16 + (lane & 15));
+  const uint32_t tag0 = a.seq * (uint32_t)Tn + 1;   // F32X: + step; launches of a call never meet (T B <= 2^24)
   // da out: pieces of 8 own gate rows of one row
   constexpr int NDT = RV == 8 ? NTH / 2 : NTH;   // threads writing DA: waves 4-7 when that is one piece each
   constexpr int NDA = 32 * RV / NDT;
@@ -794,14 +802,32 @@ __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
       const uint64_t want = h4_tag(a.seq, tau);
       f32x4 sum = f32x4{0.f, 0.f, 0.f, 0.f};
       if (rowbase + 4 * qd < rend && u0 + cu < H) {
-        uint64_t wv[MPL];
+        if constexpr (F32X) {
+          // two members (eight words) at a time
 #pragma unroll
-        for (int k = 0; k < MPL; ++k) wv[k] = k < mcount ? ll_load(base + (int64_t)k * H) : want;
-        poll_words<MPL>(wv, base, H, want, a.status);
+          for (int k0 = 0; k0 < MPL; k0 += 2) {
+            uint64_t wv[8];
+            uint32_t off[8];
 #pragma unroll
-        for (int k = 0; k < MPL; ++k)
-          if (k < mcount) sum += p15x4_decode_scaled(wv[k]);
-        sum *= 0x1p64f;
+            for (int j = 0; j < 8; ++j) {
+              const bool ok = k0 + j / 4 < mcount;
+              off[j] = ok ? (uint32_t)(((k0 + j / 4) * 4 + j % 4) * H) : 0;
+              wv[j] = ok ? ll_load(base + off[j]) : (uint64_t)(tag0 + tau) << 32;
+            }
+            poll_tagged<8>(wv, base, off, tag0 + tau, a.status);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) sum[j % 4] += __builtin_bit_cast(float, (uint32_t)wv[j]);
+          }
+        } else {
+          uint64_t wv[MPL];
+#pragma unroll
+          for (int k = 0; k < MPL; ++k) wv[k] = k < mcount ? ll_load(base + (int64_t)k * H) : want;
+          poll_words<MPL>(wv, base, H, want, a.status);
+#pragma unroll
+          for (int k = 0; k < MPL; ++k)
+            if (k < mcount) sum += p15x4_decode_scaled(wv[k]);
+          sum *= 0x1p64f;
+        }
       }
       // the lanes of one (row quad, unit) add their members' sums
       if constexpr (LPI == 1) {
@@ -842,11 +868,11 @@ __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
       const bool ok = rowbase + r < rend && u0 + cu < H;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const bf16 v = ok ? (bf16)da[q] : (bf16)0.f;
+        const float dq = ok ? da[q] : 0.f;
         // own row kk = (cu >> 4)*64 + q*16 + (cu & 15)
         const int kk = (cu >> 4) * 64 + q * 16 + (cu & 15);
-        al[((kk >> 3) * (R + 1) + r) * 8 + (kk & 7)] = v;
-        dbacc[q] += (float)v;
+        al[((kk >> 3) * (R + 1) + r) * 8 + (kk & 7)] = (bf16)dq;
+        dbacc[q] += dq;   // the bias gradient sums da before it is rounded
       }
       cc[i] = cp[i];   // c at the next step's t
     }
@@ -881,9 +907,16 @@ __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
         const int rl = tl * 16 + (lane >> 4) * 4;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const uint64_t v = p15x4_encode(acc[j]);
-          if (rl < RV && rowbase + rl < rend && w + 8 * j < NB)
-            ll_store64(xo + opub + (uint32_t)(tl * 4 * NM * H + j * 128), v | tg, local);
+          if (rl < RV && rowbase + rl < rend && w + 8 * j < NB) {
+            uint64_t* xw = xo + opub + (uint32_t)(tl * 4 * NM * WPQ * H + j * 128);
+            if constexpr (F32X) {
+#pragma unroll
+              for (int r = 0; r < 4; ++r)
+                ll_store64(xw + r * H, ((uint64_t)(tag0 + tau + 1) << 32) | __float_as_uint(acc[j][r]), local);
+            } else {
+              ll_store64(xw, p15x4_encode(acc[j]) | tg, local);
+            }
+          }
         }
       }
     }
@@ -1041,7 +1074,10 @@ int persist_groups(int groups, int members) {
 template <int RV, bool BWD>
 static hipError_t launch_one(PersistArgs a, hipStream_t s) {
   const void* fn;
-  if constexpr (BWD) fn = (const void*)lstm_bwd_persist<RV>;
+  if constexpr (BWD && RV < 32)
+    fn = a.H % PU ? (const void*)lstm_bwd_persist<RV, true> : (const void*)lstm_bwd_persist<RV, false>;
+  else if constexpr (BWD)
+    fn = (const void*)lstm_bwd_persist<RV, false>;
   else fn = (const void*)lstm_fwd_persist<RV>;
   return persist_launch(BWD ? "lstm_rec_bwd_persist" : "lstm_rec_fwd_persist", fn, dim3(a.NG * members(a.H)), NTH,
                         persist_lds_bytes(a.H, BWD, RV), &a, s);
@@ -1055,11 +1091,14 @@ static bool persist_plan(int H, int B, int* RVo, int* chunko) {
   const int NM = members(H);
   const int max_ns = std::min(persist_max_wg() / (2 * NM), PERSIST_MAX_SLICES);
   if (max_ns < 1) return false;
-  int RV = (B + 7) / 8 <= max_ns ? 8 : (B + 15) / 16 <= max_ns ? 16 : 32;
+  // (float32 partial sums, H % 64 != 0: at most 16 rows, the gather of more
+  // spills)
+  const int most = H % PU ? 16 : 32;
+  int RV = (B + 7) / 8 <= max_ns ? 8 : (B + 15) / 16 <= max_ns ? 16 : most;
   // ADPSGD_BLSTM_ROWS_PER_WG=16 or 32 keeps that many rows per workgroup at
   // any batch (fewer workgroups at small batches, for measurements and tests)
   if (const char* e = getenv("ADPSGD_BLSTM_ROWS_PER_WG"))
-    if (atoi(e) == 16 || atoi(e) == 32) RV = atoi(e);
+    if (atoi(e) == 16 || atoi(e) == 32) RV = std::min(atoi(e), most);
   *RVo = RV;
   *chunko = std::min(B, max_ns * RV);
   return true;
@@ -1088,8 +1127,8 @@ hipError_t persist_clear(bool backward, const PersistArgs& a, hipStream_t s) {
   if (!persist_plan(a.H, a.B, &RV, &chunk)) return hipErrorInvalidValue;
   // both exchange slots start without any valid tag; the forward's clear
   // also initialises the status block of a fresh workspace
-  const int64_t words = PERSIST_PLACE_WORDS + (backward ? (int64_t)2 * 2 * ((chunk + 3) / 4) * members(a.H) * a.H
-                                 : (int64_t)2 * 2 * chunk * (a.H / 4));
+  const int64_t part = (int64_t)((chunk + 3) / 4) * members(a.H) * a.H * (a.H % PU ? 4 : 1);
+  const int64_t words = PERSIST_PLACE_WORDS + 2 * 2 * (backward ? part : (int64_t)chunk * (a.H / 4));
   return persist_clear_words(a.place, words / 2, backward ? nullptr : a.status, s);
 }
 

@@ -32,6 +32,29 @@ __device__ __forceinline__ void ll_store64(uint64_t* p, uint64_t v, bool local) 
 }
 
 #define PERSIST_SPIN_LIMIT (1u << 18)
+// Polls word j at base[off[j]] until all carry `want` (one already holding
+// it is not read again); gives up after PERSIST_SPIN_LIMIT polls, or at once when
+// any wait anywhere has given up, so every wave ends.
+template <int N>
+__device__ __forceinline__ void poll_tagged(uint64_t (&wv)[N], const uint64_t* base, const uint32_t (&off)[N],
+                                            uint32_t want, int* status) {
+  for (unsigned it = 0;; ++it) {
+    bool bad = false;
+#pragma unroll
+    for (int j = 0; j < N; ++j) bad |= (uint32_t)(wv[j] >> 32) != want;
+    if (!bad) break;
+    if (it > PERSIST_SPIN_LIMIT ||
+        ((it & 63) == 63 && __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
+      __hip_atomic_store(status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      break;
+    }
+    __builtin_amdgcn_s_sleep(1);
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+      if ((uint32_t)(wv[j] >> 32) != want) wv[j] = ll_load(base + off[j]);
+  }
+}
+
 // Placement words in front of the exchange words, one per workgroup of a
 // launch: (launch mark << 32) | XCD.
 #define PERSIST_PLACE_WORDS 1024
@@ -108,12 +131,12 @@ struct PersistArgs {
 #define PERSIST_MAX_SLICES 32
 #define PERSIST_MAX_ROWS (PERSIST_MAX_SLICES * 32)
 // Exchange buffer: the placement words, then 2 slots x 2 directions x row quads x (H/64 members, rounded up) x H
-// units words of 8 bytes (the backward's partial sums, four rows per word;
-// the forward uses H/4 words per row, never more).
+// units words of 8 bytes (the backward's partial sums: four rows per word, one
+// where 64 does not divide H; the forward uses H/4 words per row, never more).
 static inline size_t persist_xch_bytes(int B, int H) {
   const size_t rows = B < PERSIST_MAX_ROWS ? B : PERSIST_MAX_ROWS;
   const size_t members = (H + 63) / 64;
-  const size_t bwd = (size_t)2 * 2 * ((rows + 3) / 4) * members * H * 8;
+  const size_t bwd = (size_t)2 * 2 * ((rows + 3) / 4) * members * H * 8 * (H % 64 ? 4 : 1);
   const size_t fwd = (size_t)2 * 2 * rows * (H / 4 > 0 ? H / 4 : 1) * 8;
   return (bwd > fwd ? bwd : fwd) + PERSIST_PLACE_WORDS * 8;
 }

@@ -69,29 +69,6 @@ __device__ __forceinline__ void p32_publish(uint64_t* p, float v, uint32_t tag, 
   ll_store64(p, ((uint64_t)tag << 32) | __builtin_bit_cast(uint32_t, v), local);
 }
 
-// Polls word j at base[off[j]] until all carry `want` (one already holding
-// it is not read again); gives up after PERSIST_SPIN_LIMIT polls, or at once when
-// any wait anywhere has given up, so every wave ends.
-template <int N>
-__device__ __forceinline__ void p32_poll(uint64_t (&wv)[N], const uint64_t* base, const uint32_t (&off)[N],
-                                         uint32_t want, int* status) {
-  for (unsigned it = 0;; ++it) {
-    bool bad = false;
-#pragma unroll
-    for (int j = 0; j < N; ++j) bad |= (uint32_t)(wv[j] >> 32) != want;
-    if (!bad) break;
-    if (it > PERSIST_SPIN_LIMIT ||
-        ((it & 63) == 63 && __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
-      __hip_atomic_store(status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      break;
-    }
-    __builtin_amdgcn_s_sleep(1);
-#pragma unroll
-    for (int j = 0; j < N; ++j)
-      if ((uint32_t)(wv[j] >> 32) != want) wv[j] = ll_load(base + off[j]);
-  }
-}
-
 // LDS row pitch (floats) of a row operand of n k values: the 4 rows x 16 k
 // of one operand read fall in 64 distinct banks.
 __host__ __device__ static inline int p32_pitch(int n) { return (n + 63) / 64 * 64 + 16; }
@@ -197,7 +174,7 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_fwd_persist32(const Persist3
             off[j] = (uint32_t)idx;
             wv[j] = idx < nwords && rowbase + idx / H < rend ? ll_load(src + idx) : (uint64_t)want << 32;
           }
-          p32_poll<GB>(wv, src, off, want, a.status);
+          poll_tagged<GB>(wv, src, off, want, a.status);
 #pragma unroll
           for (int j = 0; j < GB; ++j) {
             const int idx = j0 + j * P32_THREADS;
@@ -360,7 +337,7 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_bwd_persist32(const Persist3
             off[j] = (uint32_t)((((int64_t)d * parts + (ok ? p : 0)) * a.rows + (ok ? row - a.b0 : 0)) * H + unitc);
             wv[j] = ok ? ll_load(src + off[j]) : (uint64_t)want << 32;
           }
-          p32_poll<IB * MPP>(wv, src, off, want, a.status);
+          poll_tagged<IB * MPP>(wv, src, off, want, a.status);
 #pragma unroll
           for (int j = 0; j < IB * MPP; ++j) dhr[i0 + j / MPP] += __builtin_bit_cast(float, (uint32_t)wv[j]);
         }

@@ -13,10 +13,11 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("H,T,B", [
     (32, 3, 1), (32, 5, 301),          # one member of 32 units; 16-row workgroups
-    (96, 4, 9), (96, 3, 530),          # two members; 32-row workgroups
+    (96, 4, 9), (96, 3, 530),          # two members; two launches
     (160, 4, 203), (288, 3, 100),      # three and five members (five: groups not padded at this batch)
-    (480, 3, 130), (480, 2, 517),      # eight members: 16-row workgroups, 32-row ones in two launches
+    (480, 3, 130), (480, 2, 517),      # eight members: 16-row workgroups, in one launch and in three
     (512, 3, 511), (512, 2, 61),       # 32-row workgroups with a partial quad, padded groups
+    (192, 2, 1350),                    # 32-row workgroups in two launches
 ], ids=lambda v: str(v))
 def test_recurrence_plan_edges(gpu_lib, H, T, B):
     run_step_and_compare(dict(L=2, D=20, H=H, P=16, K=30, T=T, B=B), "bf16", BF16_TOL, seed=23, check_update=False)
