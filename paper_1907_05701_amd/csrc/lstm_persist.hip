@@ -907,15 +907,17 @@ __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
         const int rl = tl * 16 + (lane >> 4) * 4;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          if (rl < RV && rowbase + rl < rend && w + 8 * j < NB) {
-            uint64_t* xw = xo + opub + (uint32_t)(tl * 4 * NM * WPQ * H + j * 128);
-            if constexpr (F32X) {
+          if constexpr (F32X) {
+            if (rl < RV && rowbase + rl < rend && w + 8 * j < NB) {
+              uint64_t* xw = xo + opub + (uint32_t)(tl * 16 * NM * H + j * 128);
 #pragma unroll
               for (int r = 0; r < 4; ++r)
                 ll_store64(xw + r * H, ((uint64_t)(tag0 + tau + 1) << 32) | __float_as_uint(acc[j][r]), local);
-            } else {
-              ll_store64(xw, p15x4_encode(acc[j]) | tg, local);
             }
+          } else {
+            const uint64_t v = p15x4_encode(acc[j]);   // (inside the branch, two registers spill at RV = 32)
+            if (rl < RV && rowbase + rl < rend && w + 8 * j < NB)
+              ll_store64(xo + opub + (uint32_t)(tl * 4 * NM * H + j * 128), v | tg, local);
           }
         }
       }
