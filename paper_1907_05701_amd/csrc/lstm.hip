@@ -613,9 +613,8 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
   float* part = (float*)(ws + lo.SKP);
   float* csp = (float*)(ws + lo.CSP);
   constexpr bool lp = std::is_same<T, bf16>::value;
-  // W_hh^T (bf16 and float32 paths): the per-step BPTT kernels' operand and
-  // the persistent kernel's LDS staging source when a workgroup takes more
-  // than one 16-row block.  One launch makes all layers'.
+  // W_hh^T (bf16 and float32 paths): the per-step BPTT kernels' operand.  One
+  // launch makes all layers'.
   bool have_wt = false;
   auto make_copies = [&]() {
     if constexpr (lp) {
@@ -637,7 +636,7 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
     }
     have_wt = true;
   };
-  if (!use_persistent<T>(H, lo.T, true, s) || persist_bwd_needs_wt(H, B)) make_copies();
+  if (!use_persistent<T>(H, lo.T, true, s)) make_copies();
   // weight gradients on the side stream (bf16 per-step BPTT): layer l's bias
   // partials alternate by layer parity, so BPTT of layer l waits only for the
   // side work of l+2
@@ -697,7 +696,6 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
       PersistArgs pa = persist_args(lo, (const bf16*)W, ws, l);
       pa.tag = (uint32_t)(lo.L - 1 - l);   // the backward runs the layers top-down
       pa.DA = (bf16*)DA; pa.DY = dY; pa.C = (float*)Cl; pa.G = (bf16*)Gl;
-      pa.WT = have_wt ? (const bf16*)(WT + (int64_t)(2 * l) * 4 * H * H) : nullptr;
       pa.DBP = DBPl;
       if (pending_dy.n == 1) {
         pa.DYP = pending_dy.j[0].part;

@@ -1122,8 +1122,6 @@ bool persist_bwd_dy_partials_ok(int H, int B, int T) {
   return (size_t)bwd_dy_lds(RV) + (size_t)T * RV * PU * 4 <= persist_lds_bytes(H, true, RV);
 }
 
-bool persist_bwd_needs_wt(int, int) { return false; }
-
 hipError_t persist_clear(bool backward, const PersistArgs& a, hipStream_t s) {
   int RV, chunk;
   if (!persist_plan(a.H, a.B, &RV, &chunk)) return hipErrorInvalidValue;

@@ -89,7 +89,6 @@ struct PersistArgs {
   bf16* Y;            // layer output [M][2H] (forward: read h_prev, write h)
   const bf16* W;      // bf16 parameter copy (flat layout)
   int64_t whh0, whh1; // element offsets of W_hh for the two directions
-  const bf16* WT;     // unused by the persistent kernels (W_hh^T of the layer, [2][H][4H])
   bf16* Gx;           // forward: input projection incl. both biases [M][8H] (written by the
                       // kernel itself when Xin is set, else read only)
   // forward, optional: the layer input and W_ih, so that each workgroup
@@ -150,12 +149,9 @@ bool persist_bwd_dy_partials_ok(int H, int B, int T);
 bool persist_supported(int H, int T);
 // Workgroups of a layer's largest launch for this H and B.
 int persist_workgroups(int H, int B);
-// Batch rows per persistent workgroup (8 or 16) for this H and B: the row
+// Batch rows per persistent workgroup (8, 16 or 32) for this H and B: the row
 // block of the BPTT's bias partial sums (PersistArgs::DBP).
 int persist_rows_per_workgroup(int H, int B);
-// Whether the persistent BPTT of a layer reads W_hh^T (PersistArgs::WT):
-// never (its W_hh rows are read as they lie).
-bool persist_bwd_needs_wt(int H, int B);
 // Status block (PERSIST_STATUS_BYTES at the end of the activation
 // workspace): an int flag set by any exchange wait that gives up, and a tag
 // that marks the block initialised.  The flag is sticky across calls.
