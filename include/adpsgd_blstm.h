@@ -158,8 +158,11 @@ int blstm_bwd(const blstm_dims* dims, const float* theta, const void* theta_lp,
  * used): the flag is sticky, so one query after many steps (or after replays
  * of a captured graph) covers all of them.  The persistent kernels are plain
  * launches when the occupancy query shows the whole grid resident at once;
- * if other streams or processes occupy CUs, a wait gives up after its bound
- * instead of hanging and the results of that call are not valid.  The flag
+ * calls on several streams of a process take turns with them (each waits on
+ * the device for the one before; captured calls do not: replay graphs that
+ * hold them one after another).  If other processes or work that never ends
+ * occupy CUs, a wait gives up after its bound instead of hanging and the
+ * results of that call are not valid.  The flag
  * lives in the last 256 bytes of act_ws (an int32 at offset act_ws_bytes -
  * 256, nonzero after a give-up, and an initialisation tag); the query reads
  * it, clears it, and returns BLSTM_OK or BLSTM_EHIP with a message.

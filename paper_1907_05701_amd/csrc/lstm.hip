@@ -408,6 +408,68 @@ static bool use_persistent(int H, int steps, bool backward, hipStream_t s) {
   return std::is_same<T, bf16>::value ? persist_supported(H, steps) : persist32_supported(H);
 }
 
+// Whether the persistent workgroups of a layer of H cells wait for each other
+// (members of 64 units in bf16; in float32 one member up to 128 cells).
+template <typename T>
+static bool persist_exchanges(int H) { return H > (std::is_same<T, float>::value ? 128 : 64); }
+
+// The turn of one forward or backward call to run launches whose workgroups
+// wait for each other.  Two such launches on the chip at once, from two streams
+// of a program, could each hold CUs that the other's missing workgroups need,
+// and both would give up.  So a call holds its device's turn while it enqueues,
+// its stream first waits for the previous holder's last such launch, and done()
+// (or the destructor) marks its own.  Nothing under stream capture: replays are
+// ordered by whoever launches the graph.
+#define PERSIST_MAX_DEVICES 64
+class PersistTurn {
+ public:
+  PersistTurn(bool wanted, hipStream_t s) : s_(s) {
+    if (!wanted) return;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    int dev = 0;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess || hipGetDevice(&dev) != hipSuccess) {
+      (void)hipGetLastError();
+      return;
+    }
+    if (cap != hipStreamCaptureStatusNone || dev >= PERSIST_MAX_DEVICES) return;
+    Slot* slot = slots() + dev;
+    slot->m.lock();
+    // (it orders launches only, so it needs no fence towards the host)
+    if (!slot->ev &&
+        hipEventCreateWithFlags(&slot->ev, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess) {
+      (void)hipGetLastError();
+      slot->ev = nullptr;
+      slot->m.unlock();
+      return;
+    }
+    if (slot->any && hipStreamWaitEvent(s, slot->ev, 0) != hipSuccess) (void)hipGetLastError();
+    slot_ = slot;
+  }
+  ~PersistTurn() { done(); }
+  PersistTurn(const PersistTurn&) = delete;
+  PersistTurn& operator=(const PersistTurn&) = delete;
+  void done() {
+    if (!slot_) return;
+    if (hipEventRecord(slot_->ev, s_) == hipSuccess) slot_->any = true;
+    else (void)hipGetLastError();
+    slot_->m.unlock();
+    slot_ = nullptr;
+  }
+
+ private:
+  struct Slot {
+    std::mutex m;
+    hipEvent_t ev = nullptr;   // after the last holder's last launch
+    bool any = false;          // recorded
+  };
+  static Slot* slots() {   // (never destroyed: calls may run while the process ends)
+    static Slot* s = new Slot[PERSIST_MAX_DEVICES];
+    return s;
+  }
+  Slot* slot_ = nullptr;
+  hipStream_t s_;
+};
+
 static PersistArgs persist_args(const Layout& lo, const bf16* W, char* ws, int l) {
   PersistArgs pa;
   memset(&pa, 0, sizeof(pa));
@@ -485,6 +547,7 @@ static int fwd_impl(const Layout& lo, const float* theta, const T* W, const floa
     BLSTM_LAUNCH("convert_input", convert_input_kernel<T>, dim3(grid), dim3(256), 0, s, x, M, lo.D,
                  lo.Dp0, X0, (const bf16*)W + lo.Wih[0][0], lo.Wih[0][1] - lo.Wih[0][0], 4 * H, WP0);
   }
+  PersistTurn turn(persist && persist_exchanges<T>(H), s);
   for (int l = 0; l < lo.L; ++l) {
     const T* Xl = l == 0 ? X0 : (const T*)(ws + lo.Y[l - 1]);
     const int Dl = lo.layer_in(l), Dpl = lo.layer_in_pitch(l);
@@ -670,6 +733,7 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
   ColSumJob bias_jobs[MAX_LAYERS];
   int nbias = 0;
   const float* dY = dytop;
+  PersistTurn turn(persist_exchanges<T>(H) && use_persistent<T>(H, lo.T, true, s), s);
   for (int l = lo.L - 1; l >= 0; --l) {
     const int par = side ? (l & 1) : 0;
     T* DA = (T*)(ws + lo.DA + l * lo.da_bytes);
@@ -725,6 +789,7 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
       }
       step_fused = true;
     }
+    if (l == 0) turn.done();
     if (side) {
       (void)hipEventRecord(side->bptt_done[l], s);
       (void)hipStreamWaitEvent(ss, side->bptt_done[l], 0);

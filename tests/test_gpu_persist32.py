@@ -32,3 +32,50 @@ def test_float32_recurrence_many_steps(gpu_lib):
 ], ids=lambda s: f"H{s['H']}_M{s['T'] * s['B']}")
 def test_float32_products_at_block_edges(gpu_lib, shape):
     run_step_and_compare(shape, "fp32", FP32_TOL, seed=19)
+
+
+@pytest.mark.parametrize("precision,H", [("fp32", 512), ("bf16", 480)])
+def test_steps_on_two_streams(gpu_lib, precision, H):
+    """Two models stepped by two threads on streams of their own: launches that
+    need the whole chip take turns, no exchange wait gives up, and the outputs
+    are those of the same passes alone, bit for bit."""
+    import threading
+
+    import torch
+
+    from paper_1907_05701_amd.step import LearnerStep
+
+    shape = dict(L=2, D=40, H=H, P=16, K=30, T=9, B=128)
+    steps, streams = [], [torch.cuda.Stream() for _ in range(2)]
+    for i in range(2):
+        st = LearnerStep(**shape, precision=precision)
+        g = torch.Generator(device="cuda").manual_seed(41 + i)
+        st.grad.zero_()
+        st.theta.copy_(torch.rand(st.theta.numel(), generator=g, device="cuda") * 0.2 - 0.1)
+        st.pack()
+        st.x.copy_(torch.randn(st.x.shape, generator=g, device="cuda"))
+        dy = torch.randn((shape["T"], shape["B"], 2 * H), generator=g, device="cuda") * 1e-3
+        steps.append((st, dy))
+    want = []
+    for st, dy in steps:
+        st.forward()
+        st.backward(dy)
+        want.append((st.y_top.clone(), st.grad.clone()))
+    torch.cuda.synchronize()
+
+    def passes(i):
+        st, dy = steps[i]
+        with torch.cuda.stream(streams[i]):
+            for _ in range(10):
+                st.forward()
+                st.backward(dy)
+
+    threads = [threading.Thread(target=passes, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    for (st, _), (y, grad) in zip(steps, want):
+        st.check_recurrence()
+        assert torch.equal(st.y_top, y) and torch.equal(st.grad, grad)
