@@ -159,8 +159,9 @@ int blstm_bwd(const blstm_dims* dims, const float* theta, const void* theta_lp,
  * of a captured graph) covers all of them.  The persistent kernels are plain
  * launches when the occupancy query shows the whole grid resident at once;
  * calls on several streams of a process take turns with them (each waits on
- * the device for the one before; captured calls do not: replay graphs that
- * hold them one after another).  If other processes or work that never ends
+ * the device for the one before), except that bf16 calls of a width that 64
+ * divides are not waited for, and captured calls not at all: run those from
+ * one stream at a time.  If other launches of that kind or other processes
  * occupy CUs, a wait gives up after its bound instead of hanging and the
  * results of that call are not valid.  The flag
  * lives in the last 256 bytes of act_ws (an int32 at offset act_ws_bytes -
