@@ -156,20 +156,19 @@ int blstm_bwd(const blstm_dims* dims, const float* theta, const void* theta_lp,
 /* Whether every recurrent exchange wait of the persistent kernels completed
  * since the previous blstm_recurrence_ok on act_ws (or since act_ws was first
  * used): the flag is sticky, so one query after many steps (or after replays
- * of a captured graph) covers all of them.  The persistent kernels are plain
- * launches when the occupancy query shows the whole grid resident at once;
- * calls on several streams of a process take turns with them (each waits on
- * the device for the one before), except that bf16 calls of a width that 64
- * divides are not waited for, and captured calls not at all: run those from
- * one stream at a time.  If other launches of that kind or other processes
- * occupy CUs, a wait gives up after its bound instead of hanging and the
- * results of that call are not valid.  The flag
- * lives in the last 256 bytes of act_ws (an int32 at offset act_ws_bytes -
- * 256, nonzero after a give-up, and an initialisation tag); the query reads
- * it, clears it, and returns BLSTM_OK or BLSTM_EHIP with a message.
- * Synchronises `stream`; not during stream capture.
- * ADPSGD_BLSTM_COOPERATIVE=1 makes every persistent launch cooperative
- * (guaranteed residency, about 15 us more per launch). */
+ * of a captured graph) covers all of them.  The workgroups of a persistent
+ * launch that wait for each other start only once all of them run, and where
+ * other streams, graphs or processes keep some of them from that, one of them
+ * does the work of all, with the same results; so calls may overlap with any
+ * other work on the device.  Every wait is bounded all the same: should one
+ * give up, the kernel still ends, the flag is set, and the results of that call
+ * are not valid.  The flag lives in the last 256 bytes of act_ws (an int32 at
+ * offset act_ws_bytes - 256, nonzero after a give-up, one behind it that is
+ * nonzero if work was done by one workgroup in that way, and an initialisation
+ * tag); the query reads it, clears both, and returns BLSTM_OK or BLSTM_EHIP
+ * with a message.  Synchronises `stream`; not during stream capture.
+ * ADPSGD_BLSTM_COOPERATIVE=1 makes every persistent launch cooperative (about
+ * 15 us more per launch), for comparisons. */
 int blstm_recurrence_ok(const blstm_dims* dims, const void* act_ws, hipStream_t stream);
 
 /* Super-learner reduction (eq. 6): out = scale * sum_{r=0}^{R-1} grads[r],

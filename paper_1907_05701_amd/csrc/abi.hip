@@ -225,6 +225,7 @@ int make_layout(const blstm_dims* d, Layout* lo) {
   skp = std::max(skp, dw);
   L.SKP = a; a = align256(a + skp);
   L.XCH = a; a = align256(a + (es == 2 ? persist_xch_bytes(d->B, d->H) : persist32_xch_bytes(d->B, d->H)));   // recurrent step exchange
+  L.GST = a; a = align256(a + (es == 2 ? persist_state_bytes(d->B, d->H) : persist32_state_bytes(d->B, d->H)));
   // recurrence status block, the last PERSIST_STATUS_BYTES of act_ws
   L.SYNC = a; a += PERSIST_STATUS_BYTES;
   L.act_bytes = a;

@@ -408,83 +408,15 @@ static bool use_persistent(int H, int steps, bool backward, hipStream_t s) {
   return std::is_same<T, bf16>::value ? persist_supported(H, steps) : persist32_supported(H);
 }
 
-// Whether the persistent workgroups of a layer of H cells wait for each other
-// (members of 64 units in bf16; in float32 one member up to 128 cells).
-template <typename T>
-static bool persist_exchanges(int H) { return H > (std::is_same<T, float>::value ? 128 : 64); }
-
-// The turn of one forward or backward call to run launches whose workgroups
-// wait for each other.  Two such launches on the chip at once, from two streams
-// of a program, could each hold CUs that the other's missing workgroups need,
-// and both would give up.  So a call holds its device's turn while it enqueues,
-// its stream first waits for the previous holder's last such launch, and done()
-// (or the destructor) marks its own.  Nothing under stream capture: replays are
-// ordered by whoever launches the graph.  The event costs 3.3 us of GPU time a
-// call (a forward of two steps: 18.5 -> 21.8 us), the wait nothing; so bf16
-// widths that 64 divides, which a program is to run from one stream at a time,
-// wait but mark nothing (`marks`), and the others, which no such limit binds,
-// are safe among themselves.
-#define PERSIST_MAX_DEVICES 64
-class PersistTurn {
- public:
-  PersistTurn(bool wanted, bool marks, hipStream_t s) : marks_(marks), s_(s) {
-    if (!wanted) return;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    int dev = 0;
-    if (hipStreamIsCapturing(s, &cap) != hipSuccess || hipGetDevice(&dev) != hipSuccess) {
-      (void)hipGetLastError();
-      return;
-    }
-    if (cap != hipStreamCaptureStatusNone || dev >= PERSIST_MAX_DEVICES) return;
-    Slot* slot = slots() + dev;
-    slot->m.lock();
-    // (it orders launches only, so it needs no fence towards the host)
-    if (!slot->ev &&
-        hipEventCreateWithFlags(&slot->ev, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess) {
-      (void)hipGetLastError();
-      slot->ev = nullptr;
-      slot->m.unlock();
-      return;
-    }
-    if (slot->any && hipStreamWaitEvent(s, slot->ev, 0) != hipSuccess) (void)hipGetLastError();
-    slot_ = slot;
-  }
-  ~PersistTurn() { done(); }
-  PersistTurn(const PersistTurn&) = delete;
-  PersistTurn& operator=(const PersistTurn&) = delete;
-  void done() {
-    if (!slot_) return;
-    if (marks_) {
-      if (hipEventRecord(slot_->ev, s_) == hipSuccess) slot_->any = true;
-      else (void)hipGetLastError();
-    }
-    slot_->m.unlock();
-    slot_ = nullptr;
-  }
-
- private:
-  struct Slot {
-    std::mutex m;
-    hipEvent_t ev = nullptr;   // after the last holder's last launch
-    bool any = false;          // recorded
-  };
-  static Slot* slots() {   // (never destroyed: calls may run while the process ends)
-    static Slot* s = new Slot[PERSIST_MAX_DEVICES];
-    return s;
-  }
-  Slot* slot_ = nullptr;
-  bool marks_;
-  hipStream_t s_;
-};
-
 static PersistArgs persist_args(const Layout& lo, const bf16* W, char* ws, int l) {
   PersistArgs pa;
   memset(&pa, 0, sizeof(pa));
   pa.W = W;
   pa.whh0 = lo.Whh[l][0];
   pa.whh1 = lo.Whh[l][1];
-  pa.place = (uint64_t*)(ws + lo.XCH);
-  pa.X = pa.place + PERSIST_PLACE_WORDS;
+  pa.words = (uint64_t*)(ws + lo.XCH);
+  pa.X = pa.words + GROUP_WORDS;
+  pa.state = (float*)(ws + lo.GST);
   pa.status = (int*)(ws + lo.SYNC);
   pa.Tn = lo.T;
   pa.B = lo.B;
@@ -501,8 +433,9 @@ static Persist32Args persist32_args(const Layout& lo, const float* W, char* ws, 
   pa.whh1 = lo.Whh[l][1];
   pa.C = (float*)(ws + lo.C[l]);
   pa.G = (float*)(ws + lo.G[l]);
-  pa.place = (uint64_t*)(ws + lo.XCH);
-  pa.X = pa.place + PERSIST_PLACE_WORDS;
+  pa.words = (uint64_t*)(ws + lo.XCH);
+  pa.X = pa.words + GROUP_WORDS;
+  pa.state = (float*)(ws + lo.GST);
   pa.status = (int*)(ws + lo.SYNC);
   pa.Tn = lo.T;
   pa.B = lo.B;
@@ -554,7 +487,6 @@ static int fwd_impl(const Layout& lo, const float* theta, const T* W, const floa
     BLSTM_LAUNCH("convert_input", convert_input_kernel<T>, dim3(grid), dim3(256), 0, s, x, M, lo.D,
                  lo.Dp0, X0, (const bf16*)W + lo.Wih[0][0], lo.Wih[0][1] - lo.Wih[0][0], 4 * H, WP0);
   }
-  PersistTurn turn(persist && persist_exchanges<T>(H), std::is_same<T, float>::value || H % 64 != 0, s);
   for (int l = 0; l < lo.L; ++l) {
     const T* Xl = l == 0 ? X0 : (const T*)(ws + lo.Y[l - 1]);
     const int Dl = lo.layer_in(l), Dpl = lo.layer_in_pitch(l);
@@ -740,7 +672,6 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
   ColSumJob bias_jobs[MAX_LAYERS];
   int nbias = 0;
   const float* dY = dytop;
-  PersistTurn turn(persist_exchanges<T>(H) && use_persistent<T>(H, lo.T, true, s), !lp || H % 64 != 0, s);
   for (int l = lo.L - 1; l >= 0; --l) {
     const int par = side ? (l & 1) : 0;
     T* DA = (T*)(ws + lo.DA + l * lo.da_bytes);
@@ -796,7 +727,6 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
       }
       step_fused = true;
     }
-    if (l == 0) turn.done();
     if (side) {
       (void)hipEventRecord(side->bptt_done[l], s);
       (void)hipStreamWaitEvent(ss, side->bptt_done[l], 0);
@@ -937,9 +867,7 @@ extern "C" int blstm_recurrence_ok(const blstm_dims* dims, const void* act_ws, h
     return blstm_fail(BLSTM_EHIP, "blstm_recurrence_ok: %s", hipGetErrorString(hipGetLastError()));
   if (gave_up)
     return blstm_fail(BLSTM_EHIP,
-                      "blstm_recurrence_ok: a recurrent exchange wait gave up since the last query (the workgroups "
-                      "of a persistent launch were not all resident; set ADPSGD_BLSTM_COOPERATIVE=1 on a shared "
-                      "device)");
+                      "blstm_recurrence_ok: a recurrent exchange wait gave up since the last query");
   return BLSTM_OK;
 }
 

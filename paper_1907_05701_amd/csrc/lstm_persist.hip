@@ -35,9 +35,9 @@
 // the slot's current contents.  The buffer is cleared once per forward or
 // backward call, and the tag tells a word of the expected step from one of
 // step n - 2 and from one left by either of the two previous launches of the
-// call.  Every member of a group must be resident at once: the launch is
-// plain when the occupancy query shows the whole grid fits on the device,
-// cooperative otherwise (see launch_one).
+// call.  The members of a group start their steps only once all of them run
+// (see group_meet); the launch is plain when the occupancy query shows that the
+// whole grid fits on an idle device, cooperative otherwise (see persist_launch).
 #include <stdlib.h>
 #include <string.h>
 
@@ -50,6 +50,9 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
 #define PU 64                 // hidden units per member
 #define NTH 512               // threads per workgroup (8 waves)
+// the LDS holds one workgroup: the compiler need not save registers for a
+// second (the 32-row forward at B = 512: 373 -> 367 us for two layers)
+#define ONE_PER_CU __attribute__((amdgpu_waves_per_eu(2, 2)))
 #define KH_MAX 8              // forward: 32-deep k-steps per k half at H = 512
 #define STAGE_BYTES (128 * 1024)   // W_hh staging buffer (half of a member's slice)
 // backward: LDS offset of the summed dy (past the two da buffers)
@@ -294,6 +297,40 @@ __device__ __forceinline__ void gx_prologue(const PersistArgs& a, char* lds, int
   __syncthreads();
 }
 
+// The same entries for member columns u0 .. u0 + 63 without the LDS, for a
+// group that runs alone (the same sums, so the same bits).
+template <int RV>
+__device__ __forceinline__ void gx_member(const PersistArgs& a, int d, int u0, int rowbase, int rend) {
+  const int tid = pass_thread<true>(), lane = tid & 63, w = tid >> 6;
+  const int fr = lane & 15, fc = lane >> 4;
+  const int H = a.H, B = a.B, rows = a.Tn * RV;
+  for (int tile = w; tile < (rows + 15) / 16 * 16; tile += 8) {
+    const int m0 = (tile >> 4) * 16, n = (tile & 15) * 16 + fr, un = u0 + (n & 63);
+    const int r = (m0 + fr) % RV;
+    const bool xok = m0 + fr < rows && rowbase + r < rend, wok = un < H;
+    const bf16* xr = a.Xin + (xok ? ((int64_t)((m0 + fr) / RV) * B + rowbase + r) * a.ldx : 0);
+    const bf16* wr = a.Wih + (d ? a.wih_d : 0) + (wok ? ((int64_t)(n >> 6) * H + un) * a.ldw : 0);
+    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int k0 = 0; k0 < a.Kin; k0 += 32) {
+      const int k = k0 + fc * 8;
+      const bf16x8 x = xok && k < a.Kin ? *(const bf16x8*)(xr + k) : Mfma<bf16>::zero();
+      const bf16x8 v = wok && k < a.Kin ? *(const bf16x8*)(wr + k) : Mfma<bf16>::zero();
+      acc = Mfma<bf16>::mma(x, v, acc);
+    }
+    const int64_t gi = (d ? a.b_d : 0) + (int64_t)(n >> 6) * H + min(un, H - 1);
+    float bv = 0.f;
+    bv += a.bih[gi];
+    bv += a.bhh[gi];
+#pragma unroll
+    for (int rr = 0; rr < 4; ++rr) {
+      const int m = m0 + fc * 4 + rr, ro = m % RV;
+      if (m < rows && rowbase + ro < rend && wok)
+        a.Gx[((int64_t)(m / RV) * B + rowbase + ro) * 8 * H + (int64_t)d * 4 * H + (n >> 6) * H + un] = (bf16)(acc[rr] + bv);
+    }
+  }
+  __syncthreads();
+}
+
 // ---------------------------------------------------------------------------
 // Forward.
 //
@@ -304,28 +341,27 @@ __device__ __forceinline__ void gx_prologue(const PersistArgs& a, char* lds, int
 // of k half kh own row tile kh; with fewer, sharing the cells between both
 // halves measured slower (100.7 -> 127 us per 42 steps at RV = 8).
 // ---------------------------------------------------------------------------
-template <int RV>
-__global__ __launch_bounds__(NTH) void lstm_fwd_persist(const PersistArgs a) {
-  extern __shared__ __attribute__((aligned(16))) char lds_raw[];
+//
+// One pass runs steps [tau0, tau1) of member `mem`: all of them with the
+// group's other members beside it (ONE false; returns how the group runs, see
+// group_meet, and does nothing if it does not run together), or one step of
+// one member after the other (ONE, see lstm_fwd_persist), with the member's
+// registers kept in a.state between its steps.
+template <int RV, bool ONE>
+__device__ __forceinline__ int fwd_pass(const PersistArgs& a, char* lds_raw, int g, int mem, int tau0, int tau1) {
   static_assert(RV == 8 || RV == 16 || RV == 32, "rows per workgroup");
   constexpr int NT = RV > 16 ? 2 : 1;   // MFMA row tiles
   constexpr int R = 16 * NT;            // LDS rows of h
   constexpr bool BOTH = RV == 32;       // both k halves' waves own cells
   constexpr int NR = RV == 8 ? 2 : 4;   // cell rows per owner lane
   const int H = a.H, B = a.B, Tn = a.Tn;
-  const int NG = a.NG;
-  const int g = blockIdx.x % NG, mem = blockIdx.x / NG;
-  if (g >= 2 * a.NS) return;   // padding (see persist_groups)
   const int d = g & 1, s = g >> 1;
   const int u0 = mem * PU;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = pass_thread<ONE, (RV < 32)>(), lane = tid & 63, w = tid >> 6;
   const int ub = w & 3, kh = w >> 2;
   const int NM = (H + PU - 1) / PU, HP = NM * PU;   // members; units with the last member's padding
   const int KH = NM;                                // 32-deep k-steps per k half
   const bool owner = BOTH || kh == 0;
-  if (tid == 0) place_announce(a.place, a.seq + 1);
-
-  if (a.Xin) gx_prologue<RV>(a, lds_raw, d, u0, a.b0 + s * RV, a.b0 + a.rows);
 
   // W_hh fragments (B operand): gate q of unit u0 + ub*16 + lane%16, k-step
   // kh*KH + i, k = 8*(lane/16) .. +8 within it.  Staged by direct-to-LDS
@@ -334,7 +370,9 @@ __global__ __launch_bounds__(NTH) void lstm_fwd_persist(const PersistArgs a) {
   // 16-byte chunk c of row lr in slot c ^ (lr & 15) so that the 16 rows of
   // one fragment read fall in distinct bank groups.
   bf16x8 bw[KH_MAX][4];
-  bool local = false;   // the group's members share an XCD (asked for while the staging loads are in flight)
+  int how = GROUP_APART;
+  const bool meets = Tn > 1 && NM > 1;
+  uint64_t word = 0;   // (asked for while the staging loads are in flight)
   {
     char* stg = lds_raw;
     const __amdgpu_buffer_rsrc_t rw = dma_rsrc(a.W + (d ? a.whh1 : a.whh0));
@@ -342,7 +380,7 @@ __global__ __launch_bounds__(NTH) void lstm_fwd_persist(const PersistArgs a) {
     for (int p = 0; p < 2; ++p) {
 #pragma unroll
       for (int q = 0; q < 16; ++q) {
-        const int ins = q * 8 + w;                  // one instruction fills rows 2 ins, 2 ins + 1
+        const int ins = q * 8 + (w & 7);            // one instruction fills rows 2 ins, 2 ins + 1 (w < 8: said for the masks)
         const int lr = ins * 2 + (lane >> 5);
         const int c = (lane & 31) ^ (lr & 15);      // chunk held by this lane's slot
         const int un = u0 + ((lr >> 4) & 3) * 16 + (lr & 15), k = p * (HP / 2) + c * 8;
@@ -350,9 +388,9 @@ __global__ __launch_bounds__(NTH) void lstm_fwd_persist(const PersistArgs a) {
         const bool ok = c * 8 < HP / 2 && k < H && un < H;
         dma16(rw, ok ? (uint32_t)((grow * H + k) * 2) : DMA_OFF_NONE, stg + ins * 1024);
       }
-      if (p == 0) local = place_local(a.place, a.seq + 1, g, NG, NM, a.status);
       dma_wait_all();
       __syncthreads();
+      if (!ONE && p == 1 && meets) word = group_word(a.words, a.seq, g);
       if (kh == p) {
 #pragma unroll
         for (int i = 0; i < KH_MAX; ++i)
@@ -418,13 +456,16 @@ __global__ __launch_bounds__(NTH) void lstm_fwd_persist(const PersistArgs a) {
     return RV == 8 ? ((lane >> 4) & 1) * 4 + (lane >> 5) * 2 + r : (BOTH ? kh * 16 : 0) + (lane >> 4) * 4 + r;
   };
 
+  if (!ONE && meets) how = group_meet(word, a.words, a.seq, g, mem, NM, a.wait);
+  if (!ONE && how >= GROUP_ALONE) return how;
+  const bool local = how == GROUP_LOCAL;
   float creg[NR];
 #pragma unroll
-  for (int r = 0; r < NR; ++r) creg[r] = 0.f;
+  for (int r = 0; r < NR; ++r) creg[r] = ONE && tau0 > 0 ? group_state(a.state, g, mem, NM)[r] : 0.f;
 
   // input projection of a step (independent of h), loaded one step ahead so
   // that its latency hides behind the previous step's exchange
-  bf16 gx[NR][4], gxn[NR][4];
+  bf16 gxn[NR][4];
   auto load_gx = [&](int tt) {
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
@@ -435,18 +476,12 @@ __global__ __launch_bounds__(NTH) void lstm_fwd_persist(const PersistArgs a) {
       for (int q = 0; q < 4; ++q) gxn[r][q] = p[q * H];
     }
   };
-  if (owner) load_gx(d ? Tn - 1 : 0);
+  if (owner) load_gx(d ? Tn - 1 - tau0 : tau0);
 
   constexpr int NGT = NTH;   // gathering threads
   constexpr int WPT = (RV * 128 + NGT - 1) / NGT;     // gathered words per thread (at H = 512)
-  for (int tau = 0; tau < Tn; ++tau) {
+  for (int tau = tau0; tau < tau1; ++tau) {
     const int t = d ? Tn - 1 - tau : tau;
-    if (owner) {
-#pragma unroll
-      for (int r = 0; r < NR; ++r)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) gx[r][q] = gxn[r][q];
-    }
 
     f32x4 acc[NT][4];
 #pragma unroll
@@ -517,7 +552,7 @@ __global__ __launch_bounds__(NTH) void lstm_fwd_persist(const PersistArgs a) {
 #pragma unroll
       for (int r = 0; r < NR; ++r) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) gv[r][q] = pre[q][r] + (float)gx[r][q];
+        for (int q = 0; q < 4; ++q) gv[r][q] = pre[q][r] + (float)gxn[r][q];
         const float ig = sigmoidf_(gv[r][0]), fg = sigmoidf_(gv[r][1]);
         const float gg = tanhf_(gv[r][2]), og = sigmoidf_(gv[r][3]);
         const float c = fg * creg[r] + ig * gg;
@@ -554,13 +589,51 @@ __global__ __launch_bounds__(NTH) void lstm_fwd_persist(const PersistArgs a) {
         for (int q = 0; q < 4; ++q) g4[q] = (bf16)gv[r][q];
         *(bf16x4*)&sG[(rl * PU + ul) * 4] = g4;
       }
-      if (tau + 1 < Tn) load_gx(d ? Tn - 2 - tau : tau + 1);
+      if (tau + 1 < tau1) load_gx(d ? Tn - 2 - tau : tau + 1);
     }
     // the step's saved activations by the whole workgroup (the next step's
     // gather barrier comes before this buffer is rewritten)
     lds_barrier();
     store_step(t, tau & 1, 0, NTH);
   }
+  if constexpr (ONE) {
+#pragma unroll
+    for (int r = 0; r < NR; ++r) group_state(a.state, g, mem, NM)[r] = creg[r];
+    __syncthreads();   // the next pass reuses the LDS
+  }
+  return how;
+}
+
+// A group that runs on this workgroup alone: every member's input projection,
+// then every member's part of each step.
+template <int RV>
+__device__ __attribute__((noinline)) void fwd_alone(const PersistArgs* at, lds_base_t lds, int gv, int memv) {
+  char* lds_raw = (char*)lds;
+  const int g = scalar(gv), mem = scalar(memv);
+  const PersistArgs a = pass_args(at);
+  const int NM = (a.H + PU - 1) / PU;
+  if (a.Xin)
+#pragma nounroll
+    for (int m = 0; m < NM; ++m)
+      if (m != mem) gx_member<RV>(pass_args(at), g & 1, m * PU, a.b0 + (g >> 1) * RV, a.b0 + a.rows);
+#pragma nounroll
+  for (int tau = 0; tau < a.Tn; ++tau)
+#pragma nounroll
+    for (int m = 0; m < NM; ++m) fwd_pass<RV, true>(pass_args(at), lds_raw, g, m, tau, tau + 1);
+}
+
+template <int RV>
+__global__ __launch_bounds__(NTH) ONE_PER_CU void lstm_fwd_persist(const PersistArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char lds_raw[];
+  const int NM = (a.H + PU - 1) / PU;
+  int g, mem;
+  group_of(a.NG, NM, &g, &mem);
+  if (g >= 2 * a.NS) return;   // padding (see persist_groups)
+  if (a.Tn > 1 && NM > 1) group_arrive(a.words, a.seq, g, mem, a.wait);
+  if (a.Xin) gx_prologue<RV>(a, lds_raw, g & 1, mem * PU, a.b0 + (g >> 1) * RV, a.b0 + a.rows);
+  if (fwd_pass<RV, false>(a, lds_raw, g, mem, 0, a.Tn) != GROUP_ALONE) return;
+  if (threadIdx.x == 0) a.status[1] = 1;
+  fwd_alone<RV>(kernel_args<PersistArgs>(), (lds_base_t)lds_raw, g, mem);
 }
 
 // ---------------------------------------------------------------------------
@@ -589,9 +662,10 @@ __global__ __launch_bounds__(NTH) void lstm_fwd_persist(const PersistArgs a) {
 // kernels, which ran these widths before at 6.1 / 11.9 us a step for H = 96 /
 // 480, B = 128, T = 21; now 2.2 / 4.1, and the forward 5.3 / 7.4 -> 1.9 / 2.8).
 // ---------------------------------------------------------------------------
-template <int RV, bool F32X>
-__global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
-  extern __shared__ __attribute__((aligned(16))) char lds_raw[];
+//
+// Passes as in the forward.
+template <int RV, bool F32X, bool ONE>
+__device__ __forceinline__ int bwd_pass(const PersistArgs& a, char* lds_raw, int g, int mem, int tau0, int tau1) {
   static_assert(RV == 8 || RV == 16 || RV == 32, "rows per workgroup");
   constexpr int NT = RV > 16 ? 2 : 1;   // MFMA row tiles
   constexpr int R = 16 * NT;            // LDS rows of da
@@ -599,14 +673,11 @@ __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
   constexpr int RPT = 4 / LPI;          // cell rows per lane
   constexpr int MPL = 8 / LPI;          // members' words per lane (at most)
   const int H = a.H, B = a.B, Tn = a.Tn;
-  const int NM = (H + PU - 1) / PU, NG = a.NG;
-  const int g = blockIdx.x % NG, mem = blockIdx.x / NG;
-  if (g >= 2 * a.NS) return;   // padding (see persist_groups)
+  const int NM = (H + PU - 1) / PU;
   const int d = g & 1, s = g >> 1;
   const int u0 = mem * PU;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = pass_thread<ONE>(), lane = tid & 63, w = tid >> 6;
   const int NB = H / 16;                // unit blocks of the partial product
-  if (tid == 0) place_announce(a.place, a.seq + 1);
 
   // W_hh of the 256 own gate rows as the B operand: k = own row kk (gate
   // (kk>>4)&3, unit u0 + (kk>>6)*16 + (kk&15)), n = unit.  Wave w holds the
@@ -620,7 +691,9 @@ __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
   // MFMA B operand).  The swizzle spreads the 16 rows of one read over
   // distinct chunk pairs.
   bf16x8 bw[8][4];
-  bool local = false;
+  int how = GROUP_APART;
+  const bool meets = Tn > 1 && NM > 1;
+  uint64_t word = 0;
   {
     auto wswz = [](int k) { return 2 * ((k & 3) | (((k >> 3) & 1) << 2)); };
     char* stg = lds_raw;
@@ -637,9 +710,9 @@ __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
         const int64_t grow = (int64_t)((kk >> 4) & 3) * H + un;
         dma16(rw, c * 8 < H && un < H ? (uint32_t)((grow * H + c * 8) * 2) : DMA_OFF_NONE, stg + kl * 1024);
       }
-      if (p == 0) local = place_local(a.place, a.seq + 1, g, NG, NM, a.status);
       dma_wait_all();
       __syncthreads();
+      if (!ONE && p == 1 && meets) word = group_word(a.words, a.seq, g);
 #pragma unroll
       for (int ksl = 0; ksl < 4; ++ksl)
 #pragma unroll
@@ -678,11 +751,14 @@ __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
   // this lane's item: unit cu of row quad qd, rows rl0 .. rl0 + RPT - 1
   const int sub = tid % LPI, item = tid / LPI;
   const int cu = item & 63, qd = item >> 6, rl0 = qd * 4 + sub * RPT;
+  if (!ONE && meets) how = group_meet(word, a.words, a.seq, g, mem, NM, a.wait);
+  if (!ONE && how >= GROUP_ALONE) return how;
+  const bool local = how == GROUP_LOCAL;
   float dcreg[RPT], dbacc[4];
 #pragma unroll
-  for (int i = 0; i < RPT; ++i) dcreg[i] = 0.f;
+  for (int i = 0; i < RPT; ++i) dcreg[i] = ONE && tau0 > 0 ? group_state(a.state, g, mem, NM)[4 + i] : 0.f;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) dbacc[q] = 0.f;
+  for (int q = 0; q < 4; ++q) dbacc[q] = ONE && tau0 > 0 ? group_state(a.state, g, mem, NM)[q] : 0.f;
 
   // everything the cell derivative needs besides dh_rec: dy, the gate
   // pre-activations and c at t, c at the step's predecessor in forward time
@@ -754,11 +830,11 @@ __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
     }
   };
   {
-    const float* ct = a.C + (d ? 0 : Tn - 1) * fc;
+    const float* ct = a.C + (d ? tau0 : Tn - 1 - tau0) * fc;
 #pragma unroll
     for (int i = 0; i < RPT; ++i) cc[i] = ct[oc[i]];
   }
-  fetch(0);
+  fetch(tau0);
 
   const int m0 = sub * MPL, mcount = max(0, min(NM, m0 + MPL) - m0);
   const uint32_t ogath =
@@ -779,7 +855,7 @@ __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
     oda[c0] = (uint32_t)((rowbase + r) * 8 * H + d * 4 * H + ((kk >> 4) & 3) * H + u0 + (kk >> 6) * 16 + (kk & 15));
   }
 
-  for (int tau = 0; tau < Tn; ++tau) {
+  for (int tau = tau0; tau < tau1; ++tau) {
     const int t = d ? tau : Tn - 1 - tau;
     bf16* al = al0 + (tau & 1) * ALS;
     // the step's gate activations from the prefetched pre-activations,
@@ -876,7 +952,7 @@ __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
       }
       cc[i] = cp[i];   // c at the next step's t
     }
-    if (tau + 1 < Tn) fetch(tau + 1);
+    if (tau + 1 < tau1) fetch(tau + 1);
     lds_barrier();
 
     // P = da_own [RV x 256] * W_own [256 x H]; unit blocks w + 8j of this
@@ -935,7 +1011,13 @@ __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
       }
     }
   }
-  if (a.DBP) {
+  if constexpr (ONE) {
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) group_state(a.state, g, mem, NM)[4 + i] = dcreg[i];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) group_state(a.state, g, mem, NM)[q] = dbacc[q];
+  }
+  if (a.DBP && tau1 == Tn) {
     // bias partials: every lane's sum over its rows and steps, added over
     // the slice's row groups in order
     float* red = (float*)lds_raw;   // [RV / RPT][64 units][4 gates]
@@ -950,6 +1032,33 @@ __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
       a.DBP[(int64_t)(rowbase / RV) * 8 * H + (int64_t)d * 4 * H + (int64_t)(tid & 3) * H + u0 + (tid >> 2)] = sum;
     }
   }
+  if constexpr (ONE) __syncthreads();   // the next pass reuses the LDS
+  return how;
+}
+
+template <int RV, bool F32X>
+__device__ __attribute__((noinline)) void bwd_alone(const PersistArgs* at, lds_base_t lds, int gv) {
+  char* lds_raw = (char*)lds;
+  const int g = scalar(gv);
+  const PersistArgs a = pass_args(at);
+  const int NM = (a.H + PU - 1) / PU;
+#pragma nounroll
+  for (int tau = 0; tau < a.Tn; ++tau)
+#pragma nounroll
+    for (int m = 0; m < NM; ++m) bwd_pass<RV, F32X, true>(pass_args(at), lds_raw, g, m, tau, tau + 1);
+}
+
+template <int RV, bool F32X>
+__global__ __launch_bounds__(NTH) ONE_PER_CU void lstm_bwd_persist(const PersistArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char lds_raw[];
+  const int NM = (a.H + PU - 1) / PU;
+  int g, mem;
+  group_of(a.NG, NM, &g, &mem);
+  if (g >= 2 * a.NS) return;   // padding (see persist_groups)
+  if (a.Tn > 1 && NM > 1) group_arrive(a.words, a.seq, g, mem, a.wait);
+  if (bwd_pass<RV, F32X, false>(a, lds_raw, g, mem, 0, a.Tn) != GROUP_ALONE) return;
+  if (threadIdx.x == 0) a.status[1] = 1;
+  bwd_alone<RV, F32X>(kernel_args<PersistArgs>(), (lds_base_t)lds_raw, g);
 }
 
 // The recurrence status block (at the end of the activation workspace): an
@@ -963,7 +1072,7 @@ __global__ __launch_bounds__(NTH) void lstm_bwd_persist(const PersistArgs a) {
 __device__ __forceinline__ void status_init_if_fresh(int* status) {
   uint64_t* tag = (uint64_t*)(status + 2);
   if (*tag != STATUS_TAG) {
-    *status = 0;
+    status[0] = status[1] = 0;
     *tag = STATUS_TAG;
   }
 }
@@ -977,7 +1086,7 @@ __global__ __launch_bounds__(256) void clear_exchange_kernel(uint4* p, int64_t n
 }
 
 __global__ void status_reset_kernel(int* status) {
-  *status = 0;
+  status[0] = status[1] = 0;
   *(uint64_t*)(status + 2) = STATUS_TAG;
 }
 
@@ -1009,16 +1118,13 @@ bool persist_supported(int H, int T) {
   return H % 32 == 0 && H >= 32 && H <= 512;
 }
 
-// Launch mode.  Every workgroup of a launch waits for the others, so all
-// must be resident at once.  A cooperative launch guarantees that, at a
-// measured cost of about 15 us per launch on MI355X (12 launches per learner
-// step).  A plain launch is used instead when the occupancy query shows that
-// the whole grid fits on the device at once (one workgroup per CU here):
-// the stream's previous kernel has completed, so every CU is free unless
-// other streams or processes occupy some.  In that case the waits give up
-// after their bound, the kernel still ends, and the status flag (see
-// blstm_recurrence_ok) reports it.  ADPSGD_BLSTM_COOPERATIVE=1 forces
-// cooperative launches (for devices shared with other work).
+// Launch mode.  A cooperative launch has all its workgroups resident at once,
+// at a measured cost of about 15 us per launch on MI355X (12 launches per
+// learner step).  A plain launch is used instead when the occupancy query shows
+// that the whole grid fits on the device at once (one workgroup per CU here):
+// its groups all run together unless other launches hold CUs, and a group that
+// does not get all of its own in time is done by one workgroup (group_meet).
+// ADPSGD_BLSTM_COOPERATIVE=1 forces cooperative launches, for comparisons.
 static bool force_cooperative() {
   const char* e = getenv("ADPSGD_BLSTM_COOPERATIVE");
   return e && e[0] == '1';
@@ -1066,6 +1172,11 @@ hipError_t persist_launch(const char* name, const void* fn, dim3 grid, int threa
   }
   if (slot >= 0) timing_post(slot, s);
   return e;
+}
+
+uint32_t persist_group_wait() {
+  const char* e = getenv("ADPSGD_BLSTM_GROUP_WAIT_US");
+  return 100u * (uint32_t)(e ? std::min(std::max(atoi(e), 0), 1000000) : 1000);
 }
 
 int persist_groups(int groups, int members) {
@@ -1128,8 +1239,8 @@ hipError_t persist_clear(bool backward, const PersistArgs& a, hipStream_t s) {
   // both exchange slots start without any valid tag; the forward's clear
   // also initialises the status block of a fresh workspace
   const int64_t part = (int64_t)((chunk + 3) / 4) * members(a.H) * a.H * (a.H % PU ? 4 : 1);
-  const int64_t words = PERSIST_PLACE_WORDS + 2 * 2 * (backward ? part : (int64_t)chunk * (a.H / 4));
-  return persist_clear_words(a.place, words / 2, backward ? nullptr : a.status, s);
+  const int64_t words = GROUP_WORDS + 2 * 2 * (backward ? part : (int64_t)chunk * (a.H / 4));
+  return persist_clear_words(a.words, words / 2, backward ? nullptr : a.status, s);
 }
 
 hipError_t persist_clear_words(void* p, int64_t n16, int* status, hipStream_t s) {
@@ -1148,6 +1259,7 @@ hipError_t persist_status_reset(int* status, hipStream_t s) {
 hipError_t persist_layer(bool backward, PersistArgs a, hipStream_t s) {
   int RV, chunk;
   if (!persist_plan(a.H, a.B, &RV, &chunk)) return hipErrorInvalidValue;
+  const uint32_t wait = persist_group_wait();
   for (int b0 = 0; b0 < a.B; b0 += chunk) {
     PersistArgs c = a;
     c.b0 = b0;
@@ -1157,6 +1269,7 @@ hipError_t persist_layer(bool backward, PersistArgs a, hipStream_t s) {
     // the launch's position in the call (the caller's tag numbers the layers
     // in the order the call runs them)
     c.seq = a.tag * (uint32_t)cdiv(a.B, chunk) + (uint32_t)(b0 / chunk);
+    c.wait = wait;
     const hipError_t e = RV == 8    ? (backward ? launch_one<8, true>(c, s) : launch_one<8, false>(c, s))
                          : RV == 16 ? (backward ? launch_one<16, true>(c, s) : launch_one<16, false>(c, s))
                                     : (backward ? launch_one<32, true>(c, s) : launch_one<32, false>(c, s));

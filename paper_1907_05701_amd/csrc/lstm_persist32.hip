@@ -76,24 +76,22 @@ __host__ __device__ static inline int p32_pitch(int n) { return (n + 63) / 64 * 
 // ---------------------------------------------------------------------------
 // Forward.
 // ---------------------------------------------------------------------------
-// SOLO: one member (no exchange; h stays in LDS).
-template <int NCB, int RT, bool SOLO>
-__global__ __launch_bounds__(P32_THREADS) void lstm_fwd_persist32(const Persist32Args a) {
-  extern __shared__ __attribute__((aligned(16))) char lds_raw[];
+// SOLO: one member (no exchange; h stays in LDS).  One pass runs steps
+// [tau0, tau1) of member `mem`, with the group's other members beside it or
+// (ONE) one step of one member after the other, as in the bf16 kernels.
+template <int NCB, int RT, bool SOLO, bool ONE>
+__device__ __forceinline__ int fwd32_pass(const Persist32Args& a, char* lds_raw, int g, int mem, int nmem, int tau0,
+                                          int tau1) {
   constexpr int PU = 16 * NCB, KS = 8 / NCB, RV = 4 * RT, NCOL = 64 * NCB;
   constexpr int IT = RV * NCOL / P32_THREADS;   // gate values per thread
   constexpr int RPI = P32_THREADS / NCOL;       // rows between a thread's items
   const int H = a.H, B = a.B, Tn = a.Tn;
-  const int NG = a.NG;
-  const int g = blockIdx.x % NG, mem = blockIdx.x / NG;
-  if (g >= 2 * a.NS) return;   // padding (see persist_groups)
   const int d = g & 1, s = g >> 1;
   const int u0 = mem * PU;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = pass_thread<ONE, false>(), lane = tid & 63, w = tid >> 6;
   const int cb = w % NCB, ks = w / NCB;
   const int KQ = (H + 16 * KS - 1) / (16 * KS) * 16;   // k values per part (whole groups of 16)
   const int k0 = ks * KQ;
-  if (!SOLO && tid == 0) place_announce(a.place, a.tag0 + 1);
 
   // W_hh rows of this lane's gate column, k0 .. k0 + KQ (zeros past H), through
   // a wave's own piece of LDS so that the global loads take whole lines (8
@@ -148,15 +146,18 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_fwd_persist32(const Persist3
     }
   };
 #pragma unroll
-  for (int i = 0; i < IT; ++i) creg[i] = 0.f;
-  load_gx(d ? Tn - 1 : 0);
-  const bool local = !SOLO && place_local(a.place, a.tag0 + 1, g, NG, gridDim.x / NG, a.status);
+  for (int i = 0; i < IT; ++i) creg[i] = ONE && tau0 > 0 ? group_state(a.state, g, mem, nmem)[i] : 0.f;
+  load_gx(d ? Tn - 1 - tau0 : tau0);
+  int how = GROUP_APART;
+  if (!SOLO && !ONE && Tn > 1) {
+    how = group_meet(group_word(a.words, a.seq, g), a.words, a.seq, g, mem, nmem, a.wait);
+    if (how >= GROUP_ALONE) return how;
+  }
+  const bool local = how == GROUP_LOCAL;
 
-  for (int tau = 0; tau < Tn; ++tau) {
+  for (int tau = tau0; tau < tau1; ++tau) {
     const int t = d ? Tn - 1 - tau : tau;
-    float pre[IT];
-#pragma unroll
-    for (int i = 0; i < IT; ++i) pre[i] = gxn[i];
+    float sum[IT];
     if (tau > 0) {
       if constexpr (!SOLO) {
         // h of the previous step: the slice's RV rows x H words are
@@ -200,12 +201,14 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_fwd_persist32(const Persist3
       lds_barrier();
 #pragma unroll
       for (int i = 0; i < IT; ++i) {
-        float sum = red[(r0 + RPI * i) * NCOL + col];
+        sum[i] = red[(r0 + RPI * i) * NCOL + col];
 #pragma unroll
-        for (int p = 1; p < KS; ++p) sum += red[(p * RV + r0 + RPI * i) * NCOL + col];
-        pre[i] += sum;
+        for (int p = 1; p < KS; ++p) sum[i] += red[(p * RV + r0 + RPI * i) * NCOL + col];
       }
     }
+    float pre[IT];   // (the projection not before here: waiting for it at the step's start waits for the last stores too)
+#pragma unroll
+    for (int i = 0; i < IT; ++i) pre[i] = tau > 0 ? gxn[i] + sum[i] : gxn[i];
     uint64_t* xo = a.X + (tau & 1) * slot_stride;
     float hv[IT];
 #pragma unroll
@@ -231,7 +234,7 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_fwd_persist32(const Persist3
       }
     }
     // the prefetch before the stores: its wait then leaves them in flight
-    if (tau + 1 < Tn) load_gx(d ? Tn - 2 - tau : tau + 1);
+    if (tau + 1 < tau1) load_gx(d ? Tn - 2 - tau : tau + 1);
 #pragma unroll
     for (int i = 0; i < IT; ++i) {
       const int row = rowbase + r0 + RPI * i;
@@ -241,6 +244,40 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_fwd_persist32(const Persist3
       if (q == 1 || q == 2) (q == 1 ? a.C : a.Y)[f * 2 * H + (int64_t)d * H + unit] = q == 1 ? creg[i] : hv[i];
     }
   }
+  if constexpr (ONE) {
+#pragma unroll
+    for (int i = 0; i < IT; ++i) group_state(a.state, g, mem, nmem)[i] = creg[i];
+    __syncthreads();   // the next pass reuses the LDS
+  }
+  return how;
+}
+
+// A group that runs on this workgroup alone.
+template <int NCB, int RT>
+__device__ __attribute__((noinline)) void fwd32_alone(const Persist32Args* at, lds_base_t lds, int gv, int nmemv) {
+  const int g = scalar(gv), nmem = scalar(nmemv), Tn = pass_args(at).Tn;
+#pragma nounroll
+  for (int tau = 0; tau < Tn; ++tau)
+#pragma nounroll
+    for (int m = 0; m < nmem; ++m)
+      fwd32_pass<NCB, RT, false, true>(pass_args(at), (char*)lds, g, m, nmem, tau, tau + 1);
+}
+
+template <int NCB, int RT, bool SOLO>
+__global__ __launch_bounds__(P32_THREADS) void lstm_fwd_persist32(const Persist32Args a) {
+  extern __shared__ __attribute__((aligned(16))) char lds_raw[];
+  if constexpr (SOLO) {
+    fwd32_pass<NCB, RT, true, false>(a, lds_raw, blockIdx.x, 0, 1, 0, a.Tn);
+  } else {
+    const int nmem = gridDim.x / a.NG;
+    int g, mem;
+    group_of(a.NG, nmem, &g, &mem);
+    if (g >= 2 * a.NS) return;   // padding (see persist_groups)
+    if (a.Tn > 1) group_arrive(a.words, a.seq, g, mem, a.wait);
+    if (fwd32_pass<NCB, RT, false, false>(a, lds_raw, g, mem, nmem, 0, a.Tn) != GROUP_ALONE) return;
+    if (threadIdx.x == 0) a.status[1] = 1;
+    fwd32_alone<NCB, RT>(kernel_args<Persist32Args>(), (lds_base_t)lds_raw, g, nmem);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -248,9 +285,9 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_fwd_persist32(const Persist3
 // ---------------------------------------------------------------------------
 // KS: k parts of the own gate rows; SOLO: one member (the partial sums stay
 // in LDS).
-template <int NCB, int RT, int KS, bool SOLO>
-__global__ __launch_bounds__(P32_THREADS) void lstm_bwd_persist32(const Persist32Args a) {
-  extern __shared__ __attribute__((aligned(16))) char lds_raw[];
+template <int NCB, int RT, int KS, bool SOLO, bool ONE>
+__device__ __forceinline__ int bwd32_pass(const Persist32Args& a, char* lds_raw, int g, int mem, int nmem, int tau0,
+                                          int tau1) {
   constexpr int PU = 16 * NCB, RV = 4 * RT, NCOL = 64 * NCB;   // NCOL own gate rows
   constexpr int CBS = 8 / KS, KW = NCOL / KS;                  // unit blocks of 64; own rows per k part
   static_assert(KW <= P32_KW && KW % 16 == 0, "W_hh slice in registers");
@@ -259,16 +296,12 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_bwd_persist32(const Persist3
   constexpr int MPP = (MEMS * KS + 3) / 4;                     // partial sums per thread of a quad
   constexpr int AS = (NCOL + 63) / 64 * 64 + 16;
   const int H = a.H, B = a.B, Tn = a.Tn;
-  const int NG = a.NG;
-  const int g = blockIdx.x % NG, mem = blockIdx.x / NG, nmem = gridDim.x / NG;
-  if (g >= 2 * a.NS) return;   // padding (see persist_groups)
   const int d = g & 1, s = g >> 1;
   const int u0 = mem * PU;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = pass_thread<ONE, false>(), lane = tid & 63, w = tid >> 6;
   const int cb = w % CBS, ks = w / CBS;
   const int hu = cb * 64 + lane;   // hidden unit of this lane's product column
   const int parts = nmem * KS;
-  if (!SOLO && tid == 0) place_announce(a.place, a.tag0 + 1);
 
   // W_hh[own gate row][hu], own row 4 (unit - u0) + gate, the KW rows of part ks
   float bw[KW];
@@ -307,13 +340,19 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_bwd_persist32(const Persist3
   };
 #pragma unroll
   for (int i = 0; i < IT; ++i) {
-    dcreg[i] = dbacc[i] = 0.f;
-    cc[i] = a.C[((int64_t)(d ? 0 : Tn - 1) * B + rowc(i)) * 2 * H + (int64_t)d * H + unitc];
+    dcreg[i] = ONE && tau0 > 0 ? group_state(a.state, g, mem, nmem)[4 + i] : 0.f;
+    dbacc[i] = ONE && tau0 > 0 ? group_state(a.state, g, mem, nmem)[i] : 0.f;
+    cc[i] = a.C[((int64_t)(d ? tau0 : Tn - 1 - tau0) * B + rowc(i)) * 2 * H + (int64_t)d * H + unitc];
   }
-  fetch(0);
-  const bool local = !SOLO && place_local(a.place, a.tag0 + 1, g, NG, nmem, a.status);
+  fetch(tau0);
+  int how = GROUP_APART;
+  if (!SOLO && !ONE && Tn > 1) {
+    how = group_meet(group_word(a.words, a.seq, g), a.words, a.seq, g, mem, nmem, a.wait);
+    if (how >= GROUP_ALONE) return how;
+  }
+  const bool local = how == GROUP_LOCAL;
 
-  for (int tau = 0; tau < Tn; ++tau) {
+  for (int tau = tau0; tau < tau1; ++tau) {
     const int t = d ? tau : Tn - 1 - tau;
     float* alp = al + (tau & 1) * RV * AS;
     // the gathered dh_rec of each item: the quad's threads take MPP parts
@@ -401,7 +440,7 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_bwd_persist32(const Persist3
           for (int r = 0; r < 4; ++r)
             if (CBS * 64 <= PU || hu < PU) dhl[(ks * RV + rt * 4 + r) * PU + hu] = acc[rt][r];
       }
-      fetch(tau + 1);
+      if (tau + 1 < tau1) fetch(tau + 1);
     }
 #pragma unroll
     for (int i = 0; i < IT; ++i) {
@@ -410,6 +449,15 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_bwd_persist32(const Persist3
         a.DA[((int64_t)t * B + row) * 8 * H + (int64_t)d * 4 * H + (int64_t)q * H + unit] = da[i];
     }
     if constexpr (SOLO) lds_barrier();   // the partial sums in LDS
+  }
+  if constexpr (ONE) {
+#pragma unroll
+    for (int i = 0; i < IT; ++i) {
+      group_state(a.state, g, mem, nmem)[4 + i] = dcreg[i];
+      group_state(a.state, g, mem, nmem)[i] = dbacc[i];
+    }
+    __syncthreads();   // the next pass reuses the LDS
+    if (tau1 < Tn) return how;
   }
   // bias partials: the slice's rows in order
   __syncthreads();
@@ -421,6 +469,35 @@ __global__ __launch_bounds__(P32_THREADS) void lstm_bwd_persist32(const Persist3
 #pragma unroll
     for (int r = 0; r < RV; ++r) sum += al[r * AS + tid];
     a.DBP[(int64_t)(rowbase / RV) * 8 * H + (int64_t)d * 4 * H + (int64_t)q * H + unit] = sum;
+  }
+  if constexpr (ONE) __syncthreads();
+  return how;
+}
+
+template <int NCB, int RT, int KS>
+__device__ __attribute__((noinline)) void bwd32_alone(const Persist32Args* at, lds_base_t lds, int gv, int nmemv) {
+  const int g = scalar(gv), nmem = scalar(nmemv), Tn = pass_args(at).Tn;
+#pragma nounroll
+  for (int tau = 0; tau < Tn; ++tau)
+#pragma nounroll
+    for (int m = 0; m < nmem; ++m)
+      bwd32_pass<NCB, RT, KS, false, true>(pass_args(at), (char*)lds, g, m, nmem, tau, tau + 1);
+}
+
+template <int NCB, int RT, int KS, bool SOLO>
+__global__ __launch_bounds__(P32_THREADS) void lstm_bwd_persist32(const Persist32Args a) {
+  extern __shared__ __attribute__((aligned(16))) char lds_raw[];
+  if constexpr (SOLO) {
+    bwd32_pass<NCB, RT, KS, true, false>(a, lds_raw, blockIdx.x, 0, 1, 0, a.Tn);
+  } else {
+    const int nmem = gridDim.x / a.NG;
+    int g, mem;
+    group_of(a.NG, nmem, &g, &mem);
+    if (g >= 2 * a.NS) return;   // padding (see persist_groups)
+    if (a.Tn > 1) group_arrive(a.words, a.seq, g, mem, a.wait);
+    if (bwd32_pass<NCB, RT, KS, false, false>(a, lds_raw, g, mem, nmem, 0, a.Tn) != GROUP_ALONE) return;
+    if (threadIdx.x == 0) a.status[1] = 1;
+    bwd32_alone<NCB, RT, KS>(kernel_args<Persist32Args>(), (lds_base_t)lds_raw, g, nmem);
   }
 }
 
@@ -468,7 +545,13 @@ size_t persist32_xch_bytes(int B, int H) {
   const int ncb = H <= 256 ? 4 : 2;
   const int64_t members = cdiv(H, 16 * ncb);
   const int64_t rows = std::min<int64_t>(B, 256 / (2 * members) * (ncb == 2 ? 16 : 8));
-  return (size_t)2 * 2 * members * (ncb / 2) * rows * H * 8 + PERSIST_PLACE_WORDS * 8;
+  return (size_t)2 * 2 * members * (ncb / 2) * rows * H * 8 + GROUP_WORDS * 8;
+}
+
+size_t persist32_state_bytes(int B, int H) {
+  if (!persist32_supported(H) || H <= 128) return 0;
+  const int64_t members = cdiv(H, H <= 256 ? 64 : 32);
+  return (size_t)(2 * std::min<int64_t>(cdiv(B, 4), 256 / (2 * members)) * members) * P32_THREADS * GROUP_STATE * 4;
 }
 
 hipError_t persist32_clear(bool backward, const Persist32Args& a, hipStream_t s) {
@@ -476,9 +559,9 @@ hipError_t persist32_clear(bool backward, const Persist32Args& a, hipStream_t s)
   if (!plan32(a.H, a.B, &p)) return hipErrorInvalidValue;
   int64_t words = 0;   // one member exchanges nothing
   if (p.members > 1)
-    words = PERSIST_PLACE_WORDS + (int64_t)2 * 2 * (backward ? p.members * p.bks : 1) * p.chunk * a.H;
+    words = GROUP_WORDS + (int64_t)2 * 2 * (backward ? p.members * p.bks : 1) * p.chunk * a.H;
   if (backward && words == 0) return hipSuccess;
-  return persist_clear_words(a.place, words / 2, backward ? nullptr : a.status, s);
+  return persist_clear_words(a.words, words / 2, backward ? nullptr : a.status, s);
 }
 
 template <int NCB, int RT, int BKS, bool SOLO>
@@ -510,6 +593,7 @@ hipError_t persist32_layer(bool backward, Persist32Args a, hipStream_t s) {
   size_t lds = backward ? ((size_t)2 * RV * (ncol + 16) + (size_t)p.bks * RV * 16 * p.ncb) * 4
                         : ((size_t)RV * p32_pitch(a.H) + (size_t)8 / p.ncb * RV * ncol) * 4;
   if (!backward) lds = std::max(lds, (size_t)8 * 64 * 36 * 4);   // W_hh staging
+  const uint32_t wait = persist_group_wait();
   for (int b0 = 0; b0 < a.B; b0 += p.chunk) {
     Persist32Args c = a;
     c.b0 = b0;
@@ -518,7 +602,9 @@ hipError_t persist32_layer(bool backward, Persist32Args a, hipStream_t s) {
     c.NG = solo ? 2 * c.NS : persist_groups(2 * c.NS, p.members);
     // tags of one call's launches never meet: the launch's position times T,
     // plus the step (1 .. T); T B <= 2^24 keeps the product below 2^32
-    c.tag0 = (a.tag0 * (uint32_t)cdiv(a.B, p.chunk) + (uint32_t)(b0 / p.chunk)) * (uint32_t)a.Tn;
+    c.seq = a.tag0 * (uint32_t)cdiv(a.B, p.chunk) + (uint32_t)(b0 / p.chunk);
+    c.tag0 = c.seq * (uint32_t)a.Tn;
+    c.wait = wait;
     const hipError_t e = persist_launch(backward ? "lstm_rec_bwd_persist32" : "lstm_rec_fwd_persist32", fn,
                                         dim3(c.NG * p.members), P32_THREADS, lds, &c, s);
     if (e != hipSuccess) return e;
