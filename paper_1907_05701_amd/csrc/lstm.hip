@@ -504,8 +504,12 @@ static int fwd_impl(const Layout& lo, const float* theta, const T* W, const floa
     const int64_t ldw = (l == 0 && WP0) ? Dpl : Dl;
     const int64_t wih_d = (l == 0 && WP0) ? (int64_t)4 * H * Dpl : lo.Wih[l][1] - lo.Wih[l][0];
     const int kin = (l == 0 && WP0) ? Dpl : Dl;
+    // (it reads the layer input, and W_ih of a direction, through one buffer
+    // resource each, so these must lie within its 31 bits; the separate product
+    // bases its resources on each block)
     const bool fuse = persist && std::is_same<T, bf16>::value && fuse_gx(H, B) && kin % 8 == 0 && Dpl % 8 == 0 &&
-                      ldw % 8 == 0 && wih_d % 8 == 0 && ((uintptr_t)Xl & 15) == 0 && ((uintptr_t)wih & 15) == 0;
+                      ldw % 8 == 0 && wih_d % 8 == 0 && ((uintptr_t)Xl & 15) == 0 && ((uintptr_t)wih & 15) == 0 &&
+                      M * Dpl * 2 < 0x7ffffff0 && 4 * (int64_t)H * ldw * 2 < 0x7ffffff0;
     auto launch_gx = [&]() {
       if (l == 0 && WP0) {
         // bf16 with D not a multiple of 8: W_ih padded to the input's pitch

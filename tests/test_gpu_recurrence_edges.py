@@ -31,3 +31,27 @@ def test_fused_projection_with_a_partial_member(gpu_lib, monkeypatch, rows):
     monkeypatch.setenv("ADPSGD_BLSTM_FUSE_GX", "1")
     monkeypatch.setenv("ADPSGD_BLSTM_ROWS_PER_WG", rows)
     run_step_and_compare(dict(L=2, D=20, H=160, P=16, K=30, T=13, B=50), "bf16", BF16_TOL, seed=29, check_update=False)
+
+
+def test_layer_input_past_the_range_of_a_buffer_resource(gpu_lib, monkeypatch):
+    """131072 frames of 8200 features: 2.15 GB in bf16, past the 2^31 bytes that
+    one buffer resource reaches. The forward, which at this many workgroups
+    computes the projection itself where it can, gives what the separate product
+    gives, bit for bit (its resources are based on each block)."""
+    import torch
+
+    from paper_1907_05701_amd.step import LearnerStep
+
+    st = LearnerStep(L=1, D=8200, H=192, P=8, K=10, T=2, B=65536)
+    g = torch.Generator(device="cuda").manual_seed(7)
+    st.theta.copy_(torch.rand(st.theta.numel(), generator=g, device="cuda") * 0.02 - 0.01)
+    st.pack()
+    st.x.normal_(generator=g)
+    st.forward()
+    got = st.y_top.clone()
+    monkeypatch.setenv("ADPSGD_BLSTM_FUSE_GX", "0")
+    st.y_top.zero_()
+    st.forward()
+    st.check_recurrence()
+    assert torch.equal(got, st.y_top)
+    assert got[-1, -64:].float().abs().mean() > 0.05   # (near zero with an input that reads as zeros)
