@@ -79,10 +79,21 @@ __device__ __forceinline__ uint32_t lane_xor2(uint32_t v) {
 // never matches), bit 1 = bit 1 of the step number (a slot alternates
 // between steps n and n - 2), bits 2-3 = the launch's sequence number in
 // its call modulo 4 (a word can be left by one of the two launches before).
-// Readers clear the four bits, so the exchanged values are exactly the bf16
-// of h; a non-finite h (bit 14 set) reaches the other members clipped, while
-// the layer output keeps it.
+// Readers clear the four bits, so the exchanged values are exactly the bf16 of
+// h.  A NaN would be clipped to a magnitude between 1 and 2, which no h has;
+// where 64 does not divide H, readers give such a value its bit 14 back, so a
+// NaN travels on as in the per-step kernels, which ran these widths before.
+// (For the other widths it reaches the other members clipped, as it always has,
+// while the layer output keeps it: the two instructions a word cost a 21-step
+// launch at H = 512 1.5 to 5 us.)
 #define H4_TAG_BITS 0x4000400040004000ull
+template <bool NANS>
+__device__ __forceinline__ uint64_t h4_decode(uint64_t w) {
+  const uint64_t v = w & ~H4_TAG_BITS;
+  if constexpr (!NANS) return v;
+  // magnitude + 0x7F reaches bit 14 from 0x3F81 on (1.0 is 0x3F80), and no further
+  return v | ((v + 0x007F007F007F007Full) & H4_TAG_BITS);
+}
 //
 // BPTT words: four partial sums (rows 4i
 // .. 4i+3 of one unit) in a 15-bit form that frees the same bits: the bf16
@@ -347,7 +358,7 @@ __device__ __forceinline__ void gx_member(const PersistArgs& a, int d, int u0, i
 // group_meet, and does nothing if it does not run together), or one step of
 // one member after the other (ONE, see lstm_fwd_persist), with the member's
 // registers kept in a.state between its steps.
-template <int RV, bool ONE>
+template <int RV, bool NANS, bool ONE>
 __device__ __forceinline__ int fwd_pass(const PersistArgs& a, char* lds_raw, int g, int mem, int tau0, int tau1) {
   static_assert(RV == 8 || RV == 16 || RV == 32, "rows per workgroup");
   constexpr int NT = RV > 16 ? 2 : 1;   // MFMA row tiles
@@ -510,7 +521,7 @@ __device__ __forceinline__ int fwd_pass(const PersistArgs& a, char* lds_raw, int
           if (idx >= nwords) break;
           const int row = idx / wpr, wc = idx % wpr;   // units 4 wc .. 4 wc + 3
           const bool ok = rowbase + row < rend;
-          *(uint64_t*)&hl[((wc >> 1) * (R + 1) + row) * 8 + 4 * (wc & 1)] = ok ? (wv[j] & ~H4_TAG_BITS) : 0ull;
+          *(uint64_t*)&hl[((wc >> 1) * (R + 1) + row) * 8 + 4 * (wc & 1)] = ok ? h4_decode<NANS>(wv[j]) : 0ull;
         }
       }
       lds_barrier();
@@ -606,7 +617,7 @@ __device__ __forceinline__ int fwd_pass(const PersistArgs& a, char* lds_raw, int
 
 // A group that runs on this workgroup alone: every member's input projection,
 // then every member's part of each step.
-template <int RV>
+template <int RV, bool NANS>
 __device__ __attribute__((noinline)) void fwd_alone(const PersistArgs* at, lds_base_t lds, int gv, int memv) {
   char* lds_raw = (char*)lds;
   const int g = scalar(gv), mem = scalar(memv);
@@ -619,10 +630,10 @@ __device__ __attribute__((noinline)) void fwd_alone(const PersistArgs* at, lds_b
 #pragma nounroll
   for (int tau = 0; tau < a.Tn; ++tau)
 #pragma nounroll
-    for (int m = 0; m < NM; ++m) fwd_pass<RV, true>(pass_args(at), lds_raw, g, m, tau, tau + 1);
+    for (int m = 0; m < NM; ++m) fwd_pass<RV, NANS, true>(pass_args(at), lds_raw, g, m, tau, tau + 1);
 }
 
-template <int RV>
+template <int RV, bool NANS>
 __global__ __launch_bounds__(NTH) ONE_PER_CU void lstm_fwd_persist(const PersistArgs a) {
   extern __shared__ __attribute__((aligned(16))) char lds_raw[];
   const int NM = (a.H + PU - 1) / PU;
@@ -631,9 +642,9 @@ __global__ __launch_bounds__(NTH) ONE_PER_CU void lstm_fwd_persist(const Persist
   if (g >= 2 * a.NS) return;   // padding (see persist_groups)
   if (a.Tn > 1 && NM > 1) group_arrive(a.words, a.seq, g, mem, a.wait);
   if (a.Xin) gx_prologue<RV>(a, lds_raw, g & 1, mem * PU, a.b0 + (g >> 1) * RV, a.b0 + a.rows);
-  if (fwd_pass<RV, false>(a, lds_raw, g, mem, 0, a.Tn) != GROUP_ALONE) return;
+  if (fwd_pass<RV, NANS, false>(a, lds_raw, g, mem, 0, a.Tn) != GROUP_ALONE) return;
   if (threadIdx.x == 0) a.status[1] = 1;
-  fwd_alone<RV>(kernel_args<PersistArgs>(), (lds_base_t)lds_raw, g, mem);
+  fwd_alone<RV, NANS>(kernel_args<PersistArgs>(), (lds_base_t)lds_raw, g, mem);
 }
 
 // ---------------------------------------------------------------------------
@@ -1187,11 +1198,12 @@ int persist_groups(int groups, int members) {
 template <int RV, bool BWD>
 static hipError_t launch_one(PersistArgs a, hipStream_t s) {
   const void* fn;
-  if constexpr (BWD && RV < 32)
-    fn = a.H % PU ? (const void*)lstm_bwd_persist<RV, true> : (const void*)lstm_bwd_persist<RV, false>;
-  else if constexpr (BWD)
-    fn = (const void*)lstm_bwd_persist<RV, false>;
-  else fn = (const void*)lstm_fwd_persist<RV>;
+  // (widths that 64 does not divide take at most 16 rows, see persist_plan)
+  constexpr bool ODD = RV < 32;
+  if (BWD)
+    fn = ODD && a.H % PU ? (const void*)lstm_bwd_persist<RV, ODD> : (const void*)lstm_bwd_persist<RV, false>;
+  else
+    fn = ODD && a.H % PU ? (const void*)lstm_fwd_persist<RV, ODD> : (const void*)lstm_fwd_persist<RV, false>;
   return persist_launch(BWD ? "lstm_rec_bwd_persist" : "lstm_rec_fwd_persist", fn, dim3(a.NG * members(a.H)), NTH,
                         persist_lds_bytes(a.H, BWD, RV), &a, s);
 }

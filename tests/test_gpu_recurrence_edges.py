@@ -55,3 +55,29 @@ def test_layer_input_past_the_range_of_a_buffer_resource(gpu_lib, monkeypatch):
     st.check_recurrence()
     assert torch.equal(got, st.y_top)
     assert got[-1, -64:].float().abs().mean() > 0.05   # (near zero with an input that reads as zeros)
+
+
+@pytest.mark.parametrize("precision,H", [("bf16", 32), ("bf16", 96), ("bf16", 480), ("fp32", 64), ("fp32", 144)])
+def test_a_nan_reaches_every_unit_one_step_later(gpu_lib, precision, H):
+    """One unit's NaN (its forward-direction input bias) spreads through W_hh: at
+    the first step that unit alone, from the second on every unit of that
+    direction, whichever workgroup owns it; the other direction stays finite."""
+    import torch
+
+    from paper_1907_05701_amd.step import LearnerStep
+
+    D, T, B = 8, 4, 9
+    st = LearnerStep(L=1, D=D, H=H, P=8, K=10, T=T, B=B, precision=precision)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    st.theta.copy_(torch.rand(st.theta.numel(), generator=g, device="cuda") * 0.2 - 0.1)
+    unit = H - 3
+    st.theta[4 * H * D + 4 * H * H + unit] = float("nan")   # b_ih of gate i
+    st.pack()
+    st.x.normal_(generator=g)
+    st.forward()
+    st.check_recurrence()
+    bad = torch.isnan(st.y_top.float())
+    want = torch.zeros_like(bad)
+    want[0, :, unit] = True
+    want[1:, :, :H] = True
+    assert torch.equal(bad, want)
