@@ -669,8 +669,8 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
                         persist_bwd_dy_partials_ok(H, B, lo.T);
   // (float32 holds the bias sums for that launch too)
   const bool hold_bias = dy_parts || (!lp && defer);
-  // the row block of the persistent BPTT's bias partials
-  const int rows_wg = lp ? persist_rows_per_workgroup(H, B) : persist32_rows_per_workgroup(H, B);
+  // rows of the persistent BPTT's bias partials
+  const int bias_rows = lp ? persist_bias_rows(H, B) : (int)cdiv(B, persist32_rows_per_workgroup(H, B));
   ReduceGroup pending_dy;   // the held dX reduction the next BPTT takes over
   pending_dy.n = 0;
   ColSumJob bias_jobs[MAX_LAYERS];
@@ -762,7 +762,7 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
         g[2] = F32Job{opnd(DA, 8 * H, 8 * H, M), Bw, M, Dl, 8 * H, 1, lo.sp_dX[l], dst_dx, Dl, 0, part};
       // db_ih = db_hh = sum over frames of da, from the BPTT kernel's
       // per-row-block partials, in a reduction launch
-      const int dbp_rows = done ? (int)cdiv(B, rows_wg) : Tn * (int)cdiv(B, 16);
+      const int dbp_rows = done ? bias_rows : Tn * (int)cdiv(B, 16);
       const ColSumJob cs{DBPl, dbp_rows, 2, 4 * H, 8 * H, 4 * H,
                          grad + lo.bih[l][0], grad + lo.bhh[l][0], lo.bih[l][1] - lo.bih[l][0]};
       const bool with_db = step_fused && (lp || done) && colsum_job_ok(cs);
@@ -810,7 +810,7 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
     if (!db_done) {
       if (step_fused)
         colsum_parts("colsum_db", ss, DBPl,
-                     done ? (int)cdiv(B, rows_wg) : Tn * (int)cdiv(B, 16), 8 * H, 4 * H,
+                     done ? bias_rows : Tn * (int)cdiv(B, 16), 8 * H, 4 * H,
                      lo.bih[l][1] - lo.bih[l][0], grad + lo.bih[l][0], grad + lo.bhh[l][0]);
       else
         colsum<T>("colsum_db", s, DA, M, 8 * H, 8 * H, csp, 4 * H, lo.bih[l][1] - lo.bih[l][0],

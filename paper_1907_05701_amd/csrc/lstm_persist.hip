@@ -1040,7 +1040,7 @@ __device__ __forceinline__ int bwd_pass(const PersistArgs& a, char* lds_raw, int
       float sum = 0.f;
 #pragma unroll
       for (int r = 0; r < RV / RPT; ++r) sum += red[r * PU * 4 + tid];
-      a.DBP[(int64_t)(rowbase / RV) * 8 * H + (int64_t)d * 4 * H + (int64_t)(tid & 3) * H + u0 + (tid >> 2)] = sum;
+      a.DBP[(int64_t)s * 8 * H + (int64_t)d * 4 * H + (int64_t)(tid & 3) * H + u0 + (tid >> 2)] = sum;
     }
   }
   if constexpr (ONE) __syncthreads();   // the next pass reuses the LDS
@@ -1208,30 +1208,36 @@ static hipError_t launch_one(PersistArgs a, hipStream_t s) {
                         persist_lds_bytes(a.H, BWD, RV), &a, s);
 }
 
-// Rows per workgroup and rows per launch: 8 rows (half of each MFMA tile
-// idle, half the cell work and exchange per workgroup) when the batch fits
-// the chip that way (one workgroup per CU), else 16; more rows by chunking.
-// False if no launch fits.
-static bool persist_plan(int H, int B, int* RVo, int* chunko) {
-  const int NM = members(H);
-  const int max_ns = std::min(persist_max_wg() / (2 * NM), PERSIST_MAX_SLICES);
-  if (max_ns < 1) return false;
-  // (float32 partial sums, H % 64 != 0: at most 16 rows, the gather of more
-  // spills)
-  const int most = H % PU ? 16 : 32;
-  int RV = (B + 7) / 8 <= max_ns ? 8 : (B + 15) / 16 <= max_ns ? 16 : most;
-  // ADPSGD_BLSTM_ROWS_PER_WG=16 or 32 keeps that many rows per workgroup at
-  // any batch (fewer workgroups at small batches, for measurements and tests)
+// Rows per workgroup of a launch over `rows` rows: the fewest that take them all
+// at one workgroup per CU, 8 (half of each MFMA tile idle, half the cell work
+// and exchange per workgroup), 16, or 32 (the most; 16 where 64 does not divide
+// H: the gather of more rows' float32 partial sums spills).
+// ADPSGD_BLSTM_ROWS_PER_WG=16 or 32 keeps that many at any batch (fewer
+// workgroups at small batches, for measurements and tests).
+static int max_slices(int H) { return std::min(persist_max_wg(), 256) / (2 * members(H)); }
+static int launch_rows(int H, int rows) {
+  const int most = H % PU ? 16 : 32, ns = max_slices(H);
   if (const char* e = getenv("ADPSGD_BLSTM_ROWS_PER_WG"))
-    if (atoi(e) == 16 || atoi(e) == 32) RV = std::min(atoi(e), most);
+    if (atoi(e) == 16 || atoi(e) == 32) return std::min(atoi(e), most);
+  return (rows + 7) / 8 <= ns ? 8 : (rows + 15) / 16 <= ns ? 16 : most;
+}
+// Rows per workgroup of a batch's largest launches, and rows per launch (the
+// last one takes what is left, with rows per workgroup of its own: 520
+// sequences at H = 512, T = 21 run as 512 + 8, forward 322 us a layer with 32
+// rows per workgroup in both, 229 now).  False if no launch fits.
+static bool persist_plan(int H, int B, int* RVo, int* chunko) {
+  if (max_slices(H) < 1) return false;
+  const int RV = launch_rows(H, B);
   *RVo = RV;
-  *chunko = std::min(B, max_ns * RV);
+  *chunko = std::min(B, max_slices(H) * RV);
   return true;
 }
 
-int persist_rows_per_workgroup(int H, int B) {
+int persist_bias_rows(int H, int B) {
   int RV, chunk;
-  return persist_plan(H, B, &RV, &chunk) ? RV : 16;
+  if (!persist_plan(H, B, &RV, &chunk)) return 0;
+  const int left = B % chunk;
+  return (int)cdiv(B - left, RV) + (left ? (int)cdiv(left, launch_rows(H, left)) : 0);
 }
 
 int persist_workgroups(int H, int B) {
@@ -1276,14 +1282,16 @@ hipError_t persist_layer(bool backward, PersistArgs a, hipStream_t s) {
     PersistArgs c = a;
     c.b0 = b0;
     c.rows = std::min(chunk, a.B - b0);
-    c.NS = (c.rows + RV - 1) / RV;
+    if (a.DBP) c.DBP = a.DBP + (int64_t)(b0 / RV) * 8 * a.H;
+    const int rv = c.rows < chunk ? launch_rows(a.H, c.rows) : RV;
+    c.NS = (c.rows + rv - 1) / rv;
     c.NG = persist_groups(2 * c.NS, members(a.H));
     // the launch's position in the call (the caller's tag numbers the layers
     // in the order the call runs them)
     c.seq = a.tag * (uint32_t)cdiv(a.B, chunk) + (uint32_t)(b0 / chunk);
     c.wait = wait;
-    const hipError_t e = RV == 8    ? (backward ? launch_one<8, true>(c, s) : launch_one<8, false>(c, s))
-                         : RV == 16 ? (backward ? launch_one<16, true>(c, s) : launch_one<16, false>(c, s))
+    const hipError_t e = rv == 8    ? (backward ? launch_one<8, true>(c, s) : launch_one<8, false>(c, s))
+                         : rv == 16 ? (backward ? launch_one<16, true>(c, s) : launch_one<16, false>(c, s))
                                     : (backward ? launch_one<32, true>(c, s) : launch_one<32, false>(c, s));
     if (e != hipSuccess) return e;
   }

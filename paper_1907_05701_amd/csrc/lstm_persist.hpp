@@ -218,7 +218,7 @@ struct PersistArgs {
   uint64_t* X;        // step-exchange words behind them (see lstm_persist.hip)
   float* state;       // registers of groups that run alone (see group_state)
   float* DBP;         // backward, optional: sums of da over each workgroup's rows and all steps
-                      // [cdiv(B, rows per workgroup)][8H] (see persist_rows_per_workgroup)
+                      // [persist_bias_rows][8H] (per launch: its first row)
   int* status;        // recurrence status block (sticky flag, see persist_status_reset)
   uint32_t tag;       // caller: the layer's position in the order the call runs the layers
   int Tn, B, H;
@@ -228,16 +228,13 @@ struct PersistArgs {
   uint32_t wait;      // ticks a member waits for its group (filled in by persist_layer)
 };
 
-// At most this many batch slices of 8, 16 or 32 rows per launch, so one
-// launch covers at most PERSIST_MAX_ROWS rows.
-#define PERSIST_MAX_SLICES 32
-#define PERSIST_MAX_ROWS (PERSIST_MAX_SLICES * 32)
 // Exchange buffer: the groups' words, then 2 slots x 2 directions x row quads x (H/64 members, rounded up) x H
 // units words of 8 bytes (the backward's partial sums: four rows per word, one
 // where 64 does not divide H; the forward uses H/4 words per row, never more).
 static inline size_t persist_xch_bytes(int B, int H) {
-  const size_t rows = B < PERSIST_MAX_ROWS ? B : PERSIST_MAX_ROWS;
   const size_t members = (H + 63) / 64;
+  size_t rows = 256 / (2 * members) * (H % 64 ? 16 : 32);   // the most of one launch on 256 CUs
+  if (rows > (size_t)B) rows = B;
   const size_t bwd = (size_t)2 * 2 * ((rows + 3) / 4) * members * H * 8 * (H % 64 ? 4 : 1);
   const size_t fwd = (size_t)2 * 2 * rows * (H / 4 > 0 ? H / 4 : 1) * 8;
   return (bwd > fwd ? bwd : fwd) + GROUP_WORDS * 8;
@@ -247,7 +244,6 @@ static inline size_t persist_state_bytes(int B, int H) {
   const size_t members = (H + 63) / 64;
   if (members < 2) return 0;
   size_t slices = (B + 7) / 8;
-  if (slices > PERSIST_MAX_SLICES) slices = PERSIST_MAX_SLICES;
   if (slices > 256 / (2 * members)) slices = 256 / (2 * members);
   return 2 * slices * members * 512 * GROUP_STATE * 4;
 }
@@ -261,9 +257,9 @@ bool persist_bwd_dy_partials_ok(int H, int B, int T);
 bool persist_supported(int H, int T);
 // Workgroups of a layer's largest launch for this H and B.
 int persist_workgroups(int H, int B);
-// Batch rows per persistent workgroup (8, 16 or 32) for this H and B: the row
-// block of the BPTT's bias partial sums (PersistArgs::DBP).
-int persist_rows_per_workgroup(int H, int B);
+// Rows of the BPTT's bias partial sums (PersistArgs::DBP): one per slice of 8,
+// 16 or 32 batch rows.
+int persist_bias_rows(int H, int B);
 // Status block (PERSIST_STATUS_BYTES at the end of the activation
 // workspace): an int flag set by any exchange wait that gives up, an int set by
 // any group that ran alone, and a tag that marks the block initialised.  Both

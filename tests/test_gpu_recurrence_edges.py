@@ -1,8 +1,9 @@
 """The bf16 persistent recurrences against the float64 oracle where their plan
 changes: a last member of 32 units (H no multiple of 64), 8, 16 and 32 rows per
-workgroup with a partial last slice, groups padded to whole XCDs or not, two
-launches per layer, and batches that 8 does not divide (the weight gradients
-read da as it lies).  The tolerance is the bf16 path's (tests/test_gpu_parity.py)."""
+workgroup with a partial last slice, groups padded to whole XCDs or not, several
+launches per layer whose last has rows per workgroup of its own, and batches
+that 8 does not divide (the weight gradients read da as it lies).  The tolerance
+is the bf16 path's (tests/test_gpu_parity.py)."""
 
 import pytest
 
@@ -12,12 +13,16 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("H,T,B", [
-    (32, 3, 1), (32, 5, 301),          # one member of 32 units; 16-row workgroups
-    (96, 4, 9), (96, 3, 530),          # two members; two launches
-    (160, 4, 203), (288, 3, 100),      # three and five members (five: groups not padded at this batch)
-    (480, 3, 130), (480, 2, 517),      # eight members: 16-row workgroups, in one launch and in three
+    (32, 3, 1), (32, 5, 301),          # one member of 32 units
+    (96, 4, 9), (96, 3, 530),          # two members; 16-row workgroups
+    (160, 4, 203), (288, 3, 100),      # three and five members (groups padded to 32)
+    (288, 3, 200), (448, 3, 137),      # five members with 50 groups, seven with 36: the last two and four on several XCDs
+    (320, 3, 850),                     # the same with 32-row workgroups, in two launches (50 groups, then 4)
+    (480, 3, 130), (480, 2, 517),      # eight members: 16-row workgroups, in one launch and in two and one of 8-row ones
+    (480, 3, 400),                     # 16-row workgroups in both launches
     (512, 3, 511), (512, 2, 61),       # 32-row workgroups with a partial quad, padded groups
-    (192, 2, 1350),                    # 32-row workgroups in two launches
+    (512, 3, 524), (512, 3, 700),      # launches of 32-row workgroups, then of 8-row and of 16-row ones
+    (192, 2, 1350), (64, 3, 300),      # 32-row workgroups, then 8-row ones; 38 slices of one member
 ], ids=lambda v: str(v))
 def test_recurrence_plan_edges(gpu_lib, H, T, B):
     run_step_and_compare(dict(L=2, D=20, H=H, P=16, K=30, T=T, B=B), "bf16", BF16_TOL, seed=23, check_update=False)
