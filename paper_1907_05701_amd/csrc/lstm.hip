@@ -390,9 +390,14 @@ static bool step_rows_32(int H, int B) { return (int64_t)(H / 16) * cdiv(B, 32) 
 // paper's shapes): the persistent kernels for both passes;
 // ADPSGD_BLSTM_RECURRENCE=per-step (or ADPSGD_BLSTM_NO_PERSIST=1) the
 // per-step kernels.  The persistent kernels need a W_hh slice that fits a
-// workgroup's registers (H up to 512).
+// workgroup's registers (H up to 512).  A forward of one step has no use for
+// W_hh at all (two layers as one launch per step / persistent, us: bf16 H = 512,
+// B = 4 25.7 / 35.2, B = 128 28.5 / 46.8; float32 H = 64 23.3 / 25.8, H = 512
+// 39.6 / 50.0); of a few more see persist_short_fwd.
 template <typename T>
-static bool use_persistent(int H, int steps, bool backward, hipStream_t s) {
+static bool use_persistent(int H, int B, int steps, bool backward, hipStream_t s) {
+  constexpr bool lp = std::is_same<T, bf16>::value;
+  if (!backward && (steps == 1 || (lp && persist_supported(H, steps) && persist_short_fwd(H, B, steps)))) return false;
   const char* off = getenv("ADPSGD_BLSTM_NO_PERSIST");
   if (off && atoi(off)) return false;
   const char* pol = getenv("ADPSGD_BLSTM_RECURRENCE");
@@ -405,7 +410,7 @@ static bool use_persistent(int H, int steps, bool backward, hipStream_t s) {
     const char* g = getenv("ADPSGD_BLSTM_GRAPH_PERSIST");
     if (g && !atoi(g)) return false;
   }
-  return std::is_same<T, bf16>::value ? persist_supported(H, steps) : persist32_supported(H);
+  return lp ? persist_supported(H, steps) : persist32_supported(H);
 }
 
 static PersistArgs persist_args(const Layout& lo, const bf16* W, char* ws, int l) {
@@ -450,16 +455,12 @@ static bool fuse_dy() {
   return !(e && e[0] == '0');
 }
 
-// Whether the persistent forward computes the input projection itself: when
-// its workgroups fill most of the chip (a launch of a few workgroups leaves
-// the projection to them alone: full model, B = 16 431 us fused, 411 as a
-// separate product; H = 320, B = 100 with 130 workgroups 415 / 402; at B = 128,
-// 256 workgroups, 1538 / 1550).  ADPSGD_BLSTM_FUSE_GX=0 or 1 forces either, for
-// comparisons (bit-identical).
-static bool fuse_gx(int H, int B) {
+// Whether the persistent forward computes the input projection itself.
+// ADPSGD_BLSTM_FUSE_GX=0 or 1 forces either, for comparisons (bit-identical).
+static bool fuse_gx(int H, int B, int T, int K) {
   const char* e = getenv("ADPSGD_BLSTM_FUSE_GX");
   if (e && (e[0] == '0' || e[0] == '1')) return e[0] == '1';
-  return persist_workgroups(H, B) >= 192;
+  return persist_fuse_gx(H, B, T, K);
 }
 
 template <typename T>
@@ -472,7 +473,7 @@ static int fwd_impl(const Layout& lo, const float* theta, const T* W, const floa
   // the recurrence status block is initialised on first use (by the
   // persistent path's exchange clear, else here); its flag is sticky until
   // blstm_recurrence_ok reads it
-  const bool persist = use_persistent<T>(H, lo.T, false, s);
+  const bool persist = use_persistent<T>(H, B, lo.T, false, s);
   bool status_cleared = false;
   if (!persist) {
     if (persist_status_init((int*)(ws + lo.SYNC), s) != hipSuccess) return blstm_check_launch("blstm_fwd");
@@ -507,7 +508,7 @@ static int fwd_impl(const Layout& lo, const float* theta, const T* W, const floa
     // (it reads the layer input, and W_ih of a direction, through one buffer
     // resource each, so these must lie within its 31 bits; the separate product
     // bases its resources on each block)
-    const bool fuse = persist && std::is_same<T, bf16>::value && fuse_gx(H, B) && kin % 8 == 0 && Dpl % 8 == 0 &&
+    const bool fuse = persist && std::is_same<T, bf16>::value && fuse_gx(H, B, lo.T, kin) && kin % 8 == 0 && Dpl % 8 == 0 &&
                       ldw % 8 == 0 && wih_d % 8 == 0 && ((uintptr_t)Xl & 15) == 0 && ((uintptr_t)wih & 15) == 0 &&
                       M * Dpl * 2 < 0x7ffffff0 && 4 * (int64_t)H * ldw * 2 < 0x7ffffff0;
     auto launch_gx = [&]() {
@@ -642,7 +643,7 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
     }
     have_wt = true;
   };
-  if (!use_persistent<T>(H, lo.T, true, s)) make_copies();
+  if (!use_persistent<T>(H, B, lo.T, true, s)) make_copies();
   // weight gradients on the side stream (bf16 per-step BPTT): layer l's bias
   // partials alternate by layer parity, so BPTT of layer l waits only for the
   // side work of l+2
@@ -651,7 +652,7 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
   if (hipStreamIsCapturing(s, &cap) != hipSuccess) { (void)hipGetLastError(); cap = hipStreamCaptureStatusActive; }
   // not under stream capture: replaying graphs with these parallel branches
   // measured far slower on MI355X than the serial graph
-  if (lp && cap == hipStreamCaptureStatusNone && !use_persistent<T>(H, lo.T, true, s))
+  if (lp && cap == hipStreamCaptureStatusNone && !use_persistent<T>(H, B, lo.T, true, s))
     side = side_stream();
   hipStream_t ss = side ? side->st : s;
   // without the side stream each layer's weight-gradient products wait
@@ -665,7 +666,7 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
   // sums, which the next BPTT adds itself (in the reduction's order) before
   // its steps; the bias sums of every layer then wait for one reduction
   // launch after the last BPTT (on per-layer bias partials)
-  const bool dy_parts = lp && defer && fuse_dy() && use_persistent<T>(H, lo.T, true, s) &&
+  const bool dy_parts = lp && defer && fuse_dy() && use_persistent<T>(H, B, lo.T, true, s) &&
                         persist_bwd_dy_partials_ok(H, B, lo.T);
   // (float32 holds the bias sums for that launch too)
   const bool hold_bias = dy_parts || (!lp && defer);
@@ -689,7 +690,7 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
     // BPTT over the chunk, both directions at once
     bool done = false, step_fused = false;
     if constexpr (!lp) {
-      if (use_persistent<T>(H, lo.T, true, s)) {
+      if (use_persistent<T>(H, B, lo.T, true, s)) {
         Persist32Args pa = persist32_args(lo, W, ws, l);
         pa.tag0 = (uint32_t)(lo.L - 1 - l);   // the backward runs the layers top-down
         pa.DA = DA; pa.DY = dY; pa.DBP = DBPl;
@@ -698,7 +699,7 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
         if (!done) (void)hipGetLastError();
         step_fused = done;
       }
-    } else if (use_persistent<T>(H, lo.T, true, s)) {
+    } else if (use_persistent<T>(H, B, lo.T, true, s)) {
       PersistArgs pa = persist_args(lo, (const bf16*)W, ws, l);
       pa.tag = (uint32_t)(lo.L - 1 - l);   // the backward runs the layers top-down
       pa.DA = (bf16*)DA; pa.DY = dY; pa.C = (float*)Cl; pa.G = (bf16*)Gl;

@@ -1233,16 +1233,26 @@ static bool persist_plan(int H, int B, int* RVo, int* chunko) {
   return true;
 }
 
+bool persist_short_fwd(int H, int B, int T) {
+  if (H % PU == 0) return false;
+  int RV, chunk;
+  if (!persist_plan(H, B, &RV, &chunk)) return false;
+  return T <= (chunk == B ? 2 : 2 * (B % chunk) > chunk || B % chunk == 0 ? 3 : 5);
+}
+
+bool persist_fuse_gx(int H, int B, int T, int K) {
+  int RV, chunk;
+  if (!persist_plan(H, B, &RV, &chunk)) return false;
+  const int64_t rows = (int64_t)T * RV;
+  if (K <= 128 && rows <= 32) return true;
+  return 2 * cdiv(chunk, RV) * members(H) >= 192 && 4 * rows >= 3 * GXR * cdiv(rows, GXR);
+}
+
 int persist_bias_rows(int H, int B) {
   int RV, chunk;
   if (!persist_plan(H, B, &RV, &chunk)) return 0;
   const int left = B % chunk;
   return (int)cdiv(B - left, RV) + (left ? (int)cdiv(left, launch_rows(H, left)) : 0);
-}
-
-int persist_workgroups(int H, int B) {
-  int RV, chunk;
-  return persist_plan(H, B, &RV, &chunk) ? 2 * (int)cdiv(chunk, RV) * members(H) : 0;
 }
 
 bool persist_bwd_dy_partials_ok(int H, int B, int T) {

@@ -255,8 +255,24 @@ bool persist_bwd_dy_partials_ok(int H, int B, int T);
 // 512: a member's 256 W_hh rows fit in its registers; the last member may own
 // 32 units); any T.
 bool persist_supported(int H, int T);
-// Workgroups of a layer's largest launch for this H and B.
-int persist_workgroups(int H, int B);
+// Whether a forward of so few steps (two or more) is faster as one launch per
+// step than with W_hh staged for the whole chunk.  At widths that 64 does not
+// divide only: the others' exchange has always run at any T.  One launch per
+// step / persistent, two layers, us: H = 480, B = 128, T = 2 43.6 / 50.8, T = 3
+// 57.2 / 55.8; where a layer takes several persistent launches later, above all
+// where the last is nearly empty: H = 224, B = 520, T = 5 94 / 106, B = 600 116 /
+// 106; H = 480, B = 300, T = 3 94 / 129, T = 4 125 / 141.
+bool persist_short_fwd(int H, int B, int T);
+// Whether the forward computes the input projection (K columns) itself.  A
+// workgroup runs it in passes of 176 rows at one workgroup per CU, so it pays
+// where the workgroups fill most of the chip and the passes are mostly full
+// (fused / separate product, us, two layers at H = 512: B = 100 (208 workgroups
+// of 8 rows) T = 2 57 / 47, T = 12 101 / 100, T = 21 139 / 147, T = 64 368 / 370;
+// B = 250 (256 of 16) T = 12 157 / 143, T = 21 222 / 231; with 104 workgroups at
+// H = 256, B = 100, T = 40 196 / 184), and where there is next to nothing to
+// multiply (one layer of 40 or 128 columns, T = 2, B = 4 to 100: 16.2-19.5 /
+// 17.8-19.7; T = 8 25-32 / 25-30).
+bool persist_fuse_gx(int H, int B, int T, int K);
 // Rows of the BPTT's bias partial sums (PersistArgs::DBP): one per slice of 8,
 // 16 or 32 batch rows.
 int persist_bias_rows(int H, int B);

@@ -19,7 +19,7 @@ pytestmark = pytest.mark.gpu
     (288, 3, 200), (448, 3, 137),      # five members with 50 groups, seven with 36: the last two and four on several XCDs
     (320, 3, 850),                     # the same with 32-row workgroups, in two launches (50 groups, then 4)
     (480, 3, 130), (480, 2, 517),      # eight members: 16-row workgroups, in one launch and in two and one of 8-row ones
-    (480, 3, 400),                     # 16-row workgroups in both launches
+    (480, 6, 400),                     # 16-row workgroups in both launches (fewer steps run one launch each)
     (512, 3, 511), (512, 2, 61),       # 32-row workgroups with a partial quad, padded groups
     (512, 3, 524), (512, 3, 700),      # launches of 32-row workgroups, then of 8-row and of 16-row ones
     (192, 2, 1350), (64, 3, 300),      # 32-row workgroups, then 8-row ones; 38 slices of one member
