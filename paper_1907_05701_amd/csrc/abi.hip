@@ -187,9 +187,11 @@ int make_layout(const blstm_dims* d, Layout* lo) {
   L.WP0_bytes = es == 2 && d->D % 8 != 0 ? (size_t)2 * 4 * H * L.Dp0 * es : 0;
   L.WP0 = a; a = align256(a + L.WP0_bytes);
   // da [M][8H], one per layer (the weight gradients of every layer run after
-  // the last BPTT)
+  // the last BPTT); the top layer's in the forward's input projection, which
+  // the backward does not read
   L.da_bytes = align256((size_t)M * 8 * H * es);
-  L.DA = a; a += (size_t)d->L * L.da_bytes;
+  for (int l = 0; l < d->L - 1; ++l) { L.DA[l] = a; a += L.da_bytes; }
+  L.DA[d->L - 1] = L.GX;
   // per-step 16-row partials (per-step BPTT) or per-workgroup partials over
   // all steps (persistent BPTT)
   // (8-row workgroups in bf16, 4-row ones in float32)

@@ -79,7 +79,7 @@ struct Layout {
   int64_t Wih[MAX_LAYERS][2], Whh[MAX_LAYERS][2], bih[MAX_LAYERS][2], bhh[MAX_LAYERS][2];
   int64_t Wl, bl, Ws, bs;
   // act_ws byte offsets
-  size_t X0, Y[MAX_LAYERS], G[MAX_LAYERS], C[MAX_LAYERS], GX, DYa, DYb, DC, WT, DA, DBP, CSP, SKP, SYNC, XCH, GST;
+  size_t X0, Y[MAX_LAYERS], G[MAX_LAYERS], C[MAX_LAYERS], GX, DYa, DYb, DC, WT, DA[MAX_LAYERS], DBP, CSP, SKP, SYNC, XCH, GST;
   size_t WP0, WP0_bytes;   // bf16 with D % 8 != 0: layer-0 W_ih padded to Dp0 columns (else 0 bytes)
   size_t da_bytes, dbp_bytes;   // one layer's da / bias partials
   size_t act_bytes;

@@ -679,7 +679,7 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
   const float* dY = dytop;
   for (int l = lo.L - 1; l >= 0; --l) {
     const int par = side ? (l & 1) : 0;
-    T* DA = (T*)(ws + lo.DA + l * lo.da_bytes);
+    T* DA = (T*)(ws + lo.DA[l]);
     float* DBPl = (float*)(ws + lo.DBP + (hold_bias ? l : par) * lo.dbp_bytes);
     if (side && l + 2 < lo.L) (void)hipStreamWaitEvent(s, side->dw_done[l + 2], 0);
     const T* Xl = l == 0 ? (const T*)(ws + lo.X0) : (const T*)(ws + lo.Y[l - 1]);
