@@ -16,6 +16,7 @@ pytestmark = pytest.mark.gpu
     (128, 2, 1030),                                    # one member, 8-row slices, two launches
     (144, 3, 6), (240, 5, 130), (256, 3, 270),         # 64-unit members: partial last member, 4 and 8 rows, two launches
     (272, 1, 3), (272, 4, 33), (512, 3, 62), (512, 2, 130),   # 32-unit members: 4, 8 and 16 rows, two launches
+    (288, 3, 52), (432, 3, 33),                        # nine members with 26 groups, fourteen with 18: the last two on several XCDs
 ], ids=lambda v: str(v))
 def test_float32_recurrence_plan_edges(gpu_lib, H, T, B):
     run_step_and_compare(dict(L=2, D=24, H=H, P=16, K=30, T=T, B=B), "fp32", FP32_TOL, seed=17, check_update=False)

@@ -28,14 +28,15 @@ def test_recurrence_plan_edges(gpu_lib, H, T, B):
     run_step_and_compare(dict(L=2, D=20, H=H, P=16, K=30, T=T, B=B), "bf16", BF16_TOL, seed=23, check_update=False)
 
 
-@pytest.mark.parametrize("rows", ["8", "16", "32"])
-def test_fused_projection_with_a_partial_member(gpu_lib, monkeypatch, rows):
+@pytest.mark.parametrize("rows,H", [("8", 160), ("16", 160), ("32", 192)])
+def test_fused_projection_with_a_partial_member(gpu_lib, monkeypatch, rows, H):
     """The forward computes the input projection itself (a choice made by the
-    number of workgroups otherwise): same tolerance with a last member of 32
-    units, at each number of rows per workgroup."""
+    number of workgroups and steps otherwise): same tolerance with a last member
+    of 32 units, at each number of rows per workgroup that such widths take, and
+    with whole members at 32 rows."""
     monkeypatch.setenv("ADPSGD_BLSTM_FUSE_GX", "1")
     monkeypatch.setenv("ADPSGD_BLSTM_ROWS_PER_WG", rows)
-    run_step_and_compare(dict(L=2, D=20, H=160, P=16, K=30, T=13, B=50), "bf16", BF16_TOL, seed=29, check_update=False)
+    run_step_and_compare(dict(L=2, D=20, H=H, P=16, K=30, T=13, B=50), "bf16", BF16_TOL, seed=29, check_update=False)
 
 
 def test_layer_input_past_the_range_of_a_buffer_resource(gpu_lib, monkeypatch):
