@@ -321,7 +321,9 @@ __global__ __launch_bounds__(WM * WN * 64, (KcOcc<BM, BN, WM, WN, STAGES, BK>::v
 // must be finite (ds holds zeros there).
 static inline bool kc_operand_ok(const Opnd& o, int64_t K, bool kc) {
   const bool plain = o.ilH == 0 && o.ld % 8 == 0 && o.zstride % 8 == 0 && ((uintptr_t)o.base & 15) == 0;
-  if (kc) return plain && o.seg == 0 && o.ext >= rup(K, 8);
+  // (a block's rows, up to 192 of a K-contiguous operand, lie within one
+  // buffer resource's 31 bits; 256-row blocks: kc_plan)
+  if (kc) return plain && o.seg == 0 && o.ext >= rup(K, 8) && 192 * o.ld * 2 < 0x7ffffff0;
   const bool segok = o.seg == 0 || (o.seg % 64 == 0 && K <= 2 * o.seg && o.segstride % 8 == 0);
   return plain && o.rows >= K && o.ext % 8 == 0 && segok;
 }
@@ -425,7 +427,7 @@ struct KcPlan {
 // by the estimate above.
 static inline KcPlan kc_plan(int64_t M, int64_t N, int64_t K, int batches, int small_splits) {
   KcPlan best{false, small_splits};
-  if (M < 192 || N < 192) return best;
+  if (M < 192 || N < 192 || 256 * rup(K, 8) * 2 >= 0x7ffffff0) return best;   // (rows of up to K elements within 31 bits)
   const int64_t kt = cdiv(K, 64);
   const double elems = (double)batches * (double)M * (double)N;
   double lim = 0.95 * (kc_us_small(cdiv(M, 128) * cdiv(N, 128) * batches * small_splits, cdiv(kt, small_splits)) +
