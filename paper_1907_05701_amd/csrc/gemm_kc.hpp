@@ -383,8 +383,10 @@ typedef KcCfg<128, 128, 2, 4, 2> KcTile;
 typedef KcCfg<192, 128, 2, 4, 2> KcTileTall;
 // 64-row blocks (48 KB, three per CU) for products with at most one 128x128
 // block per CU: twice the workgroups, each with three quarters of the bytes
-// per k-tile (a launch this small is bound by the 64 bytes per clock that one
-// CU takes in).  Measured 128x128 / 64x128: the input projection of 336 frames
+// per k-tile.  What bounds a launch this small is the latency of its two-stage
+// ring: one k-tile is in flight while another is multiplied, about 0.8 us per
+// 64-deep k-tile at one workgroup per CU (its 24 KB would take 0.16 us at the 64
+// bytes per clock of a CU).  Measured 128x128 / 64x128: the input projection of 336 frames
 // at 1024 wide (96 blocks) 16.2 / 12.6 us, weight gradients of 320 cells over
 // 3700 frames (200 blocks) 49 / 40; with 504 blocks (dX at 2688 frames) 33 / 41.
 typedef KcCfg<64, 128, 2, 4, 2> KcTileLow;

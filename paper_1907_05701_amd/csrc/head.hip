@@ -691,8 +691,9 @@ __global__ __launch_bounds__(512) void logits_block_kernel(const LogitsArgs a) {
     issue(j + 4);
     if constexpr (PASS == 1) combine(j - 1);
     // the epilogue's wave goes first where both waves of a SIMD can issue:
-    // its chain is the longer one (a pass over 2688 frames 73.8 -> 69.9 and
-    // 84.3 -> 80.8 us, over 65536 frames 1593 -> 1540 and 1820 -> 1790)
+    // its chain is the longer one (a pass over 2688 frames 61.2 -> 58.9 and
+    // 66.3 -> 64.1 us, one card in turn; over 65536 frames 1593 -> 1540 and
+    // 1820 -> 1790 on another)
     if (product_first) {
       product(j + 1, nxt);
       if constexpr (PASS == 2) frame_data(j + 1, Ln, ln);

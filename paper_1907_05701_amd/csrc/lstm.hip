@@ -821,7 +821,8 @@ static int bwd_impl(const Layout& lo, const T* W, char* ws, const T* ytop, const
     // dX_l = sum_d da_d W_ih[d]  (the gradient reaching the layer below)
     if (!dx_done) {
       const Opnd A = opnd(DA, 8 * H, 8 * H, M);
-      gemm_f32<T, true, false, V, V>("gemm_dx", s, A, Bw, M, Dl, 8 * H, 1, lo.sp_dX[l], dst_dx, Dl, 0, part, nullptr, 0, lo.big_dX[l]);
+      gemm_f32<T, true, false, V, V>("gemm_dx", s, A, Bw, M, Dl, 8 * H, 1, lo.sp_dX[l], dst_dx, Dl, 0, part, nullptr, 0,
+                                     lo.big_dX[l]);
     }
     if (l > 0) dY = dst_dx;
   }

@@ -2,10 +2,10 @@
 // of one layer, for both directions at once, and each workgroup keeps its
 // slice of W_hh in registers for the whole chunk.
 //
-// Work split.  The batch is cut into slices of RV rows (8 or 16 when all the
-// batch's slices of that size fit one launch at one workgroup per CU, else
-// 32: persist_plan), each on 16-row MFMA tiles; a group of NM = ceil(H/64) workgroups ("members") owns one (direction, slice)
-// pair, and member m owns hidden units [64m, 64m + 64), i.e. 256 gate rows
+// Work split.  The batch is cut into slices of RV rows (8, 16 or 32: launch_rows),
+// each on 16-row MFMA tiles; a group of NM = ceil(H/64) workgroups ("members")
+// owns one (direction, slice) pair, and member m owns hidden units
+// [64m, 64m + 64), i.e. 256 gate rows
 // of W_hh (256 KB at H = 512: 128 VGPRs in each of the workgroup's 8
 // waves).  Eight members per group instead of sixteen halves the chip-wide
 // exchange volume of every step; at the paper's B = 128 a launch takes 256
@@ -336,7 +336,8 @@ __device__ __forceinline__ void gx_member(const PersistArgs& a, int d, int u0, i
     for (int rr = 0; rr < 4; ++rr) {
       const int m = m0 + fc * 4 + rr, ro = m % RV;
       if (m < rows && rowbase + ro < rend && wok)
-        a.Gx[((int64_t)(m / RV) * B + rowbase + ro) * 8 * H + (int64_t)d * 4 * H + (n >> 6) * H + un] = (bf16)(acc[rr] + bv);
+        a.Gx[((int64_t)(m / RV) * B + rowbase + ro) * 8 * H + (int64_t)d * 4 * H + (n >> 6) * H + un] =
+            (bf16)(acc[rr] + bv);
     }
   }
   __syncthreads();
@@ -391,7 +392,8 @@ __device__ __forceinline__ int fwd_pass(const PersistArgs& a, char* lds_raw, int
     for (int p = 0; p < 2; ++p) {
 #pragma unroll
       for (int q = 0; q < 16; ++q) {
-        const int ins = q * 8 + (w & 7);            // one instruction fills rows 2 ins, 2 ins + 1 (w < 8: said for the masks)
+        // one instruction fills rows 2 ins, 2 ins + 1 (w < 8: said, it shortens the masks)
+        const int ins = q * 8 + (w & 7);
         const int lr = ins * 2 + (lane >> 5);
         const int c = (lane & 31) ^ (lr & 15);      // chunk held by this lane's slot
         const int un = u0 + ((lr >> 4) & 3) * 16 + (lr & 15), k = p * (HP / 2) + c * 8;

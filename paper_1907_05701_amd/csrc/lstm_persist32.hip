@@ -516,8 +516,8 @@ struct Plan32 {
 // thread's cells and splits the products' k over all waves); else members as
 // large as the registers allow, 64 units up to 256 cells, 32 above.  Slices of
 // 4 rows while they all fit the chip at one workgroup per CU, then of 8, then
-// of 16 (32-unit members only: the cell registers of wider ones spill), in as
-// many launches as it takes.
+// of 16 (32-unit members only: the cell registers of wider ones spill more; of
+// these the backward spills 18 registers), in as many launches as it takes.
 static bool plan32(int H, int B, Plan32* p) {
   const int cus = std::min(persist_max_wg(), 256);   // the exchange buffer is sized for 256
   p->ncb = H <= 32 ? 2 : H <= 64 ? 4 : H <= 128 ? 8 : H <= 256 ? 4 : 2;
